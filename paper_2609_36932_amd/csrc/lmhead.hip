@@ -45,7 +45,9 @@ constexpr int kBM = 256, kBN = 256;
 
 // MODE_DWT: the bf16 dW GEMM computed transposed, dW^T = Bd E (rows = hidden columns, cols =
 // vocab rows, K = tokens), so that it runs on the 8-wavefront engine with E as a K-major B
-enum GemmMode { MODE_FWD = 0, MODE_DH = 1, MODE_DW = 2, MODE_DWT = 3 };
+// MODE_DHT: the bf16 dhidden GEMM of small calls, which reads W itself (K-major, K = vocab) instead
+// of a transposed copy and can cut its long K into parts (launch_bwd_direct)
+enum GemmMode { MODE_FWD = 0, MODE_DH = 1, MODE_DW = 2, MODE_DWT = 3, MODE_DHT = 4 };
 
 // wavefront geometry of the 256 x 256 block tile: every bf16 GEMM runs 8 wavefronts (two per
 // SIMD) of 128 x 64 on 16 x 16 x 32 MFMAs; every float32 GEMM runs 4 wavefronts of 128 x 128
@@ -105,6 +107,8 @@ struct GemmParams {
   const int32_t* redo_blk;  // [nnb] token blocks to evaluate again (store_e == 2)
   const int32_t* redo_any;  // nonzero iff some token block of the slab is marked
   // ---- DH epilogue
+  int32_t ksplit;           // DHT: parts of K (1: none)
+  float* part;              // DHT with ksplit > 1: [ksplit][M][d] float32 sums of each part
   void* dH;                 // [.., d] at slab offset
   int32_t dH_bf16;
   const float* cslab;       // [slab]
@@ -193,10 +197,12 @@ typedef __attribute__((address_space(3))) void lds_void_t;
 // swizzle is applied on the global side (each lane loads the chunk that belongs in its slot).
 template <int MODE>
 __device__ __forceinline__ void mainloop_bf16_dma(const GemmParams& p, int m0, int n0,
-                                                  f32x4_t (&acc)[8][4], uint16_t* smem) {
+                                                  f32x4_t (&acc)[8][4], uint16_t* smem,
+                                                  int kt0 = 0, int nkt = 0) {
   constexpr int BK = 64;
   constexpr int TILE = kBM * BK;  // elements per operand per stage
-  constexpr bool BKM = MODE == MODE_DWT;  // B stored K-major (B[n][k] at k * ldb + n)
+  constexpr bool DHT = MODE == MODE_DHT;
+  constexpr bool BKM = MODE == MODE_DWT || DHT;  // B stored K-major (B[n][k] at k * ldb + n)
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 2, wn = wave & 3;
@@ -218,7 +224,9 @@ __device__ __forceinline__ void mainloop_bf16_dma(const GemmParams& p, int m0, i
       // n-chunk that belongs there (slot = chunk ^ kmaj_swz(k))
       const int k = wave * 8 + 2 * j + (lane >> 5);
       const int swz = ((k & 3) << 1) | (((k >> 3) & 1) << 3);
-      brow[j] = int64_t(k) * p.ldb + n0 + (((lane & 31) ^ swz) << 3);
+      const int n = n0 + (((lane & 31) ^ swz) << 3);
+      // (W's rows end at N: columns past it load a valid chunk; their results are never stored)
+      brow[j] = DHT ? int64_t(min(n, p.N - 8)) : int64_t(k) * p.ldb + n;
     }
   }
   if constexpr (!BKM) {
@@ -275,9 +283,11 @@ __device__ __forceinline__ void mainloop_bf16_dma(const GemmParams& p, int m0, i
     }
   };
   const int K = p.K;
-  const int nk = (K + BK - 1) / BK;
-  const bool ktail = (K % BK) != 0;
+  // (DHT: tiles kt0 .. kt0 + nkt - 1 of K, which is padded to whole tiles)
+  const int nk = DHT ? nkt : (K + BK - 1) / BK;
+  const bool ktail = !DHT && (K % BK) != 0;
   auto issue = [&](int kt, int stage) {
+    if constexpr (DHT) kt += kt0;
     // clamp the chunk so a partial last tile never reads past the end of a row
     const int kc0 = min(kt * BK + gch[0] * 8, K - 8);
     const int kc1 = min(kt * BK + gch[1] * 8, K - 8);
@@ -288,7 +298,12 @@ __device__ __forceinline__ void mainloop_bf16_dma(const GemmParams& p, int m0, i
       const int kc = (j & 1) ? kc1 : kc0;
       __builtin_amdgcn_global_load_lds(Ag + arow[j] + kc, (lds_void_t*)(sa + j * 8 * BK), 16, 0, 0);
       // (K-major B: k-rows 8 wave + 2 j, + 1 start at the same LDS offset as rows 32 wave + 8 j)
-      const uint16_t* bsrc = BKM ? Bg + brow[j] + int64_t(kt) * BK * p.ldb : Bg + brow[j] + kc;
+      const uint16_t* bsrc;
+      if constexpr (DHT)  // vocab rows past the end load the last one (their exp-logits are 0)
+        bsrc = Bg + brow[j] +
+               int64_t(min(kt * BK + wave * 8 + 2 * j + (lane >> 5), p.Vreal - 1)) * p.ldb;
+      else
+        bsrc = BKM ? Bg + brow[j] + int64_t(kt) * BK * p.ldb : Bg + brow[j] + kc;
       __builtin_amdgcn_global_load_lds(bsrc, (lds_void_t*)(sb + j * 8 * BK), 16, 0, 0);
     }
   };
@@ -786,6 +801,28 @@ __device__ __forceinline__ void dh_epilogue_bf16(const GemmParams& p, int m0, in
     }
 }
 
+// One part of a dhidden tile whose K is cut: the plain float32 sums.
+__device__ __forceinline__ void dh_part_epilogue_bf16(const GemmParams& p, int m0, int n0, int s,
+                                                      f32x4_t (&acc)[8][4]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int wm = wave >> 2, wn = wave & 3;
+  const int g = lane >> 4, c = lane & 15;
+  float* out = p.part + int64_t(s) * p.M * p.d;
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int t = m0 + wm * 128 + 16 * i + 4 * g + q;
+      if (t < p.M) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int n = n0 + wn * 64 + 16 * j + c;
+          if (n < p.N) out[int64_t(t) * p.d + n] = acc[i][j][q];
+        }
+      }
+    }
+}
+
 // Epilogue of the bf16 dW GEMM computed transposed (C' = Bd E on the 16 x 16 layout: acc[i][j]
 // holds hidden columns n = wm*128 + 16 i + 4 (l / 16) + q of vocab row v = wn*64 + 16 j + l % 16):
 // each lane owns 4 consecutive n of one dW row and moves them as one 16-byte access.
@@ -1048,6 +1085,65 @@ void lm_bwd_kernel(const GemmParams q, const GemmParams r) {
     tile_coords<MODE_DWT>(mb, nb, r.nmb, r.nnb, b - nh, r.group);
     mainloop_bf16_dma<MODE_DWT>(r, mb * kBM, nb * kBN, acc, smem);
     dwt_epilogue_bf16(r, mb * kBM, nb * kBN, acc);
+  }
+}
+
+// The same two GEMMs for calls of few tokens (direct_dh): dhidden reads W itself, K-major, with
+// K cut into q.ksplit parts.  With few tokens there are few dhidden tiles but each has the whole
+// vocabulary as K: one block per tile is a chain of V / 64 steps of ~1.7 us on a handful of
+// compute units (12 of 256 at 507 tokens, d = 1536).  A part's float32 sums go to q.part and
+// dh_reduce_kernel adds them in part order.
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void lm_bwd_direct_kernel(const GemmParams q, const GemmParams r) {
+  __shared__ __attribute__((aligned(16))) char smem_raw[SmemBytes<uint16_t>::value];
+  uint16_t* smem = reinterpret_cast<uint16_t*>(smem_raw);
+  const int nt = q.nmb * q.nnb, nh = nt * q.ksplit;
+  const int b = blockIdx.x;
+  int mb, nb;
+  f32x4_t acc[8][4];
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+  if (b < nh) {
+    const int s = b / nt;
+    tile_coords<MODE_DH>(mb, nb, q.nmb, q.nnb, b % nt, q.group);
+    const int nk = q.K / 64;
+    const int k0 = int(int64_t(nk) * s / q.ksplit), k1 = int(int64_t(nk) * (s + 1) / q.ksplit);
+    mainloop_bf16_dma<MODE_DHT>(q, mb * kBM, nb * kBN, acc, smem, k0, k1 - k0);
+    if (q.ksplit > 1) dh_part_epilogue_bf16(q, mb * kBM, nb * kBN, s, acc);
+    else dh_epilogue_bf16(q, mb * kBM, nb * kBN, acc);
+  } else {
+    tile_coords<MODE_DWT>(mb, nb, r.nmb, r.nnb, b - nh, r.group);
+    mainloop_bf16_dma<MODE_DWT>(r, mb * kBM, nb * kBN, acc, smem);
+    dwt_epilogue_bf16(r, mb * kBM, nb * kBN, acc);
+  }
+}
+
+// dH[t] = -c_t sum_s part[s][t], parts added in order; 4 columns per thread (d is a multiple of 8)
+__global__ __launch_bounds__(256) void dh_reduce_kernel(const float* __restrict__ part,
+                                                        int32_t ksplit, int32_t Tc, int32_t d,
+                                                        const float* __restrict__ cslab,
+                                                        void* __restrict__ dH, int32_t dH_bf16) {
+  const int64_t n4 = int64_t(Tc) * (d / 4);
+  const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
+  if (i >= n4) return;
+  const f32x4_t* p4 = reinterpret_cast<const f32x4_t*>(part) + i;
+  f32x4_t a = p4[0];
+#pragma unroll 4
+  for (int s = 1; s < ksplit; ++s) a += p4[int64_t(s) * n4];
+  const float c = -cslab[i / (d / 4)];
+  if (reinterpret_cast<uintptr_t>(dH) & 15u) {  // a caller's dhidden aligned to its elements only
+    for (int e = 0; e < 4; ++e) {
+      if (dH_bf16) static_cast<uint16_t*>(dH)[4 * i + e] = f32_to_bf16(c * a[e]);
+      else static_cast<float*>(dH)[4 * i + e] = c * a[e];
+    }
+  } else if (dH_bf16) {
+    const uint32_t lo = uint32_t(f32_to_bf16(c * a[0])) | uint32_t(f32_to_bf16(c * a[1])) << 16;
+    const uint32_t hi = uint32_t(f32_to_bf16(c * a[2])) | uint32_t(f32_to_bf16(c * a[3])) << 16;
+    static_cast<uint2*>(dH)[i] = make_uint2(lo, hi);
+  } else {
+    static_cast<f32x4_t*>(dH)[i] = f32x4_t{c * a[0], c * a[1], c * a[2], c * a[3]};
   }
 }
 
@@ -1444,6 +1540,77 @@ static int launch_bwd(GemmParams q, GemmParams r, double flops, hipStream_t stre
   return FASTRL_OK;
 }
 
+// Calls of at most kDirectTokens tokens read W itself in dhidden (MODE_DHT): the transposed copy
+// of W, built per call (0.39 ms at 7B, 0.16 ms at d = 1536), costs more there than the
+// transposing LDS reads do, and K can be cut.  Measured, transposed copy -> W itself, us a call
+// with both gradients: d = 1536 (V = 151936) 507 tokens 4373 -> 1381, 2048 5165 -> 2764, 8192
+// 9837 -> 9749, 16384 18787 -> 18724; d = 3584 (V = 152064) 2048 6607 -> 6121, 8192 21271 ->
+// 20986, 16384 41628 -> 40899, 32768 82320 -> 83281, 131072 330.4 -> 333.6 ms; d = 2048
+// (V = 100000) 27000 27029 -> 27136.
+constexpr int64_t kDirectTokens = 20480;
+constexpr int kMaxKSplit = 32;
+
+static bool direct_dh(const fastrl_loss_args& a) {
+  return a.dtype == FASTRL_BF16 && a.dhidden != nullptr && a.T <= kDirectTokens;
+}
+
+// Parts of K for the dhidden tiles of a Tc-token slab: the count whose estimated time is least,
+// in K steps of 64 (~1.66 us each on a compute unit of its own).  The launch lasts at least as
+// long as its dhidden rounds (parts x tiles over 256 compute units, each K / parts plus ~6 steps
+// of start and end) and as its total work spread evenly (a dW tile: its K plus ~9 steps); parts
+// add their float32 sums' traffic (written and read at ~5 TB/s).
+static int dh_ksplit(int32_t Tc, int32_t d, int32_t V, bool dw) {
+  const double nt = double((Tc + kBM - 1) / kBM) * double((d + kBN - 1) / kBN);
+  const double nk = double((V + 63) / 64);
+  const double wt = dw ? double((V + kBN - 1) / kBN) * double((d + kBM - 1) / kBM) : 0.0;
+  const double wk = double((Tc + kBN - 1) / kBN) * 4.0 + 9.0;
+  int best = 1;
+  double best_t = 0.0;
+  for (int s = 1; s <= kMaxKSplit && double(s) * 8.0 <= nk; ++s) {
+    const double part = nk / s + 6.0;
+    const double rounds = std::ceil(nt * s / 256.0) * part;
+    const double even = (nt * s * part + wt * wk) / 256.0 + (dw ? wk : 0.0);
+    double t = std::max(rounds, even);
+    if (s > 1) t += double(s) * Tc * d * 8.0 / 5e12 / 1.66e-6;
+    if (s == 1 || t < best_t) {
+      best = s;
+      best_t = t;
+    }
+  }
+  return best;
+}
+
+static int launch_bwd_direct(GemmParams q, GemmParams r, bool dw, double flops,
+                             hipStream_t stream) {
+  q.nmb = int((q.M + kBM - 1) / kBM);
+  q.nnb = int((q.N + kBN - 1) / kBN);
+  r.nmb = dw ? int((r.M + kBM - 1) / kBM) : 0;
+  r.nnb = dw ? int((r.N + kBN - 1) / kBN) : 0;
+  q.group = tile_group(MODE_DH, q.K, q.nnb);
+  r.group = tile_group(MODE_DWT, r.K, r.nnb);
+  const int64_t nh = int64_t(q.nmb) * q.nnb * q.ksplit, nw = int64_t(r.nmb) * r.nnb;
+  if (nh + nw == 0) return FASTRL_OK;
+  FR_CHECK_ARG(nh + nw < (int64_t(1) << 31), FASTRL_ERR_UNSUPPORTED, "backward GEMMs: grid too large");
+  FR_CHECK_ARG(q.K % 64 == 0 && q.K <= q.lda && q.ldb % 8 == 0 && q.N >= 8 && q.ksplit >= 1 &&
+                   q.ksplit * 64 <= q.K && (q.ksplit == 1 || q.part),
+               FASTRL_ERR_UNSUPPORTED, "direct dhidden GEMM: unsupported shape");
+  FR_CHECK_ARG(!dw || (r.K % 64 == 0 && r.ldb >= int64_t(r.nnb) * kBN && r.ldb % 8 == 0 &&
+                       r.d % 4 == 0 && r.M == r.d),
+               FASTRL_ERR_UNSUPPORTED, "transposed dW GEMM: unsupported shape");
+  {
+    ProfScope prof(dw ? FASTRL_K_BACKWARD : FASTRL_K_DHIDDEN, stream, flops);
+    hipLaunchKernelGGL(lm_bwd_direct_kernel, dim3(unsigned(nh + nw)), dim3(512), 0, stream, q, r);
+    FR_LAUNCHED();
+  }
+  if (q.ksplit > 1) {
+    const int64_t n4 = int64_t(q.M) * (q.d / 4);
+    hipLaunchKernelGGL(dh_reduce_kernel, dim3(unsigned((n4 + 255) / 256)), dim3(256), 0, stream,
+                       q.part, q.ksplit, q.M, q.d, q.cslab, q.dH, q.dH_bf16);
+    FR_LAUNCHED();
+  }
+  return FASTRL_OK;
+}
+
 // the second evaluation of marked token blocks (store_e == 2): bf16 through lm_redo_kernel
 template <typename T>
 static int launch_redo(GemmParams p, hipStream_t stream) {
@@ -1663,13 +1830,23 @@ struct LossWs {
   double* seq_loss;
 };
 
-static size_t carve_loss(Carver& c, LossWs& w, const fastrl_loss_args& a, int64_t tc_max) {
+static size_t carve_loss(Carver& c, LossWs& w, const fastrl_loss_args& a, const SlabPlan& pl) {
+  const int64_t tc_max = pl.tc_max;
   const int esz = a.dtype == FASTRL_BF16 ? 2 : 4;
   const int64_t Vpad = rup(a.V, kBM);
   const int64_t tcp = rup(std::max<int64_t>(tc_max, 1), kBN);
   const int64_t nmb = Vpad / kBM;
   const bool dh = a.dhidden != nullptr, dw = a.dW != nullptr;
-  w.WT = dh ? c.take<char>(size_t(a.d) * Vpad * esz) : nullptr;
+  // one region holds W^T or, where dhidden reads W itself, its float32 parts (the queried size
+  // covers W^T in both cases)
+  int64_t wt = dh ? int64_t(a.d) * Vpad * esz : 0;
+  if (direct_dh(a))
+    for (size_t si = 0; si + 1 < pl.seq_begin.size(); ++si) {
+      const int64_t Tc = a.seq_off_host[pl.seq_begin[si + 1]] - a.seq_off_host[pl.seq_begin[si]];
+      const int ks = Tc > 0 ? dh_ksplit(int32_t(Tc), a.d, a.V, dw) : 1;
+      if (ks > 1) wt = std::max(wt, Tc * ks * a.d * int64_t(sizeof(float)));
+    }
+  w.WT = dh ? c.take<char>(size_t(wt)) : nullptr;
   w.E1 = (dh || dw) ? c.take<char>(size_t(tcp) * Vpad * esz) : nullptr;
   w.Bd = dw ? c.take<char>(size_t(a.d) * tcp * esz) : nullptr;
   w.pmax = c.take<float>(size_t(nmb * tcp));
@@ -1709,7 +1886,7 @@ size_t policy_loss_workspace(const fastrl_loss_args& a) {
   SlabPlan pl = plan_slabs(a.seq_off_host, a.S, slab_cap(a));
   Carver c(nullptr);
   LossWs w;
-  return carve_loss(c, w, a, pl.tc_max);
+  return carve_loss(c, w, a, pl);
 }
 
 template <typename T>
@@ -1717,7 +1894,7 @@ static int policy_loss_impl(const fastrl_loss_args& a, hipStream_t stream) {
   SlabPlan pl = plan_slabs(a.seq_off_host, a.S, slab_cap(a));
   Carver c(a.ws);
   LossWs w;
-  carve_loss(c, w, a, pl.tc_max);
+  carve_loss(c, w, a, pl);
   const int64_t Vpad = rup(a.V, kBM);
   const int64_t tcp = rup(std::max<int64_t>(pl.tc_max, 1), kBN);
   const int32_t nmb = int32_t(Vpad / kBM);
@@ -1732,7 +1909,8 @@ static int policy_loss_impl(const fastrl_loss_args& a, hipStream_t stream) {
                        reinterpret_cast<int32_t*>(a.dW), int64_t(V) * d, 0);
     FR_LAUNCHED();
   }
-  if (dh && a.S > 0) {
+  const bool direct = direct_dh(a);
+  if (dh && !direct && a.S > 0) {
     dim3 g(nb1d(d, 64), unsigned(Vpad / 64));
     hipLaunchKernelGGL((transpose_scale_kernel<T>), g, dim3(256), 0, stream,
                        static_cast<const T*>(a.W), (const int32_t*)nullptr, int64_t(0), V,
@@ -1809,10 +1987,17 @@ static int policy_loss_impl(const fastrl_loss_args& a, hipStream_t stream) {
       q.dH_bf16 = a.dhidden_dtype == FASTRL_BF16;
       q.cslab = w.cslab; q.d = d;
       q.status = a.status;
+      if (direct) {
+        q.B = a.W; q.ldb = d; q.K = int32_t(rup(V, 64)); q.Vreal = V;
+        q.ksplit = dh_ksplit(Tc, d, V, dw);
+        q.part = static_cast<float*>(w.WT);
+      }
     }
     // bf16 with both gradients: the two GEMMs run as one launch (after dW's inputs are ready)
     const bool fused = dh && dw && sizeof(T) == 2;
-    if (dh && !fused)
+    if (dh && !dw && direct)
+      FR_TRY(launch_bwd_direct(q, GemmParams{}, false, 2.0 * double(Tc) * d * V, stream));
+    else if (dh && !fused)
       FR_TRY((launch_gemm<T, MODE_DH>(q, FASTRL_K_DHIDDEN, 2.0 * double(Tc) * d * V, stream)));
     if (dw) {
       dim3 g(nb1d(d, 64), unsigned(Tr / 64));
@@ -1828,7 +2013,9 @@ static int policy_loss_impl(const fastrl_loss_args& a, hipStream_t stream) {
       if constexpr (sizeof(T) == 2) {  // dW^T = Bd E: A = Bd, B = E1 read K-major
         r.A = w.Bd; r.lda = tcp; r.M = d;
         r.B = w.E1; r.ldb = Vpad; r.N = V;
-        if (fused)
+        if (fused && direct)
+          FR_TRY(launch_bwd_direct(q, r, true, 4.0 * double(V) * d * Tc, stream));
+        else if (fused)
           FR_TRY(launch_bwd(q, r, 4.0 * double(V) * d * Tc, stream));
         else
           FR_TRY((launch_gemm<T, MODE_DWT>(r, FASTRL_K_DW, 2.0 * double(V) * d * Tc, stream)));
