@@ -1,10 +1,11 @@
 // Maximizing Differential Advantage Pruning (Sec. 3.2; Alg. 1 Phase 2), the keep-ratio
 // budget, and stream compaction of kept tokens.  Every decision is integer or exact:
-//   K1 ngram_sort   one block per trajectory: pack n-grams into 64-bit keys (21 bits per
-//                   token), bitonic-sort them in LDS, keep the distinct ones.
-//   K2 pair_conflict one block per question: |N_n(o_i) & N_n(o_j)| for every same-class
-//                   pair by binary search of the shorter key list in the longer one, then
-//                   theta < tau as  tau_den * (|U| - |I|) < tau_num * |U|  in int64.
+//   K1 ngram_set    one block per trajectory: pack n-grams into keys (21 bits per token) and list
+//                   the distinct ones through a set in LDS (bits for n = 1, else hashed).
+//   K2 pair_conflict one block per trajectory i: |N_n(o_i) & N_n(o_j)| for every j < i of its
+//                   question and class, by looking the keys of j up in a set of i in LDS, then
+//                   theta < tau as  tau_den * (|U| - |I|) < tau_num * |U|  in int64; the
+//                   outcomes are row i of the question's conflict bit matrix.
 //   K0 group_eps    (continuous rewards, appendix on the grounding task) one wavefront per
 //                   question: classes = connected components of |A_i - A_j| < eps, from the
 //                   sorted advantages (a new class wherever a gap is >= eps).
@@ -13,103 +14,158 @@
 //                   ascending index), then the budget as "keep the K smallest (tier, rank,
 //                   class position) keys" -- the same list a class round-robin produces.
 //   K3b dp_fill     (optional) Alg. 1's DP alignment of the kept count, one block.
-//   K4 compaction   exclusive scans of kept flags and kept lengths (one block), then a
-//                   coalesced fill of tok_src, one block per kept trajectory.
+//   K4 compaction   exclusive scans of kept flags and kept lengths and a coalesced fill of
+//                   tok_src, one block per trajectory (over 4096 trajectories: the scans in a
+//                   one-block launch of their own).
 #include "common.h"
 
 namespace fastrl {
 
+#define FR_TRY(x)                     \
+  do {                                \
+    int rc_ = (x);                    \
+    if (rc_ != FASTRL_OK) return rc_; \
+  } while (0)
+
 constexpr int kMaxGroupPrune = 256;
 constexpr int kMaxLenPrune = 16384;
-constexpr uint64_t kKeyPad = ~0ull;
+constexpr int kConflictWords = kMaxGroupPrune / 64;
+
+// ---- sets of n-gram keys in LDS
+// n = 1 with a vocabulary up to kMaxBitVocab: one bit per token id.  One LDS access per key and no
+// probing, so lookups of several keys overlap (19 KB at V = 152064).
+constexpr int kMaxBitVocab = 1 << 19;  // 64 KB
+struct BitSet {
+  typedef uint32_t Key;
+  static constexpr Key kNone = 0xffffffffu;
+  // 32-bit words of the set (m: keys to insert), in 16-byte pieces
+  static __host__ __device__ int words(int V, int m) { return ((V + 127) / 128) * 4; }
+  static constexpr uint32_t kClear = 0u;
+  uint32_t* w;
+  __device__ BitSet(char* lds, int V, int m) : w(reinterpret_cast<uint32_t*>(lds)) {}
+  // true if `key` was not in the set (a plain read first: head-heavy ids are mostly there already,
+  // and their atomics on one address would run one by one)
+  __device__ __forceinline__ bool insert(Key key) {
+    const uint32_t bit = 1u << (key & 31);
+    if (reinterpret_cast<volatile uint32_t*>(w)[key >> 5] & bit) return false;
+    return (atomicOr(&w[key >> 5], bit) & bit) == 0;
+  }
+  __device__ __forceinline__ bool has(Key key) const { return (w[key >> 5] >> (key & 31)) & 1u; }
+};
+// otherwise a hash set: open addressing, linear probing, of whose slots at least a sixth stay empty
+// (so every probe ends).  No key equals the empty marker: three 21-bit ids fill 63 bits.
+struct HashSet {
+  typedef uint64_t Key;
+  static constexpr Key kNone = ~0ull;
+  // half of the slots empty where the LDS allows it; 156 KB: 16384 keys leave 3584 slots empty
+  static constexpr int kMaxSlots = 19968;
+  static __host__ __device__ int slots(int m) {
+    const int s = 2 * m < 64 ? 64 : 2 * m;
+    return s < kMaxSlots ? s : kMaxSlots;
+  }
+  static __host__ __device__ int words(int V, int m) { return slots(m) * 2; }
+  static constexpr uint32_t kClear = 0xffffffffu;
+  uint64_t* tab;
+  uint32_t size;
+  __device__ HashSet(char* lds, int V, int m)
+      : tab(reinterpret_cast<uint64_t*>(lds)), size(uint32_t(slots(m))) {}
+  __device__ __forceinline__ uint32_t slot(Key k) const {
+    return __umulhi(uint32_t((k * 0x9e3779b97f4a7c15ull) >> 32), size);
+  }
+  __device__ __forceinline__ bool insert(Key key) {
+    uint32_t h = slot(key);
+    for (;;) {
+      Key c = reinterpret_cast<volatile Key*>(tab)[h];
+      if (c == kNone) {
+        c = atomicCAS(reinterpret_cast<unsigned long long*>(tab + h), (unsigned long long)kNone,
+                      (unsigned long long)key);
+        if (c == kNone) return true;
+      }
+      if (c == key) return false;
+      if (++h == size) h = 0;
+    }
+  }
+  __device__ __forceinline__ bool has(Key key) const {
+    uint32_t h = slot(key);
+    for (;;) {
+      const Key c = tab[h];
+      if (c == key) return true;
+      if (c == kNone) return false;
+      if (++h == size) h = 0;
+    }
+  }
+};
+// empties a set (its words are a multiple of 4 and at most 16-byte aligned pieces)
+template <typename S>
+__device__ __forceinline__ void set_clear(char* lds, int V, int m, int tid, int threads) {
+  const uint32_t c = S::kClear;
+  uint4* p = reinterpret_cast<uint4*>(lds);
+  for (int j = tid; j < S::words(V, m) / 4; j += threads) p[j] = make_uint4(c, c, c, c);
+}
+// a trajectory's list of distinct keys: at its first token's place in the key array
+template <typename K>
+__device__ __forceinline__ K* key_list(uint64_t* keys, int64_t first) {
+  return reinterpret_cast<K*>(keys + first);
+}
 
 // ---------------------------------------------------------------------------- K1
-__global__ __launch_bounds__(256) void ngram_sort_kernel(
+// Distinct n-grams of each trajectory, in any order (only set sizes and memberships are used).
+// Bound by latency: a few dependent LDS accesses per key.  1538 trajectories of 256-2048 tokens:
+// 78 us as a bitonic sort of P = 2048 keys per block (66 passes over LDS), 11 us as a bit set.
+template <typename S>
+__global__ __launch_bounds__(256) void ngram_set_kernel(
     const int32_t* __restrict__ tokens, const int64_t* __restrict__ toff, int64_t T_total,
-    int32_t N, int32_t V, int32_t n, int32_t max_len, int32_t P, uint64_t* __restrict__ keys,
+    int32_t V, int32_t n, int32_t max_len, uint64_t* __restrict__ keys,
     int32_t* __restrict__ nuniq, int32_t* __restrict__ status) {
-  extern __shared__ uint64_t sk[];  // P keys, then P/ (reused) int32 scan area follows
-  __shared__ int32_t wsum[4];
-  __shared__ int32_t bad_flag;
+  typedef typename S::Key K;
+  extern __shared__ __attribute__((aligned(16))) char set_raw[];
+  __shared__ int32_t count, bad_flag;
   const int i = blockIdx.x;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63;
   const int64_t a = toff[i], b = toff[i + 1];
-  if (tid == 0) bad_flag = 0;
+  const bool off_ok = a >= 0 && b >= a && b <= T_total;
+  if (!off_ok || b - a > max_len) {
+    if (tid == 0) {
+      set_status(status, off_ok ? FASTRL_SB_SEQ_TOO_LONG : FASTRL_SB_BAD_OFFSETS);
+      nuniq[i] = 0;
+    }
+    return;
+  }
+  const int L = int(b - a);
+  const int m = L >= n ? L - n + 1 : 0;
+  S set(set_raw, V, m);
+  if (tid == 0) count = bad_flag = 0;
+  if (m > 0) set_clear<S>(set_raw, V, m, tid, 256);
   __syncthreads();
-  if (a < 0 || b < a || b > T_total) {
-    if (tid == 0) {
-      set_status(status, FASTRL_SB_BAD_OFFSETS);
-      nuniq[i] = 0;
-    }
-    return;
-  }
-  const int64_t L = b - a;
-  if (L > max_len) {
-    if (tid == 0) {
-      set_status(status, FASTRL_SB_SEQ_TOO_LONG);
-      nuniq[i] = 0;
-    }
-    return;
-  }
-  const int m = L >= n ? int(L - n + 1) : 0;
-  for (int j = tid; j < P; j += 256) {
-    uint64_t key = kKeyPad;
+  K* out = key_list<K>(keys, a);
+  for (int j0 = 0; j0 < m; j0 += 256) {
+    const int j = j0 + tid;
+    bool fresh = false;
+    K key = 0;
     if (j < m) {
-      key = 0;
       for (int k = 0; k < n; ++k) {
         int32_t t = tokens[a + j + k];
         if (t < 0 || t >= V) {
           bad_flag = 1;
           t = 0;
         }
-        key |= uint64_t(uint32_t(t)) << (21 * k);
+        key |= K(uint32_t(t)) << (21 * k);
       }
+      fresh = set.insert(key);
     }
-    sk[j] = key;
+    const uint64_t mask = __ballot(fresh);
+    if (mask) {
+      int base = 0;
+      if (lane == 0) base = atomicAdd(&count, __popcll(mask));
+      base = __builtin_amdgcn_readfirstlane(base);
+      if (fresh) out[base + __popcll(mask & ((1ull << lane) - 1))] = key;
+    }
   }
   __syncthreads();
-  if (bad_flag && tid == 0) set_status(status, FASTRL_SB_BAD_TOKEN);
-  // bitonic sort, ascending
-  for (int size = 2; size <= P; size <<= 1) {
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      for (int j = tid; j < (P >> 1); j += 256) {
-        const int lo = 2 * j - (j & (stride - 1));
-        const int hi = lo + stride;
-        const bool up = ((lo & size) == 0);
-        const uint64_t x = sk[lo], y = sk[hi];
-        if ((x > y) == up) {
-          sk[lo] = y;
-          sk[hi] = x;
-        }
-      }
-      __syncthreads();
-    }
+  if (tid == 0) {
+    nuniq[i] = count;
+    if (bad_flag) set_status(status, FASTRL_SB_BAD_TOKEN);
   }
-  // distinct keys, written in order: block-wide exclusive scan over chunks of 256
-  int base = 0;
-  const int lane = tid & 63, wv = tid >> 6;
-  for (int c = 0; c < m; c += 256) {
-    const int j = c + tid;
-    const int f = (j < m) && (j == 0 || sk[j] != sk[j - 1]);
-    // wave inclusive scan
-    int v = f;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      int t = __shfl_up(v, o, 64);
-      if (lane >= o) v += t;
-    }
-    if (lane == 63) wsum[wv] = v;
-    __syncthreads();
-    int pre = 0, tot = 0;
-    for (int w = 0; w < 4; ++w) {
-      if (w < wv) pre += wsum[w];
-      tot += wsum[w];
-    }
-    if (f) keys[a + base + pre + v - 1] = sk[j];
-    base += tot;
-    __syncthreads();
-  }
-  if (tid == 0) nuniq[i] = base;
 }
 
 // ---------------------------------------------------------------------------- K0
@@ -165,40 +221,64 @@ __global__ __launch_bounds__(64) void group_eps_kernel(
 }
 
 // ---------------------------------------------------------------------------- K2
-__global__ __launch_bounds__(256) void pair_conflict_kernel(
+// Row i of its question's conflict matrix: bit j (j < i, same class) is set where theta < tau.
+// Blocks q * max_group + i: the set of i is built once in LDS and each wavefront looks up the keys
+// of every eighth candidate j, 512 at a time (coalesced reads of j's list, all in flight together;
+// one LDS read per key in a bit set).  Bound by the latency of those reads.  128 questions of 8-16
+// rollouts of 256-2048 tokens: 477 us with one block per question and binary searches in global
+// memory, 154 us with hash-set lookups (a probe loop per key), 15 us so.
+constexpr int kPairThreads = 512;
+template <typename S>
+__global__ __launch_bounds__(kPairThreads) void pair_conflict_kernel(
     const int64_t* __restrict__ toff, const int32_t* __restrict__ group_off,
-    const int32_t* __restrict__ class_id, const uint64_t* __restrict__ keys,
-    const int32_t* __restrict__ nuniq, int32_t N, int32_t max_group, int32_t tau_num,
-    int32_t tau_den, uint8_t* __restrict__ conflict) {
-  const int q = blockIdx.x;
+    const int32_t* __restrict__ class_id, uint64_t* __restrict__ keys,
+    const int32_t* __restrict__ nuniq, int32_t N, int32_t V, int32_t max_group, int32_t tau_num,
+    int32_t tau_den, uint64_t* __restrict__ conflict) {
+  typedef typename S::Key K;
+  extern __shared__ __attribute__((aligned(16))) char set_raw[];
+  __shared__ int32_t cand[kMaxGroupPrune];
+  __shared__ unsigned long long row[kConflictWords];
+  const int q = blockIdx.x / max_group, i = blockIdx.x % max_group;
   const int g0 = group_off[q], g1 = group_off[q + 1];
-  if (g0 < 0 || g1 < g0 || g1 > N || g1 - g0 > max_group) return;  // flagged by K3
-  const int G = g1 - g0;
-  const int npairs = G * (G - 1) / 2;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  uint8_t* cq = conflict + size_t(q) * max_group * max_group;
-  for (int p = wv; p < npairs; p += 4) {
-    // p -> (i, j), i > j:  p = i (i - 1) / 2 + j
-    int i = int((1.0 + sqrt(1.0 + 8.0 * double(p))) * 0.5);
-    while (i * (i - 1) / 2 > p) --i;
-    while ((i + 1) * i / 2 <= p) ++i;
-    const int j = p - i * (i - 1) / 2;
-    if (class_id[g0 + i] != class_id[g0 + j]) continue;
-    const int na = nuniq[g0 + i], nb = nuniq[g0 + j];
-    const uint64_t* ka = keys + toff[g0 + i];
-    const uint64_t* kb = keys + toff[g0 + j];
-    const uint64_t* ks = na <= nb ? ka : kb;  // shorter list, searched in the longer
-    const uint64_t* kl = na <= nb ? kb : ka;
-    const int ns = na <= nb ? na : nb, nl = na <= nb ? nb : na;
+  if (g0 < 0 || g1 < g0 || g1 > N || g1 - g0 > max_group || i >= g1 - g0) return;  // (flagged by K3)
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int words = (max_group + 63) / 64;
+  const int cls = class_id[g0 + i], na = nuniq[g0 + i];
+  // candidates j < i, listed by every wavefront alike (same values to the same places)
+  int nc = 0;
+  for (int j0 = 0; j0 < i; j0 += 64) {
+    const bool c = j0 + lane < i && class_id[g0 + j0 + lane] == cls;
+    const uint64_t mask = __ballot(c);
+    if (c) cand[nc + __popcll(mask & ((1ull << lane) - 1))] = j0 + lane;
+    nc += __popcll(mask);
+  }
+  if (tid < kConflictWords) row[tid] = 0;
+  S set(set_raw, V, na);
+  if (nc > 0 && na > 0) {
+    const K* ka = key_list<K>(keys, toff[g0 + i]);
+    set_clear<S>(set_raw, V, na, tid, kPairThreads);
+    __syncthreads();
+    for (int e = tid; e < na; e += kPairThreads) set.insert(ka[e]);
+  }
+  __syncthreads();
+  for (int p = wv; p < nc; p += kPairThreads / 64) {
+    const int j = cand[p];
+    const int nb = nuniq[g0 + j];
     int cnt = 0;
-    for (int e = lane; e < ns; e += 64) {
-      const uint64_t x = ks[e];
-      int lo = 0, hi = nl;
-      while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (kl[mid] < x) lo = mid + 1; else hi = mid;
+    if (na > 0 && nb > 0) {
+      const K* kb = key_list<K>(keys, toff[g0 + j]);
+      constexpr int U = 8;
+      for (int e0 = 0; e0 < nb; e0 += 64 * U) {
+        K k[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int e = e0 + 64 * u + lane;
+          k[u] = e < nb ? kb[e] : S::kNone;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (k[u] != S::kNone) cnt += set.has(k[u]);
       }
-      cnt += (lo < nl && kl[lo] == x);
     }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
@@ -207,10 +287,11 @@ __global__ __launch_bounds__(256) void pair_conflict_kernel(
       bool c;
       if (U == 0) c = tau_num > 0;  // theta = 0 for two empty sets
       else c = int64_t(tau_den) * (U - I) < int64_t(tau_num) * U;
-      cq[i * max_group + j] = c;
-      cq[j * max_group + i] = c;
+      if (c) atomicOr(&row[j >> 6], 1ull << (j & 63));
     }
   }
+  __syncthreads();
+  if (tid < words) conflict[(size_t(q) * max_group + i) * words + tid] = row[tid];
 }
 
 // ---------------------------------------------------------------------------- K3
@@ -218,9 +299,11 @@ __global__ __launch_bounds__(64) void select_kernel(
     const float* __restrict__ rewards, const int32_t* __restrict__ group_off,
     const int32_t* __restrict__ class_id, const float* __restrict__ adv,
     const uint8_t* __restrict__ group_valid, int32_t N, int32_t max_group, double keep_ratio,
-    const uint8_t* __restrict__ conflict, uint8_t* __restrict__ keep_mask,
+    const uint64_t* __restrict__ conflict, uint8_t* __restrict__ keep_mask,
     int32_t* __restrict__ mdap_count, int32_t* __restrict__ class_out,
     int32_t* __restrict__ status) {
+  __shared__ uint64_t crow[kMaxGroupPrune][kConflictWords];  // conflict row of member i
+  __shared__ float rew[kMaxGroupPrune];
   __shared__ uint8_t mdap[kMaxGroupPrune];
   __shared__ int32_t cls[kMaxGroupPrune];
   __shared__ int32_t vpos[kMaxGroupPrune];     // visiting position of member i
@@ -286,25 +369,60 @@ __global__ __launch_bounds__(64) void select_kernel(
     }
   }
   __syncthreads();
-  const uint8_t* cq = conflict + size_t(q) * max_group * max_group;
-  if (lane == 0) {
-    // greedy maximal independent set per class, members in visiting order
-    int count = 0;
-    for (int p = 0; p < G; ++p) {
-      const int i = ord[p];
-      uint8_t keep = 1;
-      for (int pj = 0; pj < p; ++pj) {
-        const int j = ord[pj];
-        if (mdap[j] && cls[j] == cls[i] && cq[i * max_group + j]) {
-          keep = 0;
-          break;
-        }
-      }
-      mdap[i] = keep;
-      count += keep;
-    }
-    mdap_count[q] = count;
+  const int words = (max_group + 63) / 64;
+  const uint64_t* cq = conflict + size_t(q) * max_group * words;
+  for (int e = lane; e < G * kConflictWords; e += 64) {
+    const int i = e / kConflictWords, w = e % kConflictWords;
+    crow[i][w] = w < words ? cq[i * words + w] : 0;
   }
+  for (int i = lane; i < G; i += 64) rew[i] = rewards[g0 + i];
+  __syncthreads();
+  // greedy maximal independent set per class, members in visiting order: lane l holds the whole
+  // conflict row (earlier and later members) of the members at positions l, l + 64, ..; the kept
+  // set is the same in every lane
+  uint64_t kept[kConflictWords] = {};
+  int count = 0;
+#pragma unroll
+  for (int pb = 0; pb < kConflictWords; ++pb) {
+    if (pb * 64 >= G) break;
+    const int pos = pb * 64 + lane;
+    const int me = pos < G ? ord[pos] : 0;
+    uint64_t full[kConflictWords];
+#pragma unroll
+    for (int w = 0; w < kConflictWords; ++w) full[w] = pos < G ? crow[me][w] : 0;
+    for (int j = 0; j < G; ++j) {
+      const uint64_t bit = (crow[j][me >> 6] >> (me & 63)) & 1ull;
+#pragma unroll
+      for (int w = 0; w < kConflictWords; ++w)
+        if ((j >> 6) == w) full[w] |= bit << (j & 63);
+    }
+    const int np = min(64, G - pb * 64);
+    for (int p = 0; p < np; ++p) {
+      const int i = __builtin_amdgcn_readlane(me, p);
+      uint64_t hit = 0;
+#pragma unroll
+      for (int w = 0; w < kConflictWords; ++w) {
+        if (w * 64 >= G) break;
+        const uint64_t f = uint64_t(uint32_t(__builtin_amdgcn_readlane(int(uint32_t(full[w])), p))) |
+                           uint64_t(uint32_t(__builtin_amdgcn_readlane(int(uint32_t(full[w] >> 32)), p))) << 32;
+        hit |= f & kept[w];
+      }
+      if (hit == 0) {
+#pragma unroll
+        for (int w = 0; w < kConflictWords; ++w)
+          if ((i >> 6) == w) kept[w] |= 1ull << (i & 63);
+        ++count;
+      }
+    }
+  }
+  for (int i = lane; i < G; i += 64) {
+    uint64_t k = 0;
+#pragma unroll
+    for (int w = 0; w < kConflictWords; ++w)
+      if ((i >> 6) == w) k = kept[w];
+    mdap[i] = uint8_t((k >> (i & 63)) & 1ull);
+  }
+  if (lane == 0) mdap_count[q] = count;
   __syncthreads();
   if (!(keep_ratio > 0.0)) {
     for (int i = lane; i < G; i += 64) keep_mask[g0 + i] = mdap[i];
@@ -313,24 +431,17 @@ __global__ __launch_bounds__(64) void select_kernel(
   // budget: kappa_k = |G r_k - sum_j r_j| (sum in index order, float64; r_k the reward of
   // the class's first visited member); classes ordered by kappa descending, then by their
   // lowest member index
+  double total = 0.0;
+  for (int j = 0; j < G; ++j) total = __dadd_rn(total, double(rew[j]));
   for (int c = lane; c < G; c += 64) {
-    crep[c] = -1;
-    cmin[c] = -1;
-  }
-  __syncthreads();
-  if (lane == 0) {
-    double s = 0.0;
-    for (int j = 0; j < G; ++j) s = __dadd_rn(s, double(rewards[g0 + j]));
-    for (int p = 0; p < G; ++p) {
-      const int j = ord[p];
-      const int c = cls[j];
-      if (crep[c] < 0) {
-        crep[c] = j;
-        kappa[c] = fabs(__dsub_rn(__dmul_rn(double(G), double(rewards[g0 + j])), s));
-      }
+    int rep = -1, low = -1;
+    for (int j = G - 1; j >= 0; --j) {
+      if (cls[ord[j]] == c) rep = ord[j];
+      if (cls[j] == c) low = j;
     }
-    for (int j = 0; j < G; ++j)
-      if (cmin[cls[j]] < 0) cmin[cls[j]] = j;
+    crep[c] = rep;
+    cmin[c] = low;
+    if (rep >= 0) kappa[c] = fabs(__dsub_rn(__dmul_rn(double(G), double(rew[rep])), total));
   }
   __syncthreads();
   for (int c = lane; c < G; c += 64) {
@@ -499,35 +610,106 @@ __global__ __launch_bounds__(1024) void compact_scan_kernel(
   }
 }
 
+// kpos == NULL: every block takes the exclusive sums over the trajectories before its own itself
+// (9 bytes of L2 reads each; up to kSelfScan trajectories that is ~2 us inside this launch, against
+// ~5 us for the scan as a launch of its own) and writes its entries of kept_traj and kept_tok_off.
+constexpr int kSelfScan = 4096;
 __global__ __launch_bounds__(256) void compact_fill_kernel(
-    const int32_t* __restrict__ kpos, const int64_t* __restrict__ toff,
-    const int64_t* __restrict__ kept_tok_off, int32_t* __restrict__ tok_src) {
+    const uint8_t* __restrict__ keep_mask, const int32_t* __restrict__ kpos,
+    const int64_t* __restrict__ toff, int32_t N, int32_t* __restrict__ kept_traj,
+    int64_t* __restrict__ kept_tok_off, int64_t* __restrict__ counts,
+    int32_t* __restrict__ tok_src) {
   const int i = blockIdx.x;
-  const int pos = kpos[i];
-  if (pos < 0) return;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int64_t a = toff[i], L = toff[i + 1] - a;
-  const int64_t dst = kept_tok_off[pos];
-  for (int64_t t = threadIdx.x; t < L; t += 256) tok_src[dst + t] = int32_t(a + t);
+  int64_t dst;
+  if (kpos) {
+    const int pos = kpos[i];
+    if (pos < 0) return;
+    dst = kept_tok_off[pos];
+  } else {
+    __shared__ int32_t wc[4];
+    __shared__ int64_t wl[4];
+    const int kept = keep_mask[i] != 0;
+    if (!kept && i != N - 1) return;
+    int32_t n = 0;
+    int64_t len = 0;
+    for (int j = tid; j < i; j += 256) {
+      if (keep_mask[j]) {
+        ++n;
+        len += toff[j + 1] - toff[j];
+      }
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+      n += __shfl_xor(n, o, 64);
+      len += __shfl_xor(len, o, 64);
+    }
+    if (lane == 0) {
+      wc[wv] = n;
+      wl[wv] = len;
+    }
+    __syncthreads();
+    n = wc[0] + wc[1] + wc[2] + wc[3];
+    dst = wl[0] + wl[1] + wl[2] + wl[3];
+    if (tid == 0) {
+      if (kept) {
+        kept_traj[n] = i;
+        kept_tok_off[n] = dst;
+      }
+      if (i == N - 1) {
+        kept_tok_off[n + kept] = dst + (kept ? L : 0);
+        counts[0] = n + kept;
+        counts[1] = dst + (kept ? L : 0);
+      }
+    }
+    if (!kept) return;
+  }
+  for (int64_t t = tid; t < L; t += 256) tok_src[dst + t] = int32_t(a + t);
 }
 
 // ---------------------------------------------------------------------------- host
-static int next_pow2(int x) {
-  int p = 1;
-  while (p < x) p <<= 1;
-  return p;
-}
-
 size_t prune_workspace(int32_t Q, int32_t N, int64_t T_total, int32_t max_group) {
   Carver c(nullptr);
   c.take<uint64_t>(size_t(T_total > 0 ? T_total : 1));
   c.take<int32_t>(size_t(N + 1));
-  c.take<uint8_t>(size_t(Q > 0 ? Q : 1) * max_group * max_group);
+  c.take<uint64_t>(size_t(Q > 0 ? Q : 1) * max_group * ((max_group + 63) / 64));
   c.take<int32_t>(size_t(N + 1));
   c.take<int32_t>(size_t(N + 1));
   c.take<int32_t>(size_t(N + 1));
   c.take<int32_t>(size_t(Q + 1));
   c.take<int32_t>(size_t(Q + 1));
   return c.size();
+}
+
+// K1 and K2 with one kind of set
+template <typename S>
+static int launch_sets(const int32_t* token_ids, const int64_t* toff, int64_t T_total,
+                       const int32_t* group_off, const int32_t* cls, int32_t Q, int32_t N,
+                       int32_t max_group, int32_t max_len, int32_t V, int32_t ngram_n,
+                       int32_t tau_num, int32_t tau_den, uint64_t* keys, int32_t* nuniq,
+                       uint64_t* conflict, int32_t* status, hipStream_t stream) {
+  const size_t shm = size_t(S::words(V, max_len)) * 4;
+  if (N > 0) {
+    if (shm > 64 * 1024)
+      FR_HIP(hipFuncSetAttribute((const void*)ngram_set_kernel<S>,
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, int(shm)));
+    hipLaunchKernelGGL((ngram_set_kernel<S>), dim3(N), dim3(256), shm, stream, token_ids, toff,
+                       T_total, V, ngram_n, max_len, keys, nuniq, status);
+    FR_LAUNCHED();
+  }
+  if (Q > 0 && N > 0) {
+    FR_CHECK_ARG(int64_t(Q) * max_group < (int64_t(1) << 31), FASTRL_ERR_UNSUPPORTED,
+                 "fastrl_prune: Q * max_group too large");
+    if (shm > 64 * 1024)
+      FR_HIP(hipFuncSetAttribute((const void*)pair_conflict_kernel<S>,
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, int(shm)));
+    hipLaunchKernelGGL((pair_conflict_kernel<S>), dim3(unsigned(Q) * unsigned(max_group)),
+                       dim3(kPairThreads), shm, stream, toff, group_off, cls, keys, nuniq, N, V,
+                       max_group, tau_num, tau_den, conflict);
+    FR_LAUNCHED();
+  }
+  return FASTRL_OK;
 }
 
 int launch_prune(const int32_t* token_ids, const int64_t* toff, int64_t T_total,
@@ -541,7 +723,8 @@ int launch_prune(const int32_t* token_ids, const int64_t* toff, int64_t T_total,
   Carver c(ws);
   uint64_t* keys = c.take<uint64_t>(size_t(T_total > 0 ? T_total : 1));
   int32_t* nuniq = c.take<int32_t>(size_t(N + 1));
-  uint8_t* conflict = c.take<uint8_t>(size_t(Q > 0 ? Q : 1) * max_group * max_group);
+  uint64_t* conflict =
+      c.take<uint64_t>(size_t(Q > 0 ? Q : 1) * max_group * ((max_group + 63) / 64));
   int32_t* kpos = c.take<int32_t>(size_t(N + 1));
   int32_t* cls_eps = c.take<int32_t>(size_t(N + 1));
   int32_t* frank = c.take<int32_t>(size_t(N + 1));
@@ -554,20 +737,13 @@ int launch_prune(const int32_t* token_ids, const int64_t* toff, int64_t T_total,
     FR_LAUNCHED();
     cls = cls_eps;
   }
-  if (N > 0) {
-    const int P = next_pow2(max_len > 1 ? max_len : 1);
-    const size_t shm = size_t(P) * sizeof(uint64_t);
-    if (shm > 64 * 1024)
-      FR_HIP(hipFuncSetAttribute((const void*)ngram_sort_kernel,
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, int(shm)));
-    hipLaunchKernelGGL(ngram_sort_kernel, dim3(N), dim3(256), shm, stream, token_ids, toff,
-                       T_total, N, V, ngram_n, max_len, P, keys, nuniq, status);
-    FR_LAUNCHED();
-  }
+  if (ngram_n == 1 && V <= kMaxBitVocab)
+    FR_TRY(launch_sets<BitSet>(token_ids, toff, T_total, group_off, cls, Q, N, max_group, max_len,
+                               V, ngram_n, tau_num, tau_den, keys, nuniq, conflict, status, stream));
+  else
+    FR_TRY(launch_sets<HashSet>(token_ids, toff, T_total, group_off, cls, Q, N, max_group, max_len,
+                                V, ngram_n, tau_num, tau_den, keys, nuniq, conflict, status, stream));
   if (Q > 0) {
-    hipLaunchKernelGGL(pair_conflict_kernel, dim3(Q), dim3(256), 0, stream, toff, group_off,
-                       cls, keys, nuniq, N, max_group, tau_num, tau_den, conflict);
-    FR_LAUNCHED();
     hipLaunchKernelGGL(select_kernel, dim3(Q), dim3(64), 0, stream, rewards, group_off, cls,
                        adv, group_valid, N, max_group, keep_ratio, conflict, keep_mask,
                        mdap_count, class_out, status);
@@ -579,12 +755,16 @@ int launch_prune(const int32_t* token_ids, const int64_t* toff, int64_t T_total,
       FR_LAUNCHED();
     }
   }
-  hipLaunchKernelGGL(compact_scan_kernel, dim3(1), dim3(1024), 0, stream, keep_mask, toff, N,
-                     kept_traj, kept_tok_off, kpos, counts);
-  FR_LAUNCHED();
+  const bool self_scan = N > 0 && N <= kSelfScan;
+  if (!self_scan) {
+    hipLaunchKernelGGL(compact_scan_kernel, dim3(1), dim3(1024), 0, stream, keep_mask, toff, N,
+                       kept_traj, kept_tok_off, kpos, counts);
+    FR_LAUNCHED();
+  }
   if (N > 0) {
-    hipLaunchKernelGGL(compact_fill_kernel, dim3(N), dim3(256), 0, stream, kpos, toff,
-                       kept_tok_off, tok_src);
+    hipLaunchKernelGGL(compact_fill_kernel, dim3(N), dim3(256), 0, stream, keep_mask,
+                       self_scan ? (const int32_t*)nullptr : kpos, toff, N, kept_traj,
+                       kept_tok_off, counts, tok_src);
     FR_LAUNCHED();
   }
   return FASTRL_OK;

@@ -1,0 +1,51 @@
+"""GPU pruning through the hash sets and both compaction launches, at the edges of their sizes, bit
+for bit against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from synth import CONFIGS, make_rollouts, plant_duplicates
+from tests._parity import to_dev
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def fr():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2609_36932_amd as m
+    return m
+
+
+@pytest.mark.parametrize("Q, G, lens, V, n", [
+    (1024, 4, (1, 12), 40, 1),      # 4096 trajectories: the last size that scans in the fill
+    (1366, 3, (0, 12), 40, 2),      # 4098: the scan launch
+    (3, 64, (30, 33), 40, 1),       # one full conflict word; ids past one word of bits
+    (2, 70, (1, 260), 9, 3),        # two words; trigrams over 9 ids, more keys than a block
+    (4, 8, (510, 514), 1 << 19, 1),  # a key per thread and one more; the largest bit set
+    (4, 8, (255, 258), (1 << 19) + 1, 1),  # unigrams in the hash set
+    (3, 8, (28, 36), 50, 2),        # 27-35 bigrams around the smallest hash set
+    (4, 8, (1000, 1300), 3, 1),     # at most 3 distinct ids: every insert but three is a repeat
+])
+@pytest.mark.parametrize("keep", [0.0, 0.5])
+def test_prune_sets(fr, Q, G, lens, V, n, keep):
+    ro = make_rollouts(CONFIGS[3], Q=Q, len_range=lens, G=(G,), V=V, seed=40 + Q)
+    plant_duplicates(ro, p_copy=0.6, p_mutate=0.1, seed=Q)
+    ref = oracle.hot_path_step(ro.rewards, ro.group_off, ro.token_ids, ro.traj_tok_off,
+                               lmhead=False, ngram_n=n, keep_ratio=keep)
+    st = torch.zeros(1, dtype=torch.int32, device=DEV)
+    out = fr.prune(to_dev(ro.token_ids, DEV), to_dev(ro.traj_tok_off, DEV),
+                   to_dev(ro.rewards, DEV), to_dev(ro.group_off, DEV), to_dev(ref["class_id"], DEV),
+                   to_dev(ref["group_valid"], DEV), V=V, max_group=G,
+                   max_len=int(ro.lengths.max()), ngram_n=n, keep_ratio=keep, status=st)
+    torch.cuda.synchronize()
+    assert st.item() == 0, fr.status_names(st.item())
+    nk, tk = out["counts"].cpu().tolist()
+    assert np.array_equal(out["keep_mask"].cpu().numpy(), ref["keep_mask"])
+    assert np.array_equal(out["mdap_count"].cpu().numpy(), ref["mdap_count"])
+    assert nk == len(ref["kept_traj"]) and tk == len(ref["tok_src"])
+    assert np.array_equal(out["kept_traj"][:nk].cpu().numpy(), ref["kept_traj"])
+    assert np.array_equal(out["kept_tok_off"][:nk + 1].cpu().numpy(), ref["kept_tok_off"])
+    assert np.array_equal(out["tok_src"][:tk].cpu().numpy(), ref["tok_src"])
