@@ -5,10 +5,11 @@
 // of z = H W^T and g = dL/dlogp:  dZ = g (onehot(y) - P),  dH = dZ W,  dW = dZ^T H.
 //
 // One tiled GEMM kernel does the three contractions.  C[m, n] = sum_k A[m, k] B[n, k]
-// with 256 x 256 block tiles and LDS double buffering:
-//   bf16: 8 wavefronts of 128 x 64, v_mfma_f32_16x16x32_bf16, 64-wide K steps, operands moved
-//         by direct global->LDS loads;
-//   f32:  4 wavefronts of 128 x 128, v_mfma_f32_32x32x2_f32, register-staged loads.
+// with operands moved by direct global->LDS loads:
+//   bf16: 256 x 256 block tiles, 8 wavefronts of 128 x 64, v_mfma_f32_16x16x32_bf16, 64-wide K
+//         steps in two LDS stages;
+//   f32:  4 wavefronts on v_mfma_f32_32x32x2_f32, 32-wide K steps; logits tiles of 256 vocab rows
+//         x 64 tokens, gradient tiles of 64 x 64 or 128 x 128 (f32_gemm_kernel).
 // Work is cut into slabs of whole sequences; per slab:
 //   FWD  C = W . H_slab^T  (rows = vocab, cols = tokens, K = d).  Epilogue: per token,
 //        the block's max and sum exp(z - s_t) over its 256 vocab rows (in-lane over 32
@@ -21,9 +22,9 @@
 //           g_t = c_t exp(lse_t - s_t), E1[t][y_t] -= exp(lse_t - s_t) makes
 //           c_t E1[t][v] = g_t (P[t][v] - [v = y_t]) = -dZ[t][v] for every v.
 //   DH   C = E1 . W^T  (rows = tokens, cols = d, K = vocab):  dH[t] = -c_t C[t].
-//   DW   with Bd[n][t] = c_t H[t][n] (K = tokens; E1 is read K-major through transposing LDS
-//        reads): bf16 computes C' = Bd . E1 (rows = d, cols = vocab), f32 computes
-//        C = E1^T . Bd^T (rows = vocab, cols = d):  dW[v] (+)= -C[v].
+//   DW   with B = c_t H[t] (K = tokens): bf16 computes C' = Bd . E1 (Bd = B^T; rows = d, cols =
+//        vocab; E1 is read K-major through transposing LDS reads), f32 computes C = E1^T . B
+//        (rows = vocab, cols = d; both read K-major):  dW[v] (+)= -C[v].
 // Nothing of size [T, V] exists: the exp-logit buffer holds one slab, [slab, V], and the
 // default slab (32768 tokens) does not grow with T.
 #include <algorithm>
@@ -42,43 +43,13 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kBM = 256, kBN = 256;
+constexpr int kThreads = 512;  // of a bf16 GEMM block: 8 wavefronts, two per SIMD
 
 // MODE_DWT: the bf16 dW GEMM computed transposed, dW^T = Bd E (rows = hidden columns, cols =
 // vocab rows, K = tokens), so that it runs on the 8-wavefront engine with E as a K-major B
 // MODE_DHT: the bf16 dhidden GEMM of small calls, which reads W itself (K-major, K = vocab) instead
 // of a transposed copy and can cut its long K into parts (launch_bwd_direct)
 enum GemmMode { MODE_FWD = 0, MODE_DH = 1, MODE_DW = 2, MODE_DWT = 3, MODE_DHT = 4 };
-
-// wavefront geometry of the 256 x 256 block tile: every bf16 GEMM runs 8 wavefronts (two per
-// SIMD) of 128 x 64 on 16 x 16 x 32 MFMAs; every float32 GEMM runs 4 wavefronts of 128 x 128
-// on 32 x 32 MFMAs
-template <typename T, int MODE>
-struct Geo {
-  static constexpr bool W8 = sizeof(T) == 2;
-  static_assert(MODE != (W8 ? MODE_DW : MODE_DWT), "dW runs transposed in bf16 only");
-  static constexpr int THREADS = W8 ? 512 : 256, WAVES_N = W8 ? 4 : 2, NI = W8 ? 2 : 4,
-                       WPE = W8 ? 2 : 1;
-};
-
-template <typename T>
-struct Eng;
-
-template <>
-struct Eng<uint16_t> {     // bfloat16 operands
-  static constexpr int BK = 64;
-  static constexpr int KP = 8;             // row padding (elements) against bank conflicts
-  static constexpr int LD = BK + KP;       // LDS row stride in elements
-  static constexpr int VEC = 8;            // elements per 16-byte vector
-  static constexpr int KSTEP = 16;         // K per MFMA
-};
-template <>
-struct Eng<float> {        // float32 operands
-  static constexpr int BK = 16;
-  static constexpr int KP = 4;
-  static constexpr int LD = BK + KP;
-  static constexpr int VEC = 4;
-  static constexpr int KSTEP = 2;
-};
 
 struct GemmParams {
   const void* A;            // [M, lda]
@@ -143,35 +114,6 @@ __device__ __forceinline__ void tile_coords(int& mb, int& nb, int nmb, int nnb, 
   const int a = first + in % gsz, sweep = in / gsz;
   mb = GN ? sweep : a;
   nb = GN ? a : sweep;
-}
-
-template <typename T>
-__device__ __forceinline__ void load_vec(const T* p, bool ok, u32x4_t& v) {
-  if (ok) v = *reinterpret_cast<const u32x4_t*>(p);
-  else v = u32x4_t{0u, 0u, 0u, 0u};
-}
-
-template <typename T>
-__device__ __forceinline__ float to_f32(T x);
-template <>
-__device__ __forceinline__ float to_f32<uint16_t>(uint16_t x) { return bf16_to_f32(x); }
-template <>
-__device__ __forceinline__ float to_f32<float>(float x) { return x; }
-
-template <typename T>
-__device__ __forceinline__ T from_f32(float x);
-template <>
-__device__ __forceinline__ uint16_t from_f32<uint16_t>(float x) { return f32_to_bf16(x); }
-template <>
-__device__ __forceinline__ float from_f32<float>(float x) { return x; }
-
-// accumulator (mi, ni, r) -> (row, col) inside the 256 x 256 block tile
-__device__ __forceinline__ int acc_row(int wm, int mi, int r, int lane) {
-  return wm * 128 + mi * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
-}
-template <typename T, int MODE>
-__device__ __forceinline__ int acc_col(int wn, int ni, int lane) {
-  return wn * (kBN / Geo<T, MODE>::WAVES_N) + ni * 32 + (lane & 31);
 }
 
 typedef __attribute__((address_space(3))) void lds_void_t;
@@ -450,7 +392,7 @@ __device__ __forceinline__ void mainloop_bf16_dma(const GemmParams& p, int m0, i
       __builtin_amdgcn_sched_barrier(0);
       mma_rows(fa1, fb1, 2, 4);
       __builtin_amdgcn_sched_barrier(0);
-      const uint32_t target = uint32_t(kt + 1) * (Geo<uint16_t, MODE>::THREADS / 64);
+      const uint32_t target = uint32_t(kt + 1) * (kThreads / 64);
       for (int spin = 0; spin < kSyncSpins && seen < target; ++spin) {
         __builtin_amdgcn_s_sleep(0);
         seen = __hip_atomic_load(sync, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -490,103 +432,6 @@ __device__ __forceinline__ void mainloop_bf16_dma(const GemmParams& p, int m0, i
   }
 }
 
-// float32 main loop (small problems): register-staged loads into padded LDS rows.  With
-// A_KMAJOR the A operand is stored k-major (A[m][k] at k * lda + m): a thread loads 4
-// consecutive m of one k and scatters them into the tile's rows.
-template <int MODE, bool A_KMAJOR>
-__device__ __forceinline__ void mainloop_f32(const GemmParams& p, int m0, int n0,
-                                             f32x16_t (&acc)[4][4], float* smem) {
-  using E = Eng<float>;
-  constexpr int BK = E::BK, LD = E::LD, VEC = E::VEC;
-  constexpr int VPR = BK / VEC;
-  constexpr int LOADS = kBM * VPR / Geo<float, MODE>::THREADS;
-  float* As = smem;
-  float* Bs = smem + 2 * kBM * LD;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  const float* Ag = static_cast<const float*>(p.A);
-  const float* Bg = static_cast<const float*>(p.B);
-  const float* arow[LOADS];
-  const float* brow[LOADS];
-  bool aok[LOADS], bok[LOADS];
-  int kofs[LOADS], srow[LOADS], akk[LOADS], am4[LOADS];
-#pragma unroll
-  for (int j = 0; j < LOADS; ++j) {
-    const int v = tid + j * Geo<float, MODE>::THREADS;
-    const int row = v / VPR;
-    kofs[j] = (v % VPR) * VEC;
-    srow[j] = row;
-    const int am = m0 + row;
-    aok[j] = am < p.M;
-    arow[j] = Ag + int64_t(aok[j] ? am : 0) * p.lda;
-    akk[j] = v / (kBM / VEC);         // k-major: k row of the tile
-    am4[j] = (v % (kBM / VEC)) * VEC;  // and 4 consecutive m
-    const int bn = n0 + row;
-    bok[j] = bn < p.N;
-    int64_t br = bok[j] ? bn : 0;
-    if (MODE == MODE_FWD) {
-      br += p.b_row_base;
-      if (p.b_rows) br = bok[j] ? p.b_rows[br] : 0;
-    }
-    brow[j] = Bg + br * p.ldb;
-  }
-  u32x4_t ra[LOADS], rb[LOADS];
-  const int nk = (p.K + BK - 1) / BK;
-  auto gload = [&](int kt) {
-    const int k0 = kt * BK;
-#pragma unroll
-    for (int j = 0; j < LOADS; ++j) {
-      const int k = k0 + kofs[j];
-      if (A_KMAJOR) {
-        const int ka = k0 + akk[j];
-        const int mm = m0 + am4[j];
-        load_vec<float>(Ag + int64_t(ka) * p.lda + mm, ka < p.K && mm + VEC <= p.lda, ra[j]);
-      } else {
-        load_vec<float>(arow[j] + k, aok[j] && k < p.K, ra[j]);
-      }
-      load_vec<float>(brow[j] + k, bok[j] && k < p.K, rb[j]);
-    }
-  };
-  auto sstore = [&](int buf) {
-#pragma unroll
-    for (int j = 0; j < LOADS; ++j) {
-      if (A_KMAJOR) {
-#pragma unroll
-        for (int q = 0; q < VEC; ++q)
-          As[(buf * kBM + am4[j] + q) * LD + akk[j]] = __uint_as_float(ra[j][q]);
-      } else {
-        *reinterpret_cast<u32x4_t*>(As + (buf * kBM + srow[j]) * LD + kofs[j]) = ra[j];
-      }
-      *reinterpret_cast<u32x4_t*>(Bs + (buf * kBM + srow[j]) * LD + kofs[j]) = rb[j];
-    }
-  };
-  gload(0);
-  sstore(0);
-  for (int kt = 0; kt < nk; ++kt) {
-    __syncthreads();
-    const int buf = kt & 1;
-    if (kt + 1 < nk) gload(kt + 1);
-    const float* as = As + buf * kBM * LD;
-    const float* bs = Bs + buf * kBM * LD;
-#pragma unroll
-    for (int kk = 0; kk < BK; kk += 2) {
-      float af[4], bf[4];
-      const int kq = kk + (lane >> 5);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) af[i] = as[(wm * 128 + i * 32 + (lane & 31)) * LD + kq];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) bf[j] = bs[(wn * 128 + j * 32 + (lane & 31)) * LD + kq];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[i], bf[j], acc[i][j], 0, 0, 0);
-    }
-    if (kt + 1 < nk) sstore(buf ^ 1);
-  }
-}
-
-
 // Reductions over the four 16-lane groups of a wavefront (lanes c, c + 16, c + 32, c + 48) with
 // row swaps instead of LDS-routed shuffles: a 16-lane-row swap of x with itself leaves rows
 // (r0, r0, r2, r2) and (r1, r1, r3, r3), whose sum is the xor-16 partner sum; a half swap then
@@ -618,7 +463,7 @@ __device__ __forceinline__ void fwd_epilogue_bf16(const GemmParams& p, int m0, i
   float* xmax = reinterpret_cast<float*>(smem);  // [2 wm][256 cols]
   float* xsum = xmax + 2 * kBN;
   float* xsz = xsum + 2 * kBN;
-  constexpr int NT = Geo<uint16_t, MODE_FWD>::THREADS;
+  constexpr int NT = kThreads;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 2, wn = wave & 3;
   const int g = lane >> 4, c = lane & 15;
@@ -854,209 +699,295 @@ __device__ __forceinline__ void dwt_epilogue_bf16(const GemmParams& p, int m0, i
   }
 }
 
-template <typename T>
-struct SmemBytes;
-template <>
-struct SmemBytes<uint16_t> { static constexpr int value = 2 * 2 * kBM * 64 * 2 + 16; };  // + sync word
-template <>
-struct SmemBytes<float> { static constexpr int value = 2 * 2 * kBM * Eng<float>::LD * 4; };
+constexpr int kSmemBytes = 2 * 2 * kBM * 64 * 2 + 16;  // two stages of both operands + sync word
 
+// the bf16 GEMMs (T is uint16_t)
 template <typename T, int MODE>
-__global__ __launch_bounds__((Geo<T, MODE>::THREADS))
-__attribute__((amdgpu_waves_per_eu(Geo<T, MODE>::WPE, Geo<T, MODE>::WPE)))
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void lm_gemm_kernel(const GemmParams p) {
-  __shared__ __attribute__((aligned(16))) char smem_raw[SmemBytes<T>::value];
-  T* smem = reinterpret_cast<T*>(smem_raw);
+  static_assert(sizeof(T) == 2, "float32 runs f32_gemm_kernel");
+  __shared__ __attribute__((aligned(16))) char smem_raw[kSmemBytes];
+  uint16_t* smem = reinterpret_cast<uint16_t*>(smem_raw);
   int mb, nb;
   tile_coords<MODE>(mb, nb, p.nmb, p.nnb, blockIdx.x, p.group);
-  if (MODE == MODE_FWD && p.store_e == 2 && p.redo_blk[nb] == 0) return;
   const int m0 = mb * kBM, n0 = nb * kBN;
-  constexpr int NI = Geo<T, MODE>::NI, NT = Geo<T, MODE>::THREADS;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / Geo<T, MODE>::WAVES_N, wn = wave % Geo<T, MODE>::WAVES_N;
+  f32x4_t acc[8][4];
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+  mainloop_bf16_dma<MODE>(p, m0, n0, acc, smem);
+  if constexpr (MODE == MODE_FWD) fwd_epilogue_bf16(p, m0, n0, mb, acc, smem);
+  else if constexpr (MODE == MODE_DH) dh_epilogue_bf16(p, m0, n0, acc);
+  else dwt_epilogue_bf16(p, m0, n0, acc);
+}
 
-  if constexpr (Geo<T, MODE>::W8) {
-    f32x4_t acc16[8][4];
+// ------------------------------------------------------------------ float32 GEMMs
+// C[m, n] = sum_k A[m, k] B[n, k] on v_mfma_f32_32x32x2_f32 (64 cycles each, so a wavefront needs
+// little operand traffic and the tiles can be small): 4 wavefronts as WM x WN over a BM x BN tile,
+// 32-wide K steps, ST LDS stages filled by direct global->LDS loads ST - 1 steps ahead.  Float32
+// problems are small (parity runs), so the grid has to fill the chip and the chain of K steps per
+// block has to be short: 256 x 256 tiles with register-staged loads gave 3 blocks of 256 steps
+// (1090 us) on the 640-token dhidden of d = 256, V = 4096, where these take 22 us.  Loss call with
+// both gradients, 256 x 256 tiles -> these: 300 tokens (d 256, V 4096) 1376 -> 86 us, 2048 (512,
+// 8192) 3000 -> 524, 2048 (1024, 32000) 11.0 -> 3.6 ms, 4096 (3584, 152064) 118.7 -> 118.2 ms.
+//   FWD (A = W, B = gathered hidden rows): both K-contiguous, 256 x 64, so that the partials have
+//        the same 256-row blocks as bf16.
+//   DH  (A = E1, B[n][k] = W[k][n]): B K-major; K in p.ksplit parts (dh_reduce_kernel adds them).
+//   DW  (A[v][t] = E1[t][v], B[n][t] = c_t H[t][n]): both K-major.
+// Fragments: in step s of a tile, lane l of half h = l / 32 holds k = 8 s + 4 h + j for the j-th of
+// four MFMAs.  K-contiguous rows are 128 bytes, 16-byte chunk c kept in slot c ^ ((row >> 1) & 7):
+// one 16-byte read gives the four k, conflict-free over 16 rows.  K-major rows hold BM (or BN)
+// columns, chunk c in slot c ^ (((k >> 2) & 1) << 3): the two halves of a 4-byte read (k and k + 4)
+// fall on different banks.
+template <int MODE, int BM, int BN, int WM, int WN, int ST>
+__global__ __launch_bounds__(256) void f32_gemm_kernel(const GemmParams p) {
+  constexpr bool AKM = MODE == MODE_DW, BKM = MODE != MODE_FWD;
+  constexpr int BK = 32, MI = BM / WM / 32, NI = BN / WN / 32;
+  constexpr int ASZ = BM * BK, STAGE = (BM + BN) * BK;   // floats
+  constexpr int LA = BM / 32, LB = BN / 32;              // loads per wavefront and tile
+  static_assert(WM * WN == 4 && STAGE * ST * 4 <= 160 * 1024, "");
+  __shared__ __attribute__((aligned(16))) float smem[STAGE * ST];
+  if (MODE == MODE_FWD && p.store_e == 2 && p.redo_any[0] == 0) return;
+  const int nt = p.nmb * p.nnb;
+  const int part = MODE == MODE_DH ? int(blockIdx.x) / nt : 0;
+  const int b = int(blockIdx.x) - part * nt;
+  const int mb = b % p.nmb, nb = b / p.nmb;
+  const int m0 = mb * BM, n0 = nb * BN;
+  if (MODE == MODE_FWD && p.store_e == 2 && p.redo_blk[n0 / kBN] == 0) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  const float* Ag = static_cast<const float*>(p.A);
+  const float* Bg = static_cast<const float*>(p.B);
+  const int nk_all = (p.K + BK - 1) / BK;
+  const int kt0 = MODE == MODE_DH ? int(int64_t(nk_all) * part / p.ksplit) : 0;
+  const int nk = MODE == MODE_DH ? int(int64_t(nk_all) * (part + 1) / p.ksplit) - kt0 : nk_all;
+  // K-contiguous operand: load j of this wavefront fills rows 8 (wave L + j) + lane / 8; K-major:
+  // 256 / cols k-rows.  Rows and columns past the matrix load valid ones (results not stored).
+  int64_t abase[LA], bbase[LB];
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc16[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-    mainloop_bf16_dma<MODE>(p, m0, n0, acc16, smem);
-    if constexpr (MODE == MODE_FWD) fwd_epilogue_bf16(p, m0, n0, mb, acc16, smem);
-    else if constexpr (MODE == MODE_DH) dh_epilogue_bf16(p, m0, n0, acc16);
-    else dwt_epilogue_bf16(p, m0, n0, acc16);
-    return;
+  for (int j = 0; j < LA; ++j) {
+    if constexpr (AKM) abase[j] = 0;
+    else abase[j] = int64_t(min(m0 + 8 * (wave * LA + j) + (lane >> 3), p.M - 1)) * p.lda;
   }
-  f32x16_t acc[4][NI];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int j = 0; j < LB; ++j) {
+    if constexpr (BKM) {
+      bbase[j] = 0;
+    } else {
+      int64_t r = min(n0 + 8 * (wave * LB + j) + (lane >> 3), p.N - 1) + p.b_row_base;
+      if (p.b_rows) r = p.b_rows[r];
+      bbase[j] = r * p.ldb;
+    }
+  }
+  auto issue = [&](int kt, int stage) {
+    float* sa = smem + stage * STAGE + wave * LA * 256;
+    float* sb = smem + stage * STAGE + ASZ + wave * LB * 256;
+    const int kb = (kt0 + kt) * BK;
+    auto kcontig = [&](const float* g, int64_t base, int row, float* dst) {
+      // (chunks past a partial last tile load a valid one and are not read)
+      const int k = min(kb + (((lane & 7) ^ ((row >> 1) & 7)) << 2), p.K - 4);
+      __builtin_amdgcn_global_load_lds(g + base + k, (lds_void_t*)dst, 16, 0, 0);
+    };
+    auto kmajor = [&](const float* g, int64_t ld, int kmax, int c0, int cmax, int cols, int j, float* dst) {
+      const int cpr = cols / 4, rpl = 64 / cpr;  // chunks per row, rows per load
+      const int k = j * rpl + lane / cpr;
+      const int c = ((lane % cpr) ^ (((k >> 2) & 1) << 3)) << 2;
+      __builtin_amdgcn_global_load_lds(g + int64_t(min(kb + k, kmax)) * ld + min(c0 + c, cmax),
+                                       (lds_void_t*)dst, 16, 0, 0);
+    };
+#pragma unroll
+    for (int j = 0; j < LA; ++j) {
+      if constexpr (AKM) kmajor(Ag, p.lda, p.K - 1, m0, int(p.lda) - 4, BM, wave * LA + j, sa + j * 256);
+      else kcontig(Ag, abase[j], 8 * (wave * LA + j) + (lane >> 3), sa + j * 256);
+    }
+#pragma unroll
+    for (int j = 0; j < LB; ++j) {
+      if constexpr (BKM)
+        kmajor(Bg, p.ldb, MODE == MODE_DH ? p.Vreal - 1 : p.K - 1, n0, p.N - 4, BN, wave * LB + j,
+               sb + j * 256);
+      else kcontig(Bg, bbase[j], 8 * (wave * LB + j) + (lane >> 3), sb + j * 256);
+    }
+  };
+  const int l31 = lane & 31, half = lane >> 5;
+  f32x16_t acc[MI][NI];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int j = 0; j < NI; ++j) acc[i][j] = f32x16_t{};
-  if constexpr (sizeof(T) == 4) mainloop_f32<MODE, MODE == MODE_DW>(p, m0, n0, acc, smem);
-
-  // ------------------------------------------------------------------ epilogues
-  if constexpr (MODE == MODE_FWD && sizeof(T) == 4) {  // float32 logits (bf16: fwd_epilogue_bf16)
-    __syncthreads();  // LDS operand buffers are reused for the cross-wave exchange
-    float* xmax = reinterpret_cast<float*>(smem);      // [2 wm][256 cols]
-    float* xsum = xmax + 2 * kBN;
-    float* xsz = xsum + 2 * kBN;
-    const int Vr = p.Vreal;
-    // with a stored exp (store_e != 0) the block's sum is taken relative to the row's shift
-    // s_t, sum_v exp(z - s_t): one exp per logit serves both the sum and the stored E.  The
-    // merge checks that max_t - s_t stays inside (-60, 60) and re-runs rows that do not.
-    const bool rel = p.store_e != 0;
-    const bool rows_full = m0 + kBM <= Vr;  // every vocab row of this block exists
+  // the four k of step s for row / column r of the tile
+  auto frag = [&](bool km, const float* t, int r, int cols, int s) {
+    if (km) {
+      const int k = 8 * s + 4 * half;
+      const float* q = t + k * cols + (r ^ (half << 5));
+      return f32x4_t{q[0], q[cols], q[2 * cols], q[3 * cols]};
+    }
+    return *reinterpret_cast<const f32x4_t*>(t + r * BK + (((2 * s + half) ^ ((r >> 1) & 7)) << 2));
+  };
+  constexpr int PF = ST - 1;  // tiles in flight
 #pragma unroll
-    for (int ni = 0; ni < NI; ++ni) {
-      const int cl = acc_col<T, MODE>(wn, ni, lane);
-      const int t = n0 + cl;                 // slab token
+  for (int i = 0; i < PF; ++i)
+    if (i < nk) issue(i, i);
+  for (int kt = 0; kt < nk; ++kt) {
+    // own loads of tile kt have landed (later tiles' may be in flight), then everybody's have and
+    // nobody reads the stage that the next load fills
+    // (a plain s_barrier: __syncthreads would also wait for the later tiles' loads)
+    if (kt + PF <= nk) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((PF - 1) * (LA + LB)) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (kt + PF < nk) issue(kt + PF, (kt + PF) % ST);
+    const float* as = smem + (kt % ST) * STAGE;
+    const float* bs = as + ASZ;
+    const int ns = min(4, (p.K - (kt0 + kt) * BK + 7) / 8);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      if (s >= ns) break;
+      f32x4_t fa[MI], fb[NI];
+#pragma unroll
+      for (int i = 0; i < MI; ++i) fa[i] = frag(AKM, as, wm * (BM / WM) + i * 32 + l31, BM, s);
+#pragma unroll
+      for (int j = 0; j < NI; ++j) fb[j] = frag(BKM, bs, wn * (BN / WN) + j * 32 + l31, BN, s);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+          for (int j = 0; j < NI; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][q], fb[j][q], acc[i][j], 0, 0, 0);
+    }
+  }
+  // acc[i][j][r]: row 32 i + 8 (r / 4) + 4 half + r % 4, column 32 j + l31 of the wavefront's part
+  const int rw = wm * (BM / WM) + 4 * half, cw = wn * (BN / WN) + l31;
+  if constexpr (MODE == MODE_FWD) {
+    // per token column: the block's max and sum of exp, E1 and the sampled token's logit, as in
+    // fwd_epilogue_bf16; a column's 256 rows are spread over the two halves of four wavefronts
+    __syncthreads();  // LDS operand buffers are reused for the cross-wave exchange
+    float* xmax = smem;  // [4][BN]
+    float* xsum = xmax + WM * BN;
+    float* xsz = xsum + WM * BN;
+    const int Vr = p.Vreal;
+    const bool rel = p.store_e != 0;
+    auto row = [&](int i, int r) { return m0 + rw + 32 * i + 8 * (r >> 2) + (r & 3); };
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+      const int cl = cw + 32 * j, t = n0 + cl;
       const bool tok_ok = t < p.N;
       const int y = tok_ok ? p.yslab[t] : -1;
       // columns past the slab store exp(z - inf) = 0
       const float s_t = tok_ok ? (p.shift ? p.shift[t] : 0.0f) : INFINITY;
-      // four independent chains (one per 32-row group), combined at the end
-      float mxp[4];
+      float mx = -INFINITY;
 #pragma unroll
-      for (int mi = 0; mi < 4; ++mi) {
-        mxp[mi] = -INFINITY;
-        if (rows_full) {
+      for (int i = 0; i < MI; ++i)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) mxp[mi] = fmaxf(mxp[mi], acc[mi][ni][r]);
-        } else {
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            mxp[mi] = (m0 + acc_row(wm, mi, r, lane) < Vr) ? fmaxf(mxp[mi], acc[mi][ni][r]) : mxp[mi];
+        for (int r = 0; r < 16; ++r) {
+          mx = fmaxf(mx, row(i, r) < Vr ? acc[i][j][r] : -INFINITY);
+          if (row(i, r) == y) p.zlab[t] = acc[i][j][r];
         }
-      }
-      float mx = fmaxf(fmaxf(mxp[0], mxp[1]), fmaxf(mxp[2], mxp[3]));
-      // the sampled token's logit: held by one lane half of one wavefront (rare per column)
-      const int dy = y - m0 - wm * 128;
-      if (dy >= 0 && dy < 128 && ((dy >> 2) & 1) == (lane >> 5)) {
-        float zl = 0.0f;
-#pragma unroll
-        for (int mi = 0; mi < 4; ++mi)
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            zl = (mi * 32 + (r >> 2) * 8 + (r & 3) == (dy & ~4)) ? acc[mi][ni][r] : zl;
-        p.zlab[t] = zl;
-      }
       mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      if (lane < 32) xmax[wm * kBN + cl] = mx;
+      if (half == 0) xmax[wm * BN + cl] = mx;
       if (rel) {
-        // sum exp(z - s_t) and sum exp(z - s_t) z, one chain per 32-row group
         float ssp[4] = {0.0f, 0.0f, 0.0f, 0.0f}, zsp[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        T* e1 = static_cast<T*>(p.E1) + int64_t(t) * p.ldE1;
+        float* e1 = static_cast<float*>(p.E1) + int64_t(t) * p.ldE1;
 #pragma unroll
-        for (int mi = 0; mi < 4; ++mi) {
+        for (int i = 0; i < MI; ++i)
 #pragma unroll
           for (int rg = 0; rg < 4; ++rg) {
             float e[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-              e[q] = __expf(acc[mi][ni][rg * 4 + q] - s_t);
-              if (!rows_full && m0 + acc_row(wm, mi, rg * 4 + q, lane) >= Vr) e[q] = 0.0f;
-              ssp[mi] += e[q];
-              zsp[mi] = fmaf(e[q], acc[mi][ni][rg * 4 + q], zsp[mi]);
+              const float z = acc[i][j][rg * 4 + q];
+              e[q] = row(i, rg * 4 + q) < Vr ? __expf(z - s_t) : 0.0f;
+              ssp[rg] += e[q];
+              zsp[rg] = fmaf(e[q], z, zsp[rg]);
             }
-            const int v0 = m0 + acc_row(wm, mi, rg * 4, lane);
-            *reinterpret_cast<float4*>(e1 + v0) = make_float4(e[0], e[1], e[2], e[3]);
+            *reinterpret_cast<float4*>(e1 + row(i, rg * 4)) = make_float4(e[0], e[1], e[2], e[3]);
           }
-        }
         float ssum = (ssp[0] + ssp[1]) + (ssp[2] + ssp[3]);
         float zsum = (zsp[0] + zsp[1]) + (zsp[2] + zsp[3]);
         ssum += __shfl_xor(ssum, 32, 64);
         zsum += __shfl_xor(zsum, 32, 64);
-        if (lane < 32) {
-          xsum[wm * kBN + cl] = ssum;
-          xsz[wm * kBN + cl] = zsum;
+        if (half == 0) {
+          xsum[wm * BN + cl] = ssum;
+          xsz[wm * BN + cl] = zsum;
         }
       }
     }
     __syncthreads();
+    auto col_max = [&](int cl) {
+      return fmaxf(fmaxf(xmax[cl], xmax[BN + cl]), fmaxf(xmax[2 * BN + cl], xmax[3 * BN + cl]));
+    };
     if (!rel) {
 #pragma unroll
-      for (int ni = 0; ni < NI; ++ni) {
-        const int cl = acc_col<T, MODE>(wn, ni, lane);
-        const float M = fmaxf(xmax[cl], xmax[kBN + cl]);
+      for (int j = 0; j < NI; ++j) {
+        const int cl = cw + 32 * j;
+        const float M = col_max(cl);
         float ssp[4] = {0.0f, 0.0f, 0.0f, 0.0f}, zsp[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int mi = 0; mi < 4; ++mi)
+        for (int i = 0; i < MI; ++i)
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
-            const int v = m0 + acc_row(wm, mi, r, lane);
-            if (v < Vr) {
-              const float ex = __expf(acc[mi][ni][r] - M);
-              ssp[mi] += ex;
-              zsp[mi] = fmaf(ex, acc[mi][ni][r], zsp[mi]);
+            const float z = acc[i][j][r];
+            if (row(i, r) < Vr) {
+              const float ex = __expf(z - M);
+              ssp[r >> 2] += ex;
+              zsp[r >> 2] = fmaf(ex, z, zsp[r >> 2]);
             }
           }
         float ssum = (ssp[0] + ssp[1]) + (ssp[2] + ssp[3]);
         float zsum = (zsp[0] + zsp[1]) + (zsp[2] + zsp[3]);
         ssum += __shfl_xor(ssum, 32, 64);
         zsum += __shfl_xor(zsum, 32, 64);
-        if (lane < 32) {
-          xsum[wm * kBN + cl] = ssum;
-          xsz[wm * kBN + cl] = zsum;
+        if (half == 0) {
+          xsum[wm * BN + cl] = ssum;
+          xsz[wm * BN + cl] = zsum;
         }
       }
       __syncthreads();
     }
-    for (int cl = tid; cl < kBN; cl += NT) {
-      const int t = n0 + cl;
-      if (t < p.N) {
-        p.pmax[int64_t(mb) * p.ldp + t] = fmaxf(xmax[cl], xmax[kBN + cl]);
-        p.psum[int64_t(mb) * p.ldp + t] = xsum[cl] + xsum[kBN + cl];
-        if (p.psz) p.psz[int64_t(mb) * p.ldp + t] = xsz[cl] + xsz[kBN + cl];
-      }
+    if (tid < BN && n0 + tid < p.N) {
+      const int64_t o = int64_t(mb) * p.ldp + n0 + tid;
+      auto sum4 = [&](const float* x) {
+        return (x[tid] + x[BN + tid]) + (x[2 * BN + tid] + x[3 * BN + tid]);
+      };
+      p.pmax[o] = col_max(tid);
+      p.psum[o] = sum4(xsum);
+      if (p.psz) p.psz[o] = sum4(xsz);
     }
-  } else if constexpr (MODE == MODE_DH && !Geo<T, MODE>::W8) {  // dH[t] = -c_t C[t]
+  } else {
 #pragma unroll
-    for (int mi = 0; mi < 4; ++mi)
+    for (int i = 0; i < MI; ++i) {
+      auto row = [&](int r) { return m0 + rw + 32 * i + 8 * (r >> 2) + (r & 3); };
+      // the loads of 16 rows first, so that their latencies overlap
+      float prev[16][NI];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int t = m0 + acc_row(wm, mi, r, lane);
-        if (t < p.M) {
-          const float c = p.cslab[t];
+      for (int r = 0; r < 16; ++r)
 #pragma unroll
-          for (int ni = 0; ni < NI; ++ni) {
-            const int n = n0 + acc_col<T, MODE>(wn, ni, lane);
-            if (n < p.N) {
-              const float val = -c * acc[mi][ni][r];
-              const int64_t o = int64_t(t) * p.d + n;
-              if (p.dH_bf16) static_cast<uint16_t*>(p.dH)[o] = f32_to_bf16(val);
-              else static_cast<float*>(p.dH)[o] = val;
-            }
-          }
-        }
-      }
-  } else {  // MODE_DW: dW[v] (+)= -C[v] (the one-hot term is already in E1)
-    // RB rows at a time
-    constexpr int RB = 4;
-#pragma unroll
-    for (int mi = 0; mi < 4; ++mi)
-#pragma unroll
-      for (int rh = 0; rh < 16; rh += RB) {
-        // every load of these rows first, so that their latencies overlap
-        float prev[RB][NI];
-#pragma unroll
-        for (int r = 0; r < RB; ++r) {
-          const int v = m0 + acc_row(wm, mi, rh + r, lane);
-#pragma unroll
-          for (int ni = 0; ni < NI; ++ni) {
-            const int n = n0 + acc_col<T, MODE>(wn, ni, lane);
-            prev[r][ni] = (p.dW_acc && v < p.M && n < p.N) ? p.dW[int64_t(v) * p.d + n] : 0.0f;
-          }
+        for (int j = 0; j < NI; ++j) {
+          const int n = n0 + cw + 32 * j;
+          if constexpr (MODE == MODE_DH)
+            prev[r][j] = p.ksplit == 1 && row(r) < p.M ? -p.cslab[row(r)] : 1.0f;
+          else
+            prev[r][j] = p.dW_acc && row(r) < p.M && n < p.N ? p.dW[int64_t(row(r)) * p.d + n] : 0.0f;
         }
 #pragma unroll
-        for (int r = 0; r < RB; ++r) {
-          const int v = m0 + acc_row(wm, mi, rh + r, lane);
+      for (int r = 0; r < 16; ++r)
 #pragma unroll
-          for (int ni = 0; ni < NI; ++ni) {
-            const int n = n0 + acc_col<T, MODE>(wn, ni, lane);
-            if (v < p.M && n < p.N) p.dW[int64_t(v) * p.d + n] = prev[r][ni] - acc[mi][ni][rh + r];
+        for (int j = 0; j < NI; ++j) {
+          const int n = n0 + cw + 32 * j;
+          if (row(r) >= p.M || n >= p.N) continue;
+          const int64_t o = int64_t(row(r)) * p.d + n;
+          if constexpr (MODE == MODE_DH) {
+            const float v = prev[r][j] * acc[i][j][r];
+            if (p.ksplit > 1) p.part[int64_t(part) * p.M * p.d + o] = v;
+            else if (p.dH_bf16) static_cast<uint16_t*>(p.dH)[o] = f32_to_bf16(v);
+            else static_cast<float*>(p.dH)[o] = v;
+          } else {  // dW[v] (+)= -C[v] (the one-hot term is already in E1)
+            p.dW[o] = prev[r][j] - acc[i][j][r];
           }
         }
-      }
+    }
   }
 }
 
@@ -1067,7 +998,7 @@ void lm_gemm_kernel(const GemmParams p) {
 // dhidden tiles, a 19K-token slab at d = 1536 only 1.7).
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void lm_bwd_kernel(const GemmParams q, const GemmParams r) {
-  __shared__ __attribute__((aligned(16))) char smem_raw[SmemBytes<uint16_t>::value];
+  __shared__ __attribute__((aligned(16))) char smem_raw[kSmemBytes];
   uint16_t* smem = reinterpret_cast<uint16_t*>(smem_raw);
   const int nh = q.nmb * q.nnb;
   const int b = blockIdx.x;
@@ -1095,7 +1026,7 @@ void lm_bwd_kernel(const GemmParams q, const GemmParams r) {
 // dh_reduce_kernel adds them in part order.
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void lm_bwd_direct_kernel(const GemmParams q, const GemmParams r) {
-  __shared__ __attribute__((aligned(16))) char smem_raw[SmemBytes<uint16_t>::value];
+  __shared__ __attribute__((aligned(16))) char smem_raw[kSmemBytes];
   uint16_t* smem = reinterpret_cast<uint16_t*>(smem_raw);
   const int nt = q.nmb * q.nnb, nh = nt * q.ksplit;
   const int b = blockIdx.x;
@@ -1153,7 +1084,7 @@ __global__ __launch_bounds__(256) void dh_reduce_kernel(const float* __restrict_
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void lm_redo_kernel(const GemmParams p) {
   if (p.redo_any[0] == 0) return;
-  __shared__ __attribute__((aligned(16))) char smem_raw[SmemBytes<uint16_t>::value];
+  __shared__ __attribute__((aligned(16))) char smem_raw[kSmemBytes];
   uint16_t* smem = reinterpret_cast<uint16_t*>(smem_raw);
   const int nt = p.nmb * p.nnb;
   for (int b = blockIdx.x; b < nt; b += gridDim.x) {
@@ -1423,14 +1354,13 @@ __global__ void loss_final_kernel(const double* __restrict__ seq_loss,
 // out[c][r] = scale(r) * in[row(r)][c], zero for r in [R, Rpad): 64 x 64 tiles through LDS with
 // 16-byte global loads and stores (C is a multiple of 8, in 16-byte aligned, Rpad and ldo
 // multiples of 64, out 256-byte aligned)
-template <typename T>
 __global__ __launch_bounds__(256) void transpose_scale_kernel(
-    const T* __restrict__ in, const int32_t* __restrict__ row_index, int64_t row_base,
-    int32_t R, int32_t Rpad, int32_t C, const float* __restrict__ scale, T* __restrict__ out,
+    const uint16_t* __restrict__ in, const int32_t* __restrict__ row_index, int64_t row_base,
+    int32_t R, int32_t Rpad, int32_t C, const float* __restrict__ scale, uint16_t* __restrict__ out,
     int64_t ldo) {
-  constexpr int VEC = 16 / sizeof(T);  // elements per 16-byte piece: 8 bf16 or 4 float
-  constexpr int LPR = 64 / VEC;        // threads per 64-element tile row
-  constexpr int RPP = 256 / LPR;       // tile rows per pass
+  constexpr int VEC = 8;          // elements per 16-byte piece
+  constexpr int LPR = 64 / VEC;   // threads per 64-element tile row
+  constexpr int RPP = 256 / LPR;  // tile rows per pass
   __shared__ float tile[64][65];
   const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
   const int tid = threadIdx.x;
@@ -1445,12 +1375,8 @@ __global__ __launch_bounds__(256) void transpose_scale_kernel(
       const float sc = scale ? scale[r] : 1.0f;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        if constexpr (sizeof(T) == 2) {
-          v[2 * q] = bf16_to_f32(uint16_t(raw[q] & 0xffffu)) * sc;
-          v[2 * q + 1] = bf16_to_f32(uint16_t(raw[q] >> 16)) * sc;
-        } else {
-          v[q] = __uint_as_float(raw[q]) * sc;
-        }
+        v[2 * q] = bf16_to_f32(uint16_t(raw[q] & 0xffffu)) * sc;
+        v[2 * q + 1] = bf16_to_f32(uint16_t(raw[q] >> 16)) * sc;
       }
     } else {
 #pragma unroll
@@ -1465,16 +1391,31 @@ __global__ __launch_bounds__(256) void transpose_scale_kernel(
     if (c < C && r0 + l < Rpad) {
       u32x4_t o;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if constexpr (sizeof(T) == 2)
-          o[q] = uint32_t(f32_to_bf16(tile[l + 2 * q][cc])) |
-                 (uint32_t(f32_to_bf16(tile[l + 2 * q + 1][cc])) << 16);
-        else
-          o[q] = __float_as_uint(tile[l + q][cc]);
-      }
+      for (int q = 0; q < 4; ++q)
+        o[q] = uint32_t(f32_to_bf16(tile[l + 2 * q][cc])) |
+               (uint32_t(f32_to_bf16(tile[l + 2 * q + 1][cc])) << 16);
       *reinterpret_cast<u32x4_t*>(out + int64_t(c) * ldo + r0 + l) = o;
     }
   }
+}
+
+// out[r] = scale[r] * in[row(r)] for r < R, zero rows up to Rpad (float32 dW: hidden rows times c_t)
+__global__ __launch_bounds__(256) void scale_rows_f32_kernel(
+    const float* __restrict__ in, const int32_t* __restrict__ row_index, int64_t row_base,
+    int32_t R, int32_t Rpad, int32_t C, const float* __restrict__ scale, float* __restrict__ out) {
+  const int c4 = C / 4;
+  const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
+  const int r = int(i / c4);
+  if (r >= Rpad) return;
+  f32x4_t v = {0.0f, 0.0f, 0.0f, 0.0f};
+  if (r < R) {
+    int64_t row = row_base + r;
+    if (row_index) row = row_index[row];
+    v = reinterpret_cast<const f32x4_t*>(in + row * C)[i % c4];
+    const float s = scale[r];
+    v = f32x4_t{s * v[0], s * v[1], s * v[2], s * v[3]};
+  }
+  reinterpret_cast<f32x4_t*>(out)[i] = v;
 }
 
 __global__ void fill_i32_kernel(int32_t* p, int64_t n, int32_t v) {
@@ -1487,6 +1428,17 @@ __global__ void fill_i32_kernel(int32_t* p, int64_t n, int32_t v) {
 
 static inline int64_t rup(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 
+constexpr int kMaxKSplit = 32;  // parts of K of a dhidden GEMM
+constexpr int BK_F32 = 32;      // K step of the float32 GEMMs
+
+static int launch_dh_reduce(const GemmParams& q, hipStream_t stream) {
+  const int64_t n4 = int64_t(q.M) * (q.d / 4);
+  hipLaunchKernelGGL(dh_reduce_kernel, dim3(unsigned((n4 + 255) / 256)), dim3(256), 0, stream,
+                     q.part, q.ksplit, q.M, q.d, q.cslab, q.dH, q.dH_bf16);
+  FR_LAUNCHED();
+  return FASTRL_OK;
+}
+
 // Tile group of a GEMM (tile_coords), measured back to back on the two hidden sizes of the
 // workloads: the logits GEMM takes 32 at K = d = 3584 (8 and 16 lose 5% and 2.5% there, 64 is
 // level) and 16 at d = 1536 (+5% on that GEMM against 32; 8, 12, 20, 24 and 64 are slower
@@ -1498,26 +1450,66 @@ static int tile_group(int mode, int32_t K, int32_t nnb) {
   return 4;
 }
 
+// Tiles of a float32 GEMM.  The gradient GEMMs take 128 x 128 tiles where those alone fill the
+// chip twice, else 64 x 64; dhidden then cuts its K (the vocabulary) so that there are about two
+// blocks per compute unit, of at least 8 K steps each.
+template <int MODE, int BM, int BN, int WM, int WN, int ST>
+static int launch_f32_tiles(GemmParams p, int kind, double flops, hipStream_t stream) {
+  p.nmb = int((p.M + BM - 1) / BM);
+  p.nnb = int((p.N + BN - 1) / BN);
+  const int64_t nblk = int64_t(p.nmb) * p.nnb * (MODE == MODE_DH ? p.ksplit : 1);
+  if (nblk == 0) return FASTRL_OK;
+  FR_CHECK_ARG(nblk < (int64_t(1) << 31) && p.K >= 8 && p.N >= (MODE == MODE_FWD ? 1 : 8) &&
+                   (MODE == MODE_FWD ? p.K % 8 == 0 : p.K % BK_F32 == 0),
+               FASTRL_ERR_UNSUPPORTED, "float32 GEMM: unsupported shape");
+  {
+    ProfScope prof(kind, stream, flops);
+    hipLaunchKernelGGL((f32_gemm_kernel<MODE, BM, BN, WM, WN, ST>), dim3(unsigned(nblk)), dim3(256),
+                       0, stream, p);
+    FR_LAUNCHED();
+  }
+  if (MODE == MODE_DH && p.ksplit > 1) return launch_dh_reduce(p, stream);
+  return FASTRL_OK;
+}
+
+static bool f32_big_tiles(int64_t M, int64_t N) {
+  return ((M + 127) / 128) * ((N + 127) / 128) >= 512;
+}
+
+static int f32_ksplit(int64_t M, int64_t N, int32_t V) {
+  const int64_t b = f32_big_tiles(M, N) ? 128 : 64;
+  const int64_t nt = ((M + b - 1) / b) * ((N + b - 1) / b), nk = (V + BK_F32 - 1) / BK_F32;
+  return int(std::max<int64_t>(1, std::min<int64_t>({512 / nt, nk / 8, kMaxKSplit})));
+}
+
+template <int MODE>
+static int launch_f32(const GemmParams& p, int kind, double flops, hipStream_t stream) {
+  if constexpr (MODE == MODE_FWD)
+    return launch_f32_tiles<MODE, 256, 64, 4, 1, 2>(p, kind, flops, stream);
+  else if (f32_big_tiles(p.M, p.N))
+    return launch_f32_tiles<MODE, 128, 128, 2, 2, 2>(p, kind, flops, stream);
+  else
+    return launch_f32_tiles<MODE, 64, 64, 2, 2, 4>(p, kind, flops, stream);
+}
+
 template <typename T, int MODE>
 static int launch_gemm(GemmParams p, int kind, double flops, hipStream_t stream) {
+  if constexpr (sizeof(T) == 4) return launch_f32<MODE>(p, kind, flops, stream);
+  else {
   p.nmb = int((p.M + kBM - 1) / kBM);
   p.nnb = int((p.N + kBN - 1) / kBN);
   p.group = tile_group(MODE, p.K, p.nnb);
   const int64_t nblk = int64_t(p.nmb) * p.nnb;
   if (nblk == 0) return FASTRL_OK;
-  FR_CHECK_ARG(sizeof(T) != 2 || MODE != MODE_DW ||
-                   (p.K % 64 == 0 && p.lda < (int64_t(1) << 23) && p.ldb < (int64_t(1) << 23)),
-               FASTRL_ERR_UNSUPPORTED,
-               "dW GEMM: K must be a multiple of 64 and leading dimensions below 2^23");
   // transposed dW: whole 64-k tiles, whole 256-column tiles of the K-major E, 16-byte dW rows
   FR_CHECK_ARG(MODE != MODE_DWT || (p.K % 64 == 0 && p.ldb >= int64_t(p.nnb) * kBN &&
                                     p.ldb % 8 == 0 && p.d % 4 == 0 && p.M == p.d),
                FASTRL_ERR_UNSUPPORTED, "transposed dW GEMM: unsupported shape");
   ProfScope prof(kind, stream, flops);
-  hipLaunchKernelGGL((lm_gemm_kernel<T, MODE>), dim3(unsigned(nblk)), dim3(Geo<T, MODE>::THREADS), 0,
-                     stream, p);
+  hipLaunchKernelGGL((lm_gemm_kernel<T, MODE>), dim3(unsigned(nblk)), dim3(kThreads), 0, stream, p);
   FR_LAUNCHED();
   return FASTRL_OK;
+  }
 }
 
 // dhidden (q, MODE_DH) and transposed dW (r, MODE_DWT) of one bf16 slab in one launch
@@ -1548,10 +1540,10 @@ static int launch_bwd(GemmParams q, GemmParams r, double flops, hipStream_t stre
 // 20986, 16384 41628 -> 40899, 32768 82320 -> 83281, 131072 330.4 -> 333.6 ms; d = 2048
 // (V = 100000) 27000 27029 -> 27136.
 constexpr int64_t kDirectTokens = 20480;
-constexpr int kMaxKSplit = 32;
 
+// (float32 dhidden always reads W itself)
 static bool direct_dh(const fastrl_loss_args& a) {
-  return a.dtype == FASTRL_BF16 && a.dhidden != nullptr && a.T <= kDirectTokens;
+  return a.dhidden != nullptr && (a.dtype == FASTRL_F32 || a.T <= kDirectTokens);
 }
 
 // Parts of K for the dhidden tiles of a Tc-token slab: the count whose estimated time is least,
@@ -1559,7 +1551,8 @@ static bool direct_dh(const fastrl_loss_args& a) {
 // long as its dhidden rounds (parts x tiles over 256 compute units, each K / parts plus ~6 steps
 // of start and end) and as its total work spread evenly (a dW tile: its K plus ~9 steps); parts
 // add their float32 sums' traffic (written and read at ~5 TB/s).
-static int dh_ksplit(int32_t Tc, int32_t d, int32_t V, bool dw) {
+static int dh_ksplit(int32_t Tc, int32_t d, int32_t V, int32_t dtype, bool dw) {
+  if (dtype == FASTRL_F32) return f32_ksplit(Tc, d, V);
   const double nt = double((Tc + kBM - 1) / kBM) * double((d + kBN - 1) / kBN);
   const double nk = double((V + 63) / 64);
   const double wt = dw ? double((V + kBN - 1) / kBN) * double((d + kBM - 1) / kBM) : 0.0;
@@ -1602,12 +1595,7 @@ static int launch_bwd_direct(GemmParams q, GemmParams r, bool dw, double flops,
     hipLaunchKernelGGL(lm_bwd_direct_kernel, dim3(unsigned(nh + nw)), dim3(512), 0, stream, q, r);
     FR_LAUNCHED();
   }
-  if (q.ksplit > 1) {
-    const int64_t n4 = int64_t(q.M) * (q.d / 4);
-    hipLaunchKernelGGL(dh_reduce_kernel, dim3(unsigned((n4 + 255) / 256)), dim3(256), 0, stream,
-                       q.part, q.ksplit, q.M, q.d, q.cslab, q.dH, q.dH_bf16);
-    FR_LAUNCHED();
-  }
+  if (q.ksplit > 1) return launch_dh_reduce(q, stream);
   return FASTRL_OK;
 }
 
@@ -1843,7 +1831,7 @@ static size_t carve_loss(Carver& c, LossWs& w, const fastrl_loss_args& a, const 
   if (direct_dh(a))
     for (size_t si = 0; si + 1 < pl.seq_begin.size(); ++si) {
       const int64_t Tc = a.seq_off_host[pl.seq_begin[si + 1]] - a.seq_off_host[pl.seq_begin[si]];
-      const int ks = Tc > 0 ? dh_ksplit(int32_t(Tc), a.d, a.V, dw) : 1;
+      const int ks = Tc > 0 ? dh_ksplit(int32_t(Tc), a.d, a.V, a.dtype, dw) : 1;
       if (ks > 1) wt = std::max(wt, Tc * ks * a.d * int64_t(sizeof(float)));
     }
   w.WT = dh ? c.take<char>(size_t(wt)) : nullptr;
@@ -1912,9 +1900,9 @@ static int policy_loss_impl(const fastrl_loss_args& a, hipStream_t stream) {
   const bool direct = direct_dh(a);
   if (dh && !direct && a.S > 0) {
     dim3 g(nb1d(d, 64), unsigned(Vpad / 64));
-    hipLaunchKernelGGL((transpose_scale_kernel<T>), g, dim3(256), 0, stream,
-                       static_cast<const T*>(a.W), (const int32_t*)nullptr, int64_t(0), V,
-                       int32_t(Vpad), d, (const float*)nullptr, static_cast<T*>(w.WT), Vpad);
+    hipLaunchKernelGGL(transpose_scale_kernel, g, dim3(256), 0, stream,
+                       static_cast<const uint16_t*>(a.W), (const int32_t*)nullptr, int64_t(0), V,
+                       int32_t(Vpad), d, (const float*)nullptr, static_cast<uint16_t*>(w.WT), Vpad);
     FR_LAUNCHED();
   }
   const size_t nslab = pl.seq_begin.size() - 1;
@@ -1988,29 +1976,29 @@ static int policy_loss_impl(const fastrl_loss_args& a, hipStream_t stream) {
       q.cslab = w.cslab; q.d = d;
       q.status = a.status;
       if (direct) {
-        q.B = a.W; q.ldb = d; q.K = int32_t(rup(V, 64)); q.Vreal = V;
-        q.ksplit = dh_ksplit(Tc, d, V, dw);
+        q.B = a.W; q.ldb = d; q.K = int32_t(rup(V, sizeof(T) == 2 ? 64 : BK_F32)); q.Vreal = V;
+        q.ksplit = dh_ksplit(Tc, d, V, a.dtype, dw);
         q.part = static_cast<float*>(w.WT);
       }
     }
     // bf16 with both gradients: the two GEMMs run as one launch (after dW's inputs are ready)
     const bool fused = dh && dw && sizeof(T) == 2;
-    if (dh && !dw && direct)
+    if (dh && !dw && direct && sizeof(T) == 2)
       FR_TRY(launch_bwd_direct(q, GemmParams{}, false, 2.0 * double(Tc) * d * V, stream));
     else if (dh && !fused)
       FR_TRY((launch_gemm<T, MODE_DH>(q, FASTRL_K_DHIDDEN, 2.0 * double(Tc) * d * V, stream)));
     if (dw) {
-      dim3 g(nb1d(d, 64), unsigned(Tr / 64));
-      hipLaunchKernelGGL((transpose_scale_kernel<T>), g, dim3(256), 0, stream,
-                         static_cast<const T*>(a.hidden), a.row_index, t0, Tc, int32_t(Tr), d,
-                         w.cslab, static_cast<T*>(w.Bd), tcp);
-      FR_LAUNCHED();
       GemmParams r{};
-      r.K = int32_t(Tr);
       r.dW = a.dW; r.dW_acc = (dw_written || a.dW_accumulate) ? 1 : 0;
       r.d = d;
       r.status = a.status;
       if constexpr (sizeof(T) == 2) {  // dW^T = Bd E: A = Bd, B = E1 read K-major
+        dim3 g(nb1d(d, 64), unsigned(Tr / 64));
+        hipLaunchKernelGGL(transpose_scale_kernel, g, dim3(256), 0, stream,
+                           static_cast<const uint16_t*>(a.hidden), a.row_index, t0, Tc, int32_t(Tr),
+                           d, w.cslab, static_cast<uint16_t*>(w.Bd), tcp);
+        FR_LAUNCHED();
+        r.K = int32_t(Tr);
         r.A = w.Bd; r.lda = tcp; r.M = d;
         r.B = w.E1; r.ldb = Vpad; r.N = V;
         if (fused && direct)
@@ -2019,9 +2007,15 @@ static int policy_loss_impl(const fastrl_loss_args& a, hipStream_t stream) {
           FR_TRY(launch_bwd(q, r, 4.0 * double(V) * d * Tc, stream));
         else
           FR_TRY((launch_gemm<T, MODE_DWT>(r, FASTRL_K_DW, 2.0 * double(V) * d * Tc, stream)));
-      } else {  // dW = E^T Bd^T: A = E1 read K-major (A[v][t] = E1[t][v]), B = Bd
+      } else {  // dW = E^T Bd: A = E1 and B = Bd (here c_t H[t] as rows) both read K-major
+        r.K = int32_t(rup(Tc, BK_F32));
+        const int64_t n4 = int64_t(r.K) * (d / 4);
+        hipLaunchKernelGGL(scale_rows_f32_kernel, dim3(nb1d(n4, 256)), dim3(256), 0, stream,
+                           static_cast<const float*>(a.hidden), a.row_index, t0, Tc, r.K, d,
+                           w.cslab, static_cast<float*>(w.Bd));
+        FR_LAUNCHED();
         r.A = w.E1; r.lda = Vpad; r.M = V;
-        r.B = w.Bd; r.ldb = tcp; r.N = d;
+        r.B = w.Bd; r.ldb = d; r.N = d;
         FR_TRY((launch_gemm<T, MODE_DW>(r, FASTRL_K_DW, 2.0 * double(V) * d * Tc, stream)));
       }
       dw_written = true;

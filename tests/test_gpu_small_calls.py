@@ -93,3 +93,34 @@ def test_direct_dhidden_unaligned_output_and_repeat(fr):
         torch.cuda.synchronize()
         assert torch.equal(flat[1:].view(T, d), a.dhidden) and torch.equal(a.dW, b.dW)
         assert _rel(a.dhidden, dH) < 1e-2
+
+
+@pytest.mark.parametrize("T, d, V, accumulate, dh_dtype", [
+    (1, 8, 1, False, torch.float32),          # one of everything
+    (65, 72, 257, True, torch.float32),       # a token, some columns and a vocabulary row over a tile
+    (63, 40, 31, False, torch.bfloat16),      # fewer vocabulary rows than one K step
+    (200, 136, 3001, True, torch.float32),    # dhidden in parts, a partial last K step everywhere
+    (8200, 1024, 300, False, torch.float32),  # 128 x 128 dhidden tiles
+    (130, 512, 16400, True, torch.float32),   # 128 x 128 dW tiles
+])
+def test_float32_tiles(fr, T, d, V, accumulate, dh_dtype):
+    """float32 GEMM tiles: log-probs and gradients to float32 accuracy (1e-5: the sums' terms are
+    of mixed sign, and up to 16400 of them follow each other; bf16 dhidden to its rounding)."""
+    H, W, y, z, lse, logp, old = _problem(T, d, V, T + d, torch.float32)
+    off = np.asarray(sorted({0, T // 3, T // 3 + T // 2, T}), dtype=np.int64)
+    adv = torch.linspace(-1.0, 1.5, len(off) - 1)
+    loss, dH, dW = _reference(H, W, y, z, lse, logp, old, off, adv)
+    base = 1e-3 * torch.randn(V, d, generator=torch.Generator().manual_seed(1))
+    rows = torch.arange(T - 1, -1, -1, dtype=torch.int32)  # gathered: stored in reverse order
+    call = fr.policy_loss_fwd_bwd(
+        H.flip(0).contiguous().to(DEV), W.to(DEV), y.flip(0).contiguous().to(DEV),
+        old.flip(0).contiguous().to(DEV), torch.from_numpy(off).to(DEV), torch.from_numpy(off),
+        adv.to(DEV), row_index=rows.to(DEV), dhidden_dtype=dh_dtype, need_entropy=True,
+        dW=base.to(DEV) if accumulate else None, dW_accumulate=accumulate, T=T)
+    torch.cuda.synchronize()
+    assert (call.logp.double().cpu() - logp).abs().max() < 2e-5
+    ent = lse - (torch.exp(z - lse[:, None]) * z).sum(1)
+    assert (call.entropy.double().cpu() - ent).abs().max() < 2e-5
+    if V > 1:  # (one class: every gradient is exactly a difference of equal numbers)
+        assert _rel(call.dhidden, dH) < (1e-5 if dh_dtype == torch.float32 else 4e-3)
+        assert _rel(call.dW, dW + base.double() * accumulate) < 1e-5
