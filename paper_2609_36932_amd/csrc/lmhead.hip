@@ -63,6 +63,8 @@ struct GemmParams {
   int32_t K;
   int32_t nmb, nnb;         // block grid (M blocks, N blocks)
   int32_t group;            // tile order: M-blocks per sweep over the N-blocks (tile_group)
+  int32_t tail, pieces;     // FWD: the last `tail` whole tiles are cut into `pieces` (fwd_tiles)
+  int32_t narrow;           // FWD: 64-token columns of the narrow last tile column (0: none)
   // ---- FWD epilogue
   float* pmax;              // [nmb][ldp]
   float* psum;              // [nmb][ldp]
@@ -137,10 +139,12 @@ typedef __attribute__((address_space(3))) void lds_void_t;
 // c ^ ((r >> 1) & 7).  The LDS serves a 16-byte-per-lane read 16 lanes (256 B, 64 banks) at a
 // time, and rows r..r+15 of a fragment then land on 16 distinct 16-byte bank groups; the
 // swizzle is applied on the global side (each lane loads the chunk that belongs in its slot).
-template <int MODE>
+// NJ < 4 (logits only): a tile of 256 x 64 NJ, 128 x 16 NJ per wavefront.
+template <int MODE, int NJ = 4>
 __device__ __forceinline__ void mainloop_bf16_dma(const GemmParams& p, int m0, int n0,
-                                                  f32x4_t (&acc)[8][4], uint16_t* smem,
+                                                  f32x4_t (&acc)[8][NJ], uint16_t* smem,
                                                   int kt0 = 0, int nkt = 0) {
+  static_assert(NJ == 4 || MODE == MODE_FWD, "narrow tiles: logits only");
   constexpr int BK = 64;
   constexpr int TILE = kBM * BK;  // elements per operand per stage
   constexpr bool DHT = MODE == MODE_DHT;
@@ -153,8 +157,10 @@ __device__ __forceinline__ void mainloop_bf16_dma(const GemmParams& p, int m0, i
   const int lrow = lane >> 3;
   // global k-chunk this lane moves into its slot; rows r = 32 wave + 8 j + lrow, so
   // ((r >> 1) & 7) = 4 (j & 1) + (lrow >> 1)
-  const int gch[2] = {(lane & 7) ^ (lrow >> 1), (lane & 7) ^ (4 | (lrow >> 1))};
-  int64_t arow[4], brow[4];
+  const int gch0 = (lane & 7) ^ (lrow >> 1), gch1 = gch0 ^ 4;
+  int64_t arow[4], brow[NJ];
+  // B rows r = 8 (NJ wave + j) + lrow: the chunk of load j is gch0 or, for odd j + bodd, gch1
+  const int bodd = (NJ & 1) ? (wave & 1) : 0;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int r = wave * 32 + j * 8 + lrow;
@@ -174,18 +180,19 @@ __device__ __forceinline__ void mainloop_bf16_dma(const GemmParams& p, int m0, i
   if constexpr (!BKM) {
     // B rows, gathered through b_rows when given: the four index loads are issued together
     // (one memory round trip before the first tile load, not four one after the other)
-    int64_t bi[4];
+    int64_t bi[NJ];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) bi[j] = min(n0 + wave * 32 + j * 8 + lrow, p.N - 1) + p.b_row_base;
+    for (int j = 0; j < NJ; ++j)
+      bi[j] = min(n0 + (wave * NJ + j) * 8 + lrow, p.N - 1) + p.b_row_base;
     if (p.b_rows) {
-      int32_t g[4];
+      int32_t g[NJ];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) g[j] = __builtin_nontemporal_load(p.b_rows + bi[j]);
+      for (int j = 0; j < NJ; ++j) g[j] = __builtin_nontemporal_load(p.b_rows + bi[j]);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) bi[j] = g[j];
+      for (int j = 0; j < NJ; ++j) bi[j] = g[j];
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) brow[j] = bi[j] * p.ldb;
+    for (int j = 0; j < NJ; ++j) brow[j] = bi[j] * p.ldb;
   }
   // K-major B fragments (ds_read_b64_tr_b16): in 16-lane group g, lane jj reads 4 n of k-row
   // 8 g + 4 s + jj / 4 (s = first / second 4 k of the lane's 8) at n = 16 j + 4 (jj % 4) of
@@ -214,7 +221,7 @@ __device__ __forceinline__ void mainloop_bf16_dma(const GemmParams& p, int m0, i
       bfa[j] = uint32_t(uintptr_t((lds_u16_t*)(smem + TILE + bfo[j])));
   }
   // the B fragments pass through the wait as operands, so no use of them can precede it
-  auto frag_wait = [&](bf16x8_t (&fb)[4]) {
+  auto frag_wait = [&](bf16x8_t (&fb)[NJ]) {
     if constexpr (BKM) {
       __builtin_amdgcn_sched_barrier(0);
       asm volatile("s_waitcnt lgkmcnt(0)"
@@ -231,38 +238,42 @@ __device__ __forceinline__ void mainloop_bf16_dma(const GemmParams& p, int m0, i
   auto issue = [&](int kt, int stage) {
     if constexpr (DHT) kt += kt0;
     // clamp the chunk so a partial last tile never reads past the end of a row
-    const int kc0 = min(kt * BK + gch[0] * 8, K - 8);
-    const int kc1 = min(kt * BK + gch[1] * 8, K - 8);
+    const int kc0 = min(kt * BK + gch0 * 8, K - 8);
+    const int kc1 = min(kt * BK + gch1 * 8, K - 8);
     uint16_t* sa = smem + stage * 2 * TILE + wave * 32 * BK;
-    uint16_t* sb = sa + TILE;
+    uint16_t* sb = smem + stage * 2 * TILE + TILE + wave * NJ * 8 * BK;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int kc = (j & 1) ? kc1 : kc0;
       __builtin_amdgcn_global_load_lds(Ag + arow[j] + kc, (lds_void_t*)(sa + j * 8 * BK), 16, 0, 0);
+      if (j >= NJ) continue;
       // (K-major B: k-rows 8 wave + 2 j, + 1 start at the same LDS offset as rows 32 wave + 8 j)
       const uint16_t* bsrc;
       if constexpr (DHT)  // vocab rows past the end load the last one (their exp-logits are 0)
         bsrc = Bg + brow[j] +
                int64_t(min(kt * BK + wave * 8 + 2 * j + (lane >> 5), p.Vreal - 1)) * p.ldb;
       else
-        bsrc = BKM ? Bg + brow[j] + int64_t(kt) * BK * p.ldb : Bg + brow[j] + kc;
+        bsrc = BKM ? Bg + brow[j] + int64_t(kt) * BK * p.ldb
+                   : Bg + brow[j] + (NJ == 4 ? kc : ((j + bodd) & 1) ? kc1 : kc0);
       __builtin_amdgcn_global_load_lds(bsrc, (lds_void_t*)(sb + j * 8 * BK), 16, 0, 0);
     }
   };
   auto zero_tail = [&](int kt, int stage) {  // this lane's slots past K in tile kt
     uint16_t* sa = smem + stage * 2 * TILE + wave * 32 * BK + lane * 8;
+    uint16_t* sb = smem + stage * 2 * TILE + TILE + wave * NJ * 8 * BK + lane * 8;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if (kt * BK + gch[j & 1] * 8 >= K) {
+    for (int j = 0; j < 4; ++j)
+      if (kt * BK + ((j & 1) ? gch1 : gch0) * 8 >= K)
         *reinterpret_cast<u32x4_t*>(sa + j * 8 * BK) = u32x4_t{0u, 0u, 0u, 0u};
-        *reinterpret_cast<u32x4_t*>(sa + TILE + j * 8 * BK) = u32x4_t{0u, 0u, 0u, 0u};
-      }
-    }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+      if (kt * BK + (((j + bodd) & 1) ? gch1 : gch0) * 8 >= K)
+        *reinterpret_cast<u32x4_t*>(sb + j * 8 * BK) = u32x4_t{0u, 0u, 0u, 0u};
   };
   const int sw = ((lane & 15) >> 1) & 7;  // ((row >> 1) & 7) of the fragment rows this lane reads
   // fragments of the 32-k step kk (0, 1): A rows wm*128 + i*16 + (lane & 15) and B rows
-  // wn*64 + j*16 + (lane & 15), k-chunk 4 kk + lane / 16 (8 consecutive k per lane)
-  auto frags = [&](int stage, int kk, bf16x8_t (&fa)[8], bf16x8_t (&fb)[4]) {
+  // wn*16 NJ + j*16 + (lane & 15), k-chunk 4 kk + lane / 16 (8 consecutive k per lane)
+  auto frags = [&](int stage, int kk, bf16x8_t (&fa)[8], bf16x8_t (&fb)[NJ]) {
     const uint16_t* as = smem + stage * 2 * TILE;
     const uint16_t* bs = as + TILE;
     const int slot = ((kk * 4 + (lane >> 4)) ^ sw) * 8;
@@ -294,37 +305,37 @@ __device__ __forceinline__ void mainloop_bf16_dma(const GemmParams& p, int m0, i
 #pragma unroll
       for (int i = 0; i < 8; ++i) read_a(i);
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        fb[j] = *reinterpret_cast<const bf16x8_t*>(bs + (wn * 64 + j * 16 + (lane & 15)) * BK + slot);
+      for (int j = 0; j < NJ; ++j)
+        fb[j] = *reinterpret_cast<const bf16x8_t*>(bs + (wn * 16 * NJ + j * 16 + (lane & 15)) * BK + slot);
     }
   };
-  auto mma = [&](const bf16x8_t (&fa)[8], const bf16x8_t (&fb)[4]) {
+  auto mma = [&](const bf16x8_t (&fa)[8], const bf16x8_t (&fb)[NJ]) {
 #pragma unroll
     for (int i = 0; i < 8; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < NJ; ++j)
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
   };
-  auto mma_rows = [&](const bf16x8_t (&fa)[8], const bf16x8_t (&fb)[4], int i0, int i1) {
+  auto mma_rows = [&](const bf16x8_t (&fa)[8], const bf16x8_t (&fb)[NJ], int i0, int i1) {
 #pragma unroll
     for (int i = i0; i < i1; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < NJ; ++j)
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
   };
-  auto mma_half = [&](const bf16x8_t (&fa)[8], const bf16x8_t (&fb)[4], int h) {
+  auto mma_half = [&](const bf16x8_t (&fa)[8], const bf16x8_t (&fb)[NJ], int h) {
     mma_rows(fa, fb, 4 * h, 4 * h + 4);
   };
 
-  bf16x8_t fa0[8], fb0[4], fa1[8], fb1[4];
+  bf16x8_t fa0[8], fb0[NJ], fa1[8], fb1[NJ];
   // fragment reads per k-step that the scheduler places: 8 A reads and 4 B reads, or (K-major
   // B) the 8 A reads, each followed in program order by the assembly B reads
-  constexpr int NRD = BKM ? 8 : 12;
+  constexpr int NRD = BKM ? 8 : 8 + NJ;
   // pin the order inside a k-step: the 32 MFMAs of this step with the fragment reads of the
   // next step spread among the first 24 (at most one step's reads in flight, so the wait before
   // the next step's MFMAs is exact, and the last read still has 8 MFMAs to land)
-  auto kstep = [&](int stage, int kk_next, bf16x8_t (&fa)[8], bf16x8_t (&fb)[4],
-                   bf16x8_t (&na)[8], bf16x8_t (&nb)[4]) {
+  auto kstep = [&](int stage, int kk_next, bf16x8_t (&fa)[8], bf16x8_t (&fb)[NJ],
+                   bf16x8_t (&na)[8], bf16x8_t (&nb)[NJ]) {
     frag_wait(fb);
     // raised wave priority while this k-step's MFMAs issue: the SIMD's other wavefront (at a
     // barrier, its loads or its epilogue) yields the issue slots (+1-4% on dW, +0-2% on
@@ -338,14 +349,14 @@ __device__ __forceinline__ void mainloop_bf16_dma(const GemmParams& p, int m0, i
         __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);
         __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       }
-    } else {
+    } else if constexpr (NJ >= 3) {
 #pragma unroll
-      for (int q = 0; q < 12; ++q) {
+      for (int q = 0; q < NRD; ++q) {
         __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
         __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       }
     }
-    __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
+    if constexpr (NJ >= 3) __builtin_amdgcn_sched_group_barrier(0x008, 8 * NJ - 2 * (8 + NJ), 0);
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_setprio(0);
   };
@@ -413,7 +424,7 @@ __device__ __forceinline__ void mainloop_bf16_dma(const GemmParams& p, int m0, i
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
       __builtin_amdgcn_sched_group_barrier(0x020, 4, 0);
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x020, 4, 0);
+      __builtin_amdgcn_sched_group_barrier(0x020, NJ, 0);
     }
     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
     __builtin_amdgcn_sched_group_barrier(0x100, NRD / 2, 0);
@@ -451,14 +462,15 @@ __device__ __forceinline__ float group_max4(float x) {
 }
 
 // Epilogue of the bf16 logits GEMM (16 x 16 accumulator tiles: acc[i][j] covers vocab rows
-// wm*128 + 16 i .. +15 and tokens wn*64 + 16 j .. +15; lane l holds rows 4 (l / 16) + q of
+// wm*128 + 16 i .. +15 and tokens wn*16 NJ + 16 j .. +15; lane l holds rows 4 (l / 16) + q of
 // token column l % 16).  Per token column: the block's max over its vocab rows, the sampled
 // token's logit, and with a stored exp (store_e != 0) E[t][v] = exp(z - s_t) with the sums
 // sum exp(z - s_t) and sum exp(z - s_t) z; without one (old / ref log-probs), the sums relative
 // to the block max.  A column's 256 rows are spread over the 4 lane groups of two wavefronts:
 // lane-row swaps, then one LDS exchange between the wavefronts.
+template <int NJ>
 __device__ __forceinline__ void fwd_epilogue_bf16(const GemmParams& p, int m0, int n0, int mb,
-                                                  f32x4_t (&acc)[8][4], uint16_t* smem) {
+                                                  f32x4_t (&acc)[8][NJ], uint16_t* smem) {
   __syncthreads();  // LDS operand buffers are reused for the cross-wave exchange
   float* xmax = reinterpret_cast<float*>(smem);  // [2 wm][256 cols]
   float* xsum = xmax + 2 * kBN;
@@ -472,8 +484,8 @@ __device__ __forceinline__ void fwd_epilogue_bf16(const GemmParams& p, int m0, i
   const bool rows_full = m0 + kBM <= Vr;  // every vocab row of this block exists
   const int rbase = m0 + wm * 128 + 4 * g;  // vocab row of acc[i][j][q]: rbase + 16 i + q
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int cl = wn * 64 + j * 16 + c;
+  for (int j = 0; j < NJ; ++j) {
+    const int cl = wn * 16 * NJ + j * 16 + c;
     const int t = n0 + cl;  // slab token
     const bool tok_ok = t < p.N;
     const int y = tok_ok ? p.yslab[t] : -1;
@@ -574,8 +586,8 @@ __device__ __forceinline__ void fwd_epilogue_bf16(const GemmParams& p, int m0, i
     auto pass = [&](auto full_c, auto z_c) {
       constexpr bool FULL = decltype(full_c)::value, WZ = decltype(z_c)::value;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int cl = wn * 64 + j * 16 + c;
+      for (int j = 0; j < NJ; ++j) {
+        const int cl = wn * 16 * NJ + j * 16 + c;
         const float ml = fmaxf(xmax[cl], xmax[kBN + cl]) * 1.4426950408889634f;
         float ssp[4] = {0.0f, 0.0f, 0.0f, 0.0f}, zsp[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
@@ -606,7 +618,7 @@ __device__ __forceinline__ void fwd_epilogue_bf16(const GemmParams& p, int m0, i
     }
     __syncthreads();
   }
-  for (int cl = tid; cl < kBN; cl += NT) {
+  for (int cl = tid; cl < 64 * NJ; cl += NT) {
     const int t = n0 + cl;
     if (t < p.N) {
       p.pmax[int64_t(mb) * p.ldp + t] = fmaxf(xmax[cl], xmax[kBN + cl]);
@@ -701,6 +713,52 @@ __device__ __forceinline__ void dwt_epilogue_bf16(const GemmParams& p, int m0, i
 
 constexpr int kSmemBytes = 2 * 2 * kBM * 64 * 2 + 16;  // two stages of both operands + sync word
 
+// one logits tile of 256 vocab rows x 64 NJ tokens
+template <int NJ>
+__device__ __forceinline__ void fwd_tile(const GemmParams& p, int mb, int n0, uint16_t* smem) {
+  f32x4_t acc[8][NJ];
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+  mainloop_bf16_dma<MODE_FWD, NJ>(p, mb * kBM, n0, acc, smem);
+  fwd_epilogue_bf16<NJ>(p, mb * kBM, n0, mb, acc, smem);
+}
+
+// The tiles of a logits GEMM (fwd_tiles), in tile order over p.nnb columns: the last `tail` are cut
+// into 64- or 128-token pieces; with p.narrow the last column is 64 p.narrow tokens wide.  Up to
+// kMixCols columns the narrow tiles run among the others of their vocab block, which share its rows
+// of W (read again from HBM otherwise: 300 tokens at 7B 504 -> 398 us, 2309 tokens 2180 -> 2098);
+// beyond, they run last and fill the final wave (20600 tokens: 17.2 ms among the others, 16.7 last).
+constexpr int kMixCols = 12;
+__device__ __forceinline__ void fwd_block(const GemmParams& p, int b, uint16_t* smem) {
+  const bool own = p.narrow && p.nnb > kMixCols;  // narrow column after all others
+  const int cols = p.nnb - (own ? 1 : 0);
+  const int whole = p.nmb * cols - p.tail;
+  int mb, nb, piece = -1;
+  if (own && b >= whole) {
+    mb = b - whole;
+    nb = cols;
+  } else {
+    if (b >= whole) {
+      piece = (b - whole) % p.pieces;
+      b = whole + (b - whole) / p.pieces;
+    }
+    tile_coords<MODE_FWD>(mb, nb, p.nmb, cols, b, p.group);
+  }
+  const int n0 = nb * kBN;
+  if (piece >= 0) {
+    if (p.pieces == 2) fwd_tile<2>(p, mb, n0 + 128 * piece, smem);
+    else fwd_tile<1>(p, mb, n0 + 64 * piece, smem);
+  } else if (p.narrow && nb == p.nnb - 1) {
+    if (p.narrow == 1) fwd_tile<1>(p, mb, n0, smem);
+    else if (p.narrow == 2) fwd_tile<2>(p, mb, n0, smem);
+    else fwd_tile<3>(p, mb, n0, smem);
+  } else {
+    fwd_tile<4>(p, mb, n0, smem);
+  }
+}
+
 // the bf16 GEMMs (T is uint16_t)
 template <typename T, int MODE>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
@@ -708,18 +766,21 @@ void lm_gemm_kernel(const GemmParams p) {
   static_assert(sizeof(T) == 2, "float32 runs f32_gemm_kernel");
   __shared__ __attribute__((aligned(16))) char smem_raw[kSmemBytes];
   uint16_t* smem = reinterpret_cast<uint16_t*>(smem_raw);
-  int mb, nb;
-  tile_coords<MODE>(mb, nb, p.nmb, p.nnb, blockIdx.x, p.group);
-  const int m0 = mb * kBM, n0 = nb * kBN;
-  f32x4_t acc[8][4];
+  if constexpr (MODE == MODE_FWD) {
+    fwd_block(p, blockIdx.x, smem);
+  } else {
+    int mb, nb;
+    tile_coords<MODE>(mb, nb, p.nmb, p.nnb, blockIdx.x, p.group);
+    const int m0 = mb * kBM, n0 = nb * kBN;
+    f32x4_t acc[8][4];
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < 8; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-  mainloop_bf16_dma<MODE>(p, m0, n0, acc, smem);
-  if constexpr (MODE == MODE_FWD) fwd_epilogue_bf16(p, m0, n0, mb, acc, smem);
-  else if constexpr (MODE == MODE_DH) dh_epilogue_bf16(p, m0, n0, acc);
-  else dwt_epilogue_bf16(p, m0, n0, acc);
+      for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    mainloop_bf16_dma<MODE>(p, m0, n0, acc, smem);
+    if constexpr (MODE == MODE_DH) dh_epilogue_bf16(p, m0, n0, acc);
+    else dwt_epilogue_bf16(p, m0, n0, acc);
+  }
 }
 
 // ------------------------------------------------------------------ float32 GEMMs
@@ -1091,13 +1152,7 @@ void lm_redo_kernel(const GemmParams p) {
     int mb, nb;
     tile_coords<MODE_FWD>(mb, nb, p.nmb, p.nnb, b, p.group);
     if (p.redo_blk[nb] == 0) continue;  // the same for the whole block
-    f32x4_t acc[8][4];
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-    mainloop_bf16_dma<MODE_FWD>(p, mb * kBM, nb * kBN, acc, smem);
-    fwd_epilogue_bf16(p, mb * kBM, nb * kBN, mb, acc, smem);
+    fwd_tile<4>(p, mb, nb * kBN, smem);
     __syncthreads();  // the epilogue's LDS exchange is read before the next tile's loads land
   }
 }
@@ -1122,13 +1177,16 @@ __global__ void slab_prep_kernel(const int32_t* __restrict__ token_ids,
   if (shift) shift[t] = 0.0f;
 }
 
-// partials -> lse, logp.  One block of 256 threads handles 64 tokens; its 4 wavefronts
-// each combine a quarter of the vocabulary blocks, then combine through LDS.
+// partials -> lse, logp.  A block of 1024 threads handles 32 tokens in 32 slices of the vocabulary
+// blocks (slice s takes blocks s, s + 32, ..), combined through lane swaps and LDS.  Bound by the
+// latency of a thread's loads, four of each array in flight: at 193 tokens and V = 151936 four
+// wavefronts per 64 tokens walked 149 blocks each one by one in 73 us, 11 us so.
 //   rel == 0: psum = sum exp(z - pmax) per vocab block (log-prob only path)
 //   rel == 1: psum = sum exp(z - s_t); with check != 0 a row whose max is too far from s_t
 //             (exp(z - s_t) could leave float range) gets s_t = max and its token block is
 //             marked for a second evaluation.
-__global__ __launch_bounds__(256) void merge_kernel(
+constexpr int kMergeTok = 32;
+__global__ __launch_bounds__(1024) void merge_kernel(
     const float* __restrict__ pmax, const float* __restrict__ psum,
     const float* __restrict__ psz, int64_t ldp, int32_t nmb, const float* __restrict__ zlab,
     const int32_t* __restrict__ yslab, int32_t Tc, int32_t rel, int32_t check,
@@ -1137,66 +1195,76 @@ __global__ __launch_bounds__(256) void merge_kernel(
     int32_t* __restrict__ redo_any, int32_t only_after_redo) {
   // the second merge only matters when the first marked a row (every block reads the same flag)
   if (only_after_redo && redo_any[0] == 0) return;
-  __shared__ float sm[4][64], ss[4][64], sz[4][64];
+  __shared__ float sm[16][kMergeTok], ss[16][kMergeTok], sz[16][kMergeTok];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int t = blockIdx.x * 64 + lane;
+  const int tok = lane & 31, slice = wv * 2 + (lane >> 5);
+  const int t = blockIdx.x * kMergeTok + tok;
   const bool ok = t < Tc;
   const bool ent = psz != nullptr;
   // S = sum exp(z - ref), Z = sum exp(z - ref) z, both relative to the same reference
   float M = -INFINITY, S = 0.0f, Z = 0.0f;
-  if (ok) {
-    for (int b = wv; b < nmb; b += 4) {
-      const float m = pmax[int64_t(b) * ldp + t];
-      const float x = psum[int64_t(b) * ldp + t];
-      const float y = ent ? psz[int64_t(b) * ldp + t] : 0.0f;
-      if (rel) {
-        M = fmaxf(M, m);
-        S += x;
-        Z += y;
-      } else if (m > M) {
-        const float f = __expf(M - m);
-        S = S * f + x;
-        Z = Z * f + y;
-        M = m;
-      } else {
-        const float f = __expf(m - M);
-        S += x * f;
-        Z += y * f;
-      }
-    }
-  }
-  sm[wv][lane] = M;
-  ss[wv][lane] = S;
-  sz[wv][lane] = Z;
-  __syncthreads();
-  if (wv != 0 || !ok) return;
-  float Mt = sm[0][lane], St = ss[0][lane], Zt = sz[0][lane];
-  for (int w = 1; w < 4; ++w) {
-    const float m = sm[w][lane], x = ss[w][lane], y = sz[w][lane];
+  // one more partial (m, x, y) into (M, S, Z)
+  auto add = [&](float m, float x, float y) {
     if (rel) {
-      Mt = fmaxf(Mt, m);
-      St += x;
-      Zt += y;
-    } else if (m > Mt) {
-      const float f = __expf(Mt - m);
-      St = St * f + x;
-      Zt = Zt * f + y;
-      Mt = m;
-    } else if (m > -INFINITY) {
-      const float f = __expf(m - Mt);
-      St += x * f;
-      Zt += y * f;
+      M = fmaxf(M, m);
+      S += x;
+      Z += y;
+    } else if (m > M) {
+      const float f = __expf(M - m);
+      S = S * f + x;
+      Z = Z * f + y;
+      M = m;
+    } else {
+      const float f = __expf(m - M);
+      S += x * f;
+      Z += y * f;
+    }
+  };
+  if (ok) {
+    for (int b = slice; b < nmb; b += 128) {
+      float m[4], x[4], y[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int64_t o = int64_t(b + 32 * u) * ldp + t;
+        const bool in = b + 32 * u < nmb;
+        m[u] = in ? pmax[o] : 0.0f;
+        x[u] = in ? psum[o] : 0.0f;
+        y[u] = in && ent ? psz[o] : 0.0f;
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (b + 32 * u < nmb) add(m[u], x[u], y[u]);
     }
   }
+  // slices without a block hold (-inf, 0, 0) and add nothing
+  auto join = [&](float m, float x, float y) {
+    if (m > -INFINITY || x != 0.0f) add(m, x, y);
+  };
+  {
+    const float m = __shfl_down(M, 32, 64), x = __shfl_down(S, 32, 64), y = __shfl_down(Z, 32, 64);
+    join(m, x, y);
+  }
+  if (lane < 32) {
+    sm[wv][tok] = M;
+    ss[wv][tok] = S;
+    sz[wv][tok] = Z;
+  }
+  __syncthreads();
+  if (wv != 0 || lane >= 32 || !ok) return;
+  M = sm[0][tok];
+  S = ss[0][tok];
+  Z = sz[0][tok];
+#pragma unroll
+  for (int w = 1; w < 16; ++w) join(sm[w][tok], ss[w][tok], sz[w][tok]);
   const float s_t = (rel && shift) ? shift[t] : 0.0f;
-  const float l = rel ? s_t + __logf(St) : Mt + __logf(St);
+  const float l = rel ? s_t + __logf(S) : M + __logf(S);
   const int y = yslab[t];
   if (lse_out) lse_out[t] = l;
   if (logp_out) logp_out[t] = y >= 0 ? zlab[t] - l : __int_as_float(0x7fc00000);
   // entropy -sum_v p_v log p_v = lse - sum_v p_v z_v, sum_v p_v z_v = Z / S
-  if (ent_out) ent_out[t] = l - Zt / St;
-  if (rel && check && !(Mt - s_t < 60.0f && Mt - s_t > -60.0f)) {
-    shift[t] = Mt;
+  if (ent_out) ent_out[t] = l - Z / S;
+  if (rel && check && !(M - s_t < 60.0f && M - s_t > -60.0f)) {
+    shift[t] = M;
     redo_blk[t / kBN] = 1;
     redo_any[0] = 1;
     atomicAdd(redo_count, 1);
@@ -1450,6 +1518,24 @@ static int tile_group(int mode, int32_t K, int32_t nnb) {
   return 4;
 }
 
+// Tiles of a logits GEMM; returns the blocks.  The last N % 256 tokens take a column of narrow tiles
+// (64, 128 or 192 wide) in place of whole ones that are mostly padding.  Without those, a last
+// wave of at most 128 (64) whole tiles on the 256 compute units is cut into 2 (4) pieces per tile,
+// which run at once.  token_logprob, us, whole tiles only -> so (and with the merge in 32 slices):
+// d = 1536 (V = 151936) 16 tokens 207 -> 121, 193 216 -> 147, 300 289 -> 198, 1200 557 -> 492;
+// d = 3584 (V = 152064) 16 348 -> 245, 300 520 -> 398, 2309 2235 -> 2097, 33733 27819 -> 27372.
+static int64_t fwd_tiles(GemmParams& p) {
+  p.nmb = int((p.M + kBM - 1) / kBM);
+  p.nnb = int((p.N + kBN - 1) / kBN);
+  p.narrow = ((p.N % kBN + 63) / 64) % 4;
+  p.group = tile_group(MODE_FWD, p.K, p.nnb);
+  const int64_t whole = int64_t(p.nmb) * p.nnb;
+  const int last = int(whole % 256);
+  p.tail = p.narrow == 0 && last <= 128 ? last : 0;
+  p.pieces = p.tail == 0 ? 1 : p.tail <= 64 ? 4 : 2;
+  return whole + int64_t(p.tail) * (p.pieces - 1);
+}
+
 // Tiles of a float32 GEMM.  The gradient GEMMs take 128 x 128 tiles where those alone fill the
 // chip twice, else 64 x 64; dhidden then cuts its K (the vocabulary) so that there are about two
 // blocks per compute unit, of at least 8 K steps each.
@@ -1496,10 +1582,15 @@ template <typename T, int MODE>
 static int launch_gemm(GemmParams p, int kind, double flops, hipStream_t stream) {
   if constexpr (sizeof(T) == 4) return launch_f32<MODE>(p, kind, flops, stream);
   else {
-  p.nmb = int((p.M + kBM - 1) / kBM);
-  p.nnb = int((p.N + kBN - 1) / kBN);
-  p.group = tile_group(MODE, p.K, p.nnb);
-  const int64_t nblk = int64_t(p.nmb) * p.nnb;
+  int64_t nblk;
+  if constexpr (MODE == MODE_FWD) {
+    nblk = fwd_tiles(p);
+  } else {
+    p.nmb = int((p.M + kBM - 1) / kBM);
+    p.nnb = int((p.N + kBN - 1) / kBN);
+    p.group = tile_group(MODE, p.K, p.nnb);
+    nblk = int64_t(p.nmb) * p.nnb;
+  }
   if (nblk == 0) return FASTRL_OK;
   // transposed dW: whole 64-k tiles, whole 256-column tiles of the K-major E, 16-byte dW rows
   FR_CHECK_ARG(MODE != MODE_DWT || (p.K % 64 == 0 && p.ldb >= int64_t(p.nnb) * kBN &&
@@ -1556,7 +1647,7 @@ static int dh_ksplit(int32_t Tc, int32_t d, int32_t V, int32_t dtype, bool dw) {
   const double nt = double((Tc + kBM - 1) / kBM) * double((d + kBN - 1) / kBN);
   const double nk = double((V + 63) / 64);
   const double wt = dw ? double((V + kBN - 1) / kBN) * double((d + kBM - 1) / kBM) : 0.0;
-  const double wk = double((Tc + kBN - 1) / kBN) * 4.0 + 9.0;
+  const double wk = double((Tc + 63) / 64) + 9.0;
   int best = 1;
   double best_t = 0.0;
   for (int s = 1; s <= kMaxKSplit && double(s) * 8.0 <= nk; ++s) {
@@ -1679,7 +1770,7 @@ static int token_logprob_impl(const void* hidden, const int32_t* row_index, cons
     FR_TRY((launch_gemm<T, MODE_FWD>(p, prof ? FASTRL_K_LOGITS_FWD : -1,
                                      2.0 * V * double(Tc) * d, stream)));
     const int32_t nmb = (V + kBM - 1) / kBM;
-    hipLaunchKernelGGL(merge_kernel, dim3(nb1d(Tc, 64)), dim3(256), 0, stream, w.pmax, w.psum,
+    hipLaunchKernelGGL(merge_kernel, dim3(nb1d(Tc, kMergeTok)), dim3(1024), 0, stream, w.pmax, w.psum,
                        (const float*)nullptr, ch, nmb, w.zlab, w.yslab, Tc, 0, 0,
                        lse ? lse + t0 : (float*)nullptr, logp + t0, (float*)nullptr,
                        (float*)nullptr, (int32_t*)nullptr, (int32_t*)nullptr,
@@ -1921,8 +2012,7 @@ static int policy_loss_impl(const fastrl_loss_args& a, hipStream_t stream) {
       FR_LAUNCHED();
       continue;
     }
-    const int64_t Tr = rup(Tc, kBN);
-    const int32_t nnb = int32_t(Tr / kBN);
+    const int32_t nnb = int32_t(rup(Tc, kBN) / kBN);
     hipLaunchKernelGGL(slab_prep_kernel, dim3(nb1d(Tc, 256)), dim3(256), 0, stream,
                        a.token_ids, a.row_index, t0, Tc, V, w.yslab, w.shift, a.status);
     FR_LAUNCHED();
@@ -1941,7 +2031,7 @@ static int policy_loss_impl(const fastrl_loss_args& a, hipStream_t stream) {
     const double f_fwd = 2.0 * double(V) * Tc * d;
     FR_TRY((launch_gemm<T, MODE_FWD>(p, FASTRL_K_LOGITS_FWD, f_fwd, stream)));
     const bool store = dh || dw;
-    hipLaunchKernelGGL(merge_kernel, dim3(nb1d(Tc, 64)), dim3(256), 0, stream,
+    hipLaunchKernelGGL(merge_kernel, dim3(nb1d(Tc, kMergeTok)), dim3(1024), 0, stream,
                        w.pmax, w.psum, w.psz, tcp, nmb, w.zlab, w.yslab, Tc, store ? 1 : 0,
                        store ? 1 : 0, w.lse + t0, w.logp + t0, w.ent ? w.ent + t0 : nullptr,
                        store ? w.shift : (float*)nullptr, w.redo_blk, w.redo_count,
@@ -1951,7 +2041,7 @@ static int policy_loss_impl(const fastrl_loss_args& a, hipStream_t stream) {
       // token blocks holding a row that needs a shift: evaluate again, then merge again (both
       // return at once on the device when no row was marked)
       FR_TRY(launch_redo<T>(p, stream));
-      hipLaunchKernelGGL(merge_kernel, dim3(nb1d(Tc, 64)), dim3(256), 0, stream,
+      hipLaunchKernelGGL(merge_kernel, dim3(nb1d(Tc, kMergeTok)), dim3(1024), 0, stream,
                          w.pmax, w.psum, w.psz, tcp, nmb, w.zlab, w.yslab, Tc, 1, 0, w.lse + t0,
                          w.logp + t0, w.ent ? w.ent + t0 : nullptr, w.shift, w.redo_blk,
                          w.redo_count, w.redo_blk + nnb, 1);
@@ -1993,6 +2083,8 @@ static int policy_loss_impl(const fastrl_loss_args& a, hipStream_t stream) {
       r.d = d;
       r.status = a.status;
       if constexpr (sizeof(T) == 2) {  // dW^T = Bd E: A = Bd, B = E1 read K-major
+        // (the logits tiles zero the exp-logit rows up to a multiple of 64 tokens)
+        const int64_t Tr = rup(Tc, 64);
         dim3 g(nb1d(d, 64), unsigned(Tr / 64));
         hipLaunchKernelGGL(transpose_scale_kernel, g, dim3(256), 0, stream,
                            static_cast<const uint16_t*>(a.hidden), a.row_index, t0, Tc, int32_t(Tr),

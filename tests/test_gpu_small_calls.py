@@ -124,3 +124,35 @@ def test_float32_tiles(fr, T, d, V, accumulate, dh_dtype):
     if V > 1:  # (one class: every gradient is exactly a difference of equal numbers)
         assert _rel(call.dhidden, dH) < (1e-5 if dh_dtype == torch.float32 else 4e-3)
         assert _rel(call.dW, dW + base.double() * accumulate) < 1e-5
+
+
+@pytest.mark.parametrize("T, d, V", [
+    (1, 8, 1), (64, 40, 257), (65, 72, 700), (128, 264, 255), (129, 200, 511), (192, 64, 256),
+    (193, 64, 20000),    # whole tiles, the last 79 cut in two
+    (256, 64, 9000),     # 36 whole tiles, each cut in four
+    (300, 136, 3000),    # a narrow column among the others
+    (3200, 64, 5200),    # a narrow column after 12 whole ones
+    (4096, 72, 5200),    # 16 whole columns of 21: the last 80 tiles cut in two
+])
+def test_logits_tiles(fr, T, d, V):
+    """Logits tiles of every width: token_logprob (partials only) and the loss call (exp-logits
+    stored, gradients from them) on gathered rows.  2e-5 absolute for the log-probs: float32 sums
+    of values around 1 (bf16 inputs are exact in both)."""
+    H, W, y, z, lse, logp, old = _problem(T, d, V, T + V)
+    rows = torch.arange(T - 1, -1, -1, dtype=torch.int32).to(DEV)
+    Hr, yr = H.flip(0).contiguous().to(DEV), y.flip(0).contiguous().to(DEV)
+    lp, ls = fr.token_logprob(Hr, W.to(DEV), yr, row_index=rows)
+    torch.cuda.synchronize()
+    assert (lp.double().cpu() - logp).abs().max() < 2e-5
+    assert (ls.double().cpu() - lse).abs().max() < 2e-5
+    if V == 1:
+        return
+    off = np.asarray(sorted({0, T // 3, T // 3 + T // 2, T}), dtype=np.int64)
+    adv = torch.linspace(-1.0, 1.5, len(off) - 1)
+    loss, dH, dW = _reference(H, W, y, z, lse, logp, old, off, adv)
+    call = fr.policy_loss_fwd_bwd(
+        Hr, W.to(DEV), yr, old.flip(0).contiguous().to(DEV), torch.from_numpy(off).to(DEV),
+        torch.from_numpy(off), adv.to(DEV), row_index=rows, T=T)
+    torch.cuda.synchronize()
+    assert (call.logp.double().cpu() - logp).abs().max() < 2e-5
+    assert _rel(call.dhidden, dH) < 1e-2 and _rel(call.dW, dW) < 1e-2
