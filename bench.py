@@ -333,7 +333,7 @@ def main():
     max_len = int(ro.lengths.max())
 
     # device status word of every call in the warmup and timed steps: read once after the
-    # timed loop; a data fault or a timed-out stage hand-over invalidates the line
+    # timed loop; a data fault invalidates the line
     status = torch.zeros(1, dtype=torch.int32, device=dev)
 
     def step():

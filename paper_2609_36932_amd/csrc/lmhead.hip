@@ -89,7 +89,6 @@ struct GemmParams {
   // ---- DW epilogue
   float* dW;                // [V, d]
   int32_t dW_acc;           // add to dW (later slabs) instead of overwriting it
-  int32_t* status;
 };
 
 // Tile order: consecutive blocks are dealt round-robin to the 8 XCDs and run at about the same
@@ -100,9 +99,6 @@ struct GemmParams {
 // Backward GEMMs (long K): 4 at d = 3584; all XCDs walk neighbouring tiles through K together,
 // so a strip that several XCDs read is fetched once into the shared last-level cache (giving
 // each XCD its own contiguous range of tiles measured 2-4% slower here).
-// spins of a split-barrier wait before it gives up (each spin one LDS read, ~0.1 us; a
-// wavefront normally waits for a few hundred cycles at most)
-constexpr int kSyncSpins = 1 << 16;
 template <int MODE>
 __device__ __forceinline__ void tile_coords(int& mb, int& nb, int nmb, int nnb, int b, int group) {
   // the groups are vocab blocks in both dW forms: M blocks of MODE_DW, N blocks of MODE_DWT
@@ -121,70 +117,97 @@ __device__ __forceinline__ void tile_coords(int& mb, int& nb, int nmb, int nnb, 
 typedef __attribute__((address_space(3))) void lds_void_t;
 
 // bf16 main loop of the logits GEMM (z = W h: A = LM-head rows, B = gathered hidden rows, K = d),
-// the dhidden GEMM (A = the slab's exp-logit rows, B = W^T rows, K = padded vocab) and the
-// transposed dW GEMM (A = Bd rows, B = the exp-logit tile read K-major, K = padded slab).
-// Eight wavefronts (two per SIMD, so one can issue MFMAs while the other waits on memory) each
-// own a 128 x 64 part of the block tile.  LDS holds two stages of a 256 x 64 A tile and a
-// 256 x 64 B tile (32 KB each), written by direct global->LDS loads (global_load_lds_dwordx4):
-// one load instruction moves 1 KB, lane l writing its 16-byte slot l; each wavefront moves
-// 4 KB of each operand per tile.  Tile kt+1 is in flight while tile kt is multiplied;
-// fragments of k-step kk+1 are read while the MFMAs of k-step kk run.  The MFMAs are
-// v_mfma_f32_16x16x32_bf16 (8 x 4 tiles of 16 x 16 per wavefront, two 32-k steps per tile):
-// per FLOP they move less accumulator data through the register file than 32 x 32 x 16, and
-// measured 7% faster on the logits GEMM and 4% on dhidden (where this engine also beat a
-// four-wavefront one, as it does on dW); lane l holds rows 4 (l / 16) .. 4 (l / 16) + 3 of
-// column l % 16 of each 16 x 16 tile.
+// the dhidden GEMM (A = the slab's exp-logit rows, B = W^T rows or, K-major, W itself, K = padded
+// vocab) and the transposed dW GEMM (A = Bd rows, B = the exp-logit tile read K-major, K = padded
+// slab).  A tile of 256 x 64 NJ (NJ < 4: logits only), K in tiles of 64; eight wavefronts, each a
+// 128 x 16 NJ part on v_mfma_f32_16x16x32_bf16 (8 x NJ accumulators of 16 x 16; lane l holds rows
+// 4 (l / 16) .. + 3 of column l % 16).
+//
+// The two wavefronts of a SIMD (wm = 0, 1) take turns: in one phase one of them multiplies a whole
+// K tile out of registers (64 MFMAs), with the loads of later tiles issued in between, while the
+// other reads the 24 fragments of its next K tile from LDS; a barrier, and they swap.  So a matrix
+// core is always fed by one wavefront that waits for nothing, and LDS reads and the rendezvous are
+// hidden behind the other one's MFMAs.  (When both ran MFMAs and reads interleaved in step, with one
+// rendezvous per K tile, the matrix cores were busy 68% of the time at 1.85 GHz; so, 79% at 1.73 GHz
+// under the same power limit.  Logits of 27136 tokens at 7B 21.9 -> 20.5 ms, loss call of 27000
+// tokens 68.3 -> 63.8 ms, 507 tokens at d = 1536 1061 -> 914 us.  With the loads in the reading
+// phase, that phase outlasted the other's MFMAs: 61% busy, 22.4 ms.)  The barrier that ends a
+// multiplying phase comes before its last MFMAs, which cover its latency.
+//
+// LDS: two stages of A (32 KB each) and three of B.  Wavefronts wm = 0 read tile k in phase 2k and
+// multiply it in phase 2k + 1, wm = 1 one phase later.  Loads (global_load_lds_dwordx4, 1 KB an
+// instruction, lane l into 16-byte slot l) go out in a multiplying phase, as soon as their stage is
+// free: in the phase of tile k, wm = 0 loads the A rows it reads itself (0 .. 127) of tile k + 2 and
+// half of B of tile k + 2; wm = 1 its A rows (128 .. 255) of tile k + 2 and the other half of B of
+// tile k + 3.  The end of the next multiplying phase waits for them: two phases later.
 //
 // LDS layout (rows of 64 k = 128 B): row r keeps its k-chunk c (8 bf16) in slot
 // c ^ ((r >> 1) & 7).  The LDS serves a 16-byte-per-lane read 16 lanes (256 B, 64 banks) at a
 // time, and rows r..r+15 of a fragment then land on 16 distinct 16-byte bank groups; the
 // swizzle is applied on the global side (each lane loads the chunk that belongs in its slot).
-// NJ < 4 (logits only): a tile of 256 x 64 NJ, 128 x 16 NJ per wavefront.
+// A K-major B tile is 64 k-rows of 256 columns (512 B), column chunk c of row k in slot c ^ swz(k),
+// swz(k) = ((k & 3) << 1) | (((k >> 3) & 1) << 3).
+constexpr int kStage = kBM * 64;                          // elements of one operand's stage
+constexpr int kSmemBytes = (2 + 3) * kStage * 2;          // 160 KB: all of a compute unit's LDS
+// LDS that no wavefront reads or loads into any more once one of them is past its last K tile:
+// the A stage of the tile before the last (of nk)
+__device__ __forceinline__ uint16_t* free_stage(uint16_t* smem, int nk) {
+  return smem + (nk & 1) * kStage;
+}
 template <int MODE, int NJ = 4>
-__device__ __forceinline__ void mainloop_bf16_dma(const GemmParams& p, int m0, int n0,
-                                                  f32x4_t (&acc)[8][NJ], uint16_t* smem,
-                                                  int kt0 = 0, int nkt = 0) {
+__device__ __forceinline__ void mainloop_bf16(const GemmParams& p, int m0, int n0,
+                                              f32x4_t (&acc)[8][NJ], uint16_t* smem, int kt0 = 0,
+                                              int nkt = 0) {
   static_assert(NJ == 4 || MODE == MODE_FWD, "narrow tiles: logits only");
   constexpr int BK = 64;
-  constexpr int TILE = kBM * BK;  // elements per operand per stage
   constexpr bool DHT = MODE == MODE_DHT;
   constexpr bool BKM = MODE == MODE_DWT || DHT;  // B stored K-major (B[n][k] at k * ldb + n)
+  constexpr bool GATHER = MODE == MODE_FWD;      // B rows through b_rows
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 2, wn = wave & 3;
-  const uint16_t* Ag = static_cast<const uint16_t*>(p.A);
-  const uint16_t* Bg = static_cast<const uint16_t*>(p.B);
+  const char* Ag = static_cast<const char*>(p.A);
+  const char* Bg = static_cast<const char*>(p.B);
+  uint16_t* const sA = smem;
+  uint16_t* const sB = smem + 2 * kStage;
+  const int K = p.K;
+  const int nk = DHT ? nkt : (K + BK - 1) / BK;
+  // ---- loads.  Addresses are a uniform base (the first of a load's rows) plus a 32-bit lane offset
+  // in bytes; gathered rows take 64-bit lane addresses.  Rows past the edge load a valid one (their
+  // results are never stored).
   const int lrow = lane >> 3;
-  // global k-chunk this lane moves into its slot; rows r = 32 wave + 8 j + lrow, so
-  // ((r >> 1) & 7) = 4 (j & 1) + (lrow >> 1)
-  const int gch0 = (lane & 7) ^ (lrow >> 1), gch1 = gch0 ^ 4;
-  int64_t arow[4], brow[NJ];
-  // B rows r = 8 (NJ wave + j) + lrow: the chunk of load j is gch0 or, for odd j + bodd, gch1
-  const int bodd = (NJ & 1) ? (wave & 1) : 0;
+  const int gch0 = (lane & 7) ^ (lrow >> 1), gch1 = gch0 ^ 4;  // k-chunk of an even / odd load
+  const char* abase[4];
+  uint32_t aoff[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const int r = wave * 32 + j * 8 + lrow;
-    const int ra = min(m0 + r, p.M - 1);  // rows past the edge load a valid row; their
-    arow[j] = int64_t(ra) * p.lda;        // results are never stored
-    if constexpr (BKM) {
-      // K-major B tile: 64 k-rows of 256 n (512 B); load j of this wavefront fills k-rows
-      // 8 wave + 2 j and the next, lane l slot l % 32 of row 8 wave + 2 j + l / 32, with the
-      // n-chunk that belongs there (slot = chunk ^ kmaj_swz(k))
-      const int k = wave * 8 + 2 * j + (lane >> 5);
-      const int swz = ((k & 3) << 1) | (((k >> 3) & 1) << 3);
-      const int n = n0 + (((lane & 31) ^ swz) << 3);
-      // (W's rows end at N: columns past it load a valid chunk; their results are never stored)
-      brow[j] = DHT ? int64_t(min(n, p.N - 8)) : int64_t(k) * p.ldb + n;
-    }
+    const int r0 = min(m0 + wave * 32 + j * 8, p.M - 1);
+    abase[j] = Ag + 2 * int64_t(r0) * p.lda;
+    aoff[j] = 2u * uint32_t(min(r0 + lrow, p.M - 1) - r0) * uint32_t(p.lda);
+    if constexpr (MODE != MODE_FWD) aoff[j] += 16u * uint32_t((j & 1) ? gch1 : gch0);
   }
-  if constexpr (!BKM) {
-    // B rows, gathered through b_rows when given: the four index loads are issued together
-    // (one memory round trip before the first tile load, not four one after the other)
+  const char* bbase[NJ];  // uniform (not gathered) or lane address
+  uint32_t boff[NJ];
+  const int bodd = (NJ & 1) ? (wave & 1) : 0;  // load j of B: an odd one if j + bodd is
+  uint32_t bhi = 0;
+  if constexpr (BKM) {
+    // load j fills k-rows 8 wave + 2 j and the next: lane l slot l % 32 of the first or second
+    bhi = (lane >> 5) ? 2u * uint32_t(p.ldb) : 0u;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const int k = wave * 8 + 2 * j + (lane >> 5);
+      const int n = (((lane & 31) ^ (((k & 3) << 1) | (((k >> 3) & 1) << 3))) << 3);
+      // (W's rows end at N: columns past it load a valid chunk)
+      boff[j] = 2u * uint32_t(DHT ? min(n, p.N - 8 - n0) : n);
+      if constexpr (!DHT) boff[j] += bhi;
+      bbase[j] = Bg + 2 * int64_t(n0);
+    }
+  } else if constexpr (GATHER) {
     int64_t bi[NJ];
 #pragma unroll
     for (int j = 0; j < NJ; ++j)
       bi[j] = min(n0 + (wave * NJ + j) * 8 + lrow, p.N - 1) + p.b_row_base;
-    if (p.b_rows) {
+    if (p.b_rows) {  // the index loads are issued together: one memory round trip
       int32_t g[NJ];
 #pragma unroll
       for (int j = 0; j < NJ; ++j) g[j] = __builtin_nontemporal_load(p.b_rows + bi[j]);
@@ -192,255 +215,219 @@ __device__ __forceinline__ void mainloop_bf16_dma(const GemmParams& p, int m0, i
       for (int j = 0; j < NJ; ++j) bi[j] = g[j];
     }
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) brow[j] = bi[j] * p.ldb;
+    for (int j = 0; j < NJ; ++j) bbase[j] = Bg + 2 * bi[j] * p.ldb;
+  } else {
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const int r0 = min(n0 + (wave * NJ + j) * 8, p.N - 1);
+      bbase[j] = Bg + 2 * int64_t(r0) * p.ldb;
+      boff[j] = 2u * uint32_t(min(r0 + lrow, p.N - 1) - r0) * uint32_t(p.ldb) +
+                16u * uint32_t((j & 1) ? gch1 : gch0);
+    }
   }
+  // byte offset of a lane's chunk inside tile kt (logits: K need not be whole tiles, and a partial
+  // last tile loads a valid chunk for those past K)
+  auto chunk = [&](int kt, bool odd) { return 2 * min((odd ? gch1 : gch0) * 8, K - 8 - kt * BK); };
+  auto issue_a = [&](int kt, int st) {
+    uint16_t* d = sA + st * kStage + wave * 32 * BK;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      uint32_t o = aoff[j];
+      if constexpr (MODE == MODE_FWD) o += uint32_t(chunk(kt, j & 1));
+      const char* base = abase[j] + int64_t(DHT ? kt + kt0 : kt) * (2 * BK);
+      __builtin_amdgcn_global_load_lds(base + o, (lds_void_t*)(d + j * 8 * BK), 16, 0, 0);
+    }
+  };
+  auto issue_b = [&](int kt, int st) {
+    uint16_t* d = sB + st * kStage + wave * NJ * 8 * BK;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const char* src;
+      if constexpr (BKM) {
+        int k = (DHT ? kt + kt0 : kt) * BK + wave * 8 + 2 * j;
+        uint32_t o = boff[j];
+        if constexpr (DHT) {  // vocab rows past the end load the last one (their exp-logits are 0)
+          if (k + 1 < p.Vreal) o += bhi;
+          k = min(k, p.Vreal - 1);
+        }
+        src = bbase[j] + 2 * int64_t(k) * p.ldb + o;
+      } else if constexpr (GATHER) {
+        src = bbase[j] + (kt * (2 * BK) + chunk(kt, ((j + bodd) & 1) != 0));
+      } else {
+        src = bbase[j] + int64_t(kt) * (2 * BK) + boff[j];
+      }
+      __builtin_amdgcn_global_load_lds(src, (lds_void_t*)(d + j * 8 * BK), 16, 0, 0);
+    }
+  };
+  // ---- fragments of a whole K tile: A rows wm*128 + i*16 + (lane & 15), B rows wn*16 NJ + j*16 +
+  // (lane & 15), k-chunk 4 kk + lane / 16 (8 consecutive k per lane) of the 32-k step kk
+  bf16x8_t fa[2][8], fb[2][NJ];
+  const int sw = ((lane & 15) >> 1) & 7;  // ((row >> 1) & 7) of the fragment rows this lane reads
+  const int slot0 = ((lane >> 4) ^ sw) * 8, slot1 = ((4 + (lane >> 4)) ^ sw) * 8;
+  const int afo = (wm * 128 + (lane & 15)) * BK, bfo = (wn * 16 * NJ + (lane & 15)) * BK;
   // K-major B fragments (ds_read_b64_tr_b16): in 16-lane group g, lane jj reads 4 n of k-row
   // 8 g + 4 s + jj / 4 (s = first / second 4 k of the lane's 8) at n = 16 j + 4 (jj % 4) of
   // the wavefront's 64 columns, and receives the 4 k of column n = 16 j + jj.  The row swizzle
-  // puts the 8 rows that lanes 0-31 (and 32-63) read on 16 distinct 16-byte bank groups.
-  int bfo[4];
-  if constexpr (BKM) {
-    const int g = lane >> 4, jj = lane & 15;
-    const int swz = ((jj >> 2) << 1) | ((g & 1) << 3);  // kmaj_swz of the rows this lane reads
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = wn * 64 + 16 * j + 4 * (jj & 3);
-      bfo[j] = (8 * g + (jj >> 2)) * kBN + (((n >> 3) ^ swz) << 3) + (n & 7);
-    }
-  }
-  // The transposing reads are issued as inline assembly: before the builtin form the compiler
-  // waits for every outstanding direct-to-LDS load (it cannot tell the two stages apart), which
-  // drains the next tile's prefetch in every k-step (measured 10% slower).  Their results are
-  // waited for explicitly (frag_wait) before the MFMAs that read them, and before the barrier
-  // that hands their stage back to the loads.
+  // puts the 8 rows that lanes 0-31 (and 32-63) read on 16 distinct 16-byte bank groups.  They are
+  // inline assembly: before the builtin form the compiler waits for every outstanding direct-to-LDS
+  // load.  frag_wait waits for them, and passes them on as operands so that no use precedes it.
   uint32_t bfa[4];  // LDS byte addresses of this lane's K-major B fragments in stage 0
   if constexpr (BKM) {
     typedef __attribute__((address_space(3))) const uint16_t lds_u16_t;
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      bfa[j] = uint32_t(uintptr_t((lds_u16_t*)(smem + TILE + bfo[j])));
-  }
-  // the B fragments pass through the wait as operands, so no use of them can precede it
-  auto frag_wait = [&](bf16x8_t (&fb)[NJ]) {
-    if constexpr (BKM) {
-      __builtin_amdgcn_sched_barrier(0);
-      asm volatile("s_waitcnt lgkmcnt(0)"
-                   : "+v"(fb[0]), "+v"(fb[1]), "+v"(fb[2]), "+v"(fb[3])
-                   :
-                   : "memory");
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-  const int K = p.K;
-  // (DHT: tiles kt0 .. kt0 + nkt - 1 of K, which is padded to whole tiles)
-  const int nk = DHT ? nkt : (K + BK - 1) / BK;
-  const bool ktail = !DHT && (K % BK) != 0;
-  auto issue = [&](int kt, int stage) {
-    if constexpr (DHT) kt += kt0;
-    // clamp the chunk so a partial last tile never reads past the end of a row
-    const int kc0 = min(kt * BK + gch0 * 8, K - 8);
-    const int kc1 = min(kt * BK + gch1 * 8, K - 8);
-    uint16_t* sa = smem + stage * 2 * TILE + wave * 32 * BK;
-    uint16_t* sb = smem + stage * 2 * TILE + TILE + wave * NJ * 8 * BK;
+    const int g = lane >> 4, jj = lane & 15;
+    const int swz = ((jj >> 2) << 1) | ((g & 1) << 3);  // swz of the rows this lane reads
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int kc = (j & 1) ? kc1 : kc0;
-      __builtin_amdgcn_global_load_lds(Ag + arow[j] + kc, (lds_void_t*)(sa + j * 8 * BK), 16, 0, 0);
-      if (j >= NJ) continue;
-      // (K-major B: k-rows 8 wave + 2 j, + 1 start at the same LDS offset as rows 32 wave + 8 j)
-      const uint16_t* bsrc;
-      if constexpr (DHT)  // vocab rows past the end load the last one (their exp-logits are 0)
-        bsrc = Bg + brow[j] +
-               int64_t(min(kt * BK + wave * 8 + 2 * j + (lane >> 5), p.Vreal - 1)) * p.ldb;
-      else
-        bsrc = BKM ? Bg + brow[j] + int64_t(kt) * BK * p.ldb
-                   : Bg + brow[j] + (NJ == 4 ? kc : ((j + bodd) & 1) ? kc1 : kc0);
-      __builtin_amdgcn_global_load_lds(bsrc, (lds_void_t*)(sb + j * 8 * BK), 16, 0, 0);
+      const int n = wn * 64 + 16 * j + 4 * (jj & 3);
+      const int o = (8 * g + (jj >> 2)) * kBN + (((n >> 3) ^ swz) << 3) + (n & 7);
+      bfa[j] = uint32_t(uintptr_t((lds_u16_t*)(sB + o)));
     }
-  };
-  auto zero_tail = [&](int kt, int stage) {  // this lane's slots past K in tile kt
-    uint16_t* sa = smem + stage * 2 * TILE + wave * 32 * BK + lane * 8;
-    uint16_t* sb = smem + stage * 2 * TILE + TILE + wave * NJ * 8 * BK + lane * 8;
+  }
+  auto read_frags = [&](int sta, int stb) {
+    const uint16_t* as = sA + sta * kStage + afo;
+    const uint16_t* bs = sB + stb * kStage + bfo;
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if (kt * BK + ((j & 1) ? gch1 : gch0) * 8 >= K)
-        *reinterpret_cast<u32x4_t*>(sa + j * 8 * BK) = u32x4_t{0u, 0u, 0u, 0u};
+    for (int kk = 0; kk < 2; ++kk) {
+      const int slot = kk ? slot1 : slot0;
+      if constexpr (BKM) {
 #pragma unroll
-    for (int j = 0; j < NJ; ++j)
-      if (kt * BK + (((j + bodd) & 1) ? gch1 : gch0) * 8 >= K)
-        *reinterpret_cast<u32x4_t*>(sb + j * 8 * BK) = u32x4_t{0u, 0u, 0u, 0u};
-  };
-  const int sw = ((lane & 15) >> 1) & 7;  // ((row >> 1) & 7) of the fragment rows this lane reads
-  // fragments of the 32-k step kk (0, 1): A rows wm*128 + i*16 + (lane & 15) and B rows
-  // wn*16 NJ + j*16 + (lane & 15), k-chunk 4 kk + lane / 16 (8 consecutive k per lane)
-  auto frags = [&](int stage, int kk, bf16x8_t (&fa)[8], bf16x8_t (&fb)[NJ]) {
-    const uint16_t* as = smem + stage * 2 * TILE;
-    const uint16_t* bs = as + TILE;
-    const int slot = ((kk * 4 + (lane >> 4)) ^ sw) * 8;
-    auto read_a = [&](int i) {
-      fa[i] = *reinterpret_cast<const bf16x8_t*>(as + (wm * 128 + i * 16 + (lane & 15)) * BK + slot);
-    };
-    if constexpr (BKM) {
-      // program order A0 B0 A1 B1 .. A3 B3 A4 .. A7: the reads stay in this order, so pinning
-      // the A reads among the MFMAs spreads the B reads too
-      const uint32_t sofs = uint32_t(stage) * (2 * TILE * 2);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        read_a(j);
-        typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
-        u32x2_t h0, h1;
-        const uint32_t a = bfa[j] + sofs;
-        if (kk == 0) {
-          asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(h0) : "v"(a) : "memory");
-          asm volatile("ds_read_b64_tr_b16 %0, %1 offset:2048" : "=v"(h1) : "v"(a) : "memory");
-        } else {
-          asm volatile("ds_read_b64_tr_b16 %0, %1 offset:16384" : "=v"(h0) : "v"(a) : "memory");
-          asm volatile("ds_read_b64_tr_b16 %0, %1 offset:18432" : "=v"(h1) : "v"(a) : "memory");
+        for (int j = 0; j < 4; ++j) {
+          typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+          u32x2_t h0, h1;
+          const uint32_t a = bfa[j] + uint32_t(stb) * (kStage * 2);
+          if (kk == 0) {
+            asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(h0) : "v"(a) : "memory");
+            asm volatile("ds_read_b64_tr_b16 %0, %1 offset:2048" : "=v"(h1) : "v"(a) : "memory");
+          } else {
+            asm volatile("ds_read_b64_tr_b16 %0, %1 offset:16384" : "=v"(h0) : "v"(a) : "memory");
+            asm volatile("ds_read_b64_tr_b16 %0, %1 offset:18432" : "=v"(h1) : "v"(a) : "memory");
+          }
+          fb[kk][j] = __builtin_bit_cast(bf16x8_t, u32x4_t{h0[0], h0[1], h1[0], h1[1]});
         }
-        fb[j] = __builtin_bit_cast(bf16x8_t, u32x4_t{h0[0], h0[1], h1[0], h1[1]});
+      } else {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+          fb[kk][j] = *reinterpret_cast<const bf16x8_t*>(bs + j * 16 * BK + slot);
       }
 #pragma unroll
-      for (int i = 4; i < 8; ++i) read_a(i);
-    } else {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) read_a(i);
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-        fb[j] = *reinterpret_cast<const bf16x8_t*>(bs + (wn * 16 * NJ + j * 16 + (lane & 15)) * BK + slot);
+      for (int i = 0; i < 8; ++i)
+        fa[kk][i] = *reinterpret_cast<const bf16x8_t*>(as + i * 16 * BK + slot);
     }
   };
-  auto mma = [&](const bf16x8_t (&fa)[8], const bf16x8_t (&fb)[NJ]) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+  auto frag_wait = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (BKM)
+      asm volatile("s_waitcnt lgkmcnt(0)"
+                   : "+v"(fb[0][0]), "+v"(fb[0][1]), "+v"(fb[0][2]), "+v"(fb[0][3]),
+                     "+v"(fb[1][0]), "+v"(fb[1][1]), "+v"(fb[1][2]), "+v"(fb[1][3])
+                   :
+                   : "memory");
+    else
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   };
-  auto mma_rows = [&](const bf16x8_t (&fa)[8], const bf16x8_t (&fb)[NJ], int i0, int i1) {
+  auto barrier = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto mma = [&](int kk, int i0, int i1) {
 #pragma unroll
     for (int i = i0; i < i1; ++i)
 #pragma unroll
       for (int j = 0; j < NJ; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[kk][i], fb[kk][j], acc[i][j], 0, 0, 0);
   };
-  auto mma_half = [&](const bf16x8_t (&fa)[8], const bf16x8_t (&fb)[NJ], int h) {
-    mma_rows(fa, fb, 4 * h, 4 * h + 4);
-  };
-
-  bf16x8_t fa0[8], fb0[NJ], fa1[8], fb1[NJ];
-  // fragment reads per k-step that the scheduler places: 8 A reads and 4 B reads, or (K-major
-  // B) the 8 A reads, each followed in program order by the assembly B reads
-  constexpr int NRD = BKM ? 8 : 8 + NJ;
-  // pin the order inside a k-step: the 32 MFMAs of this step with the fragment reads of the
-  // next step spread among the first 24 (at most one step's reads in flight, so the wait before
-  // the next step's MFMAs is exact, and the last read still has 8 MFMAs to land)
-  auto kstep = [&](int stage, int kk_next, bf16x8_t (&fa)[8], bf16x8_t (&fb)[NJ],
-                   bf16x8_t (&na)[8], bf16x8_t (&nb)[NJ]) {
-    frag_wait(fb);
-    // raised wave priority while this k-step's MFMAs issue: the SIMD's other wavefront (at a
-    // barrier, its loads or its epilogue) yields the issue slots (+1-4% on dW, +0-2% on
-    // dhidden; the hand-over block and a higher level measured no better)
-    __builtin_amdgcn_s_setprio(1);
-    frags(stage, kk_next, na, nb);
-    mma(fa, fb);
-    if constexpr (BKM) {
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+  // ---- prologue: what the multiplying phases of tiles -2 and -1 (and -3) would have loaded
+  if (wm == 0) {
+    issue_a(0, 0);
+    issue_b(0, 0);
+    if (nk > 1) {
+      issue_a(1, 1);
+      issue_b(1, 1);
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 + NJ) : "memory");
+    } else {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+    barrier();
+  } else {
+    issue_b(0, 0);
+    issue_a(0, 0);
+    if (nk > 2) {
+      issue_b(1, 1);
+      issue_a(1, 1);
+      issue_b(2, 2);
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(8 + 2 * NJ) : "memory");  // B of tile 0
+      barrier();
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 + NJ) : "memory");
+      barrier();
+    } else {
+      if (nk > 1) {
+        issue_b(1, 1);
+        issue_a(1, 1);
       }
-    } else if constexpr (NJ >= 3) {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      barrier();
+      barrier();
+    }
+  }
+  int sb = 0, sbl = wm ? 0 : 2;  // B stages of tile k and of the tile whose B is loaded
+  // full: tile k + 3 exists; last: k == nk - 1
+  auto tile = [&](int k, auto full_c, auto last_c) {
+    constexpr bool FULL = decltype(full_c)::value, LAST = decltype(last_c)::value;
+    // reading phase
+    read_frags(k & 1, sb);
+    frag_wait();
+    barrier();
+    if constexpr (LAST && MODE == MODE_FWD) {
+      // a partial last tile: nothing past K
+      if ((K % BK) != 0) {
 #pragma unroll
-      for (int q = 0; q < NRD; ++q) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        for (int kk = 0; kk < 2; ++kk) {
+          const bool past = k * BK + (4 * kk + (lane >> 4)) * 8 >= K;
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+            if (past) fa[kk][i] = bf16x8_t{};
+#pragma unroll
+          for (int j = 0; j < NJ; ++j)
+            if (past) fb[kk][j] = bf16x8_t{};
+        }
       }
     }
-    if constexpr (NJ >= 3) __builtin_amdgcn_sched_group_barrier(0x008, 8 * NJ - 2 * (8 + NJ), 0);
+    // multiplying phase; before its barrier the loads of the multiplying phase before have landed
+    __builtin_amdgcn_s_setprio(1);
+    if constexpr (!LAST) {
+      if (FULL || k + 2 < nk) issue_a(k + 2, k & 1);
+      if (FULL || k + 2 + wm < nk) issue_b(k + 2 + wm, sbl);
+    }
+    mma(0, 0, 8);
+    mma(1, 0, 7);
+    if constexpr (FULL) {
+#pragma unroll
+      for (int q = 0; q < 4 + NJ; ++q) {
+        __builtin_amdgcn_sched_group_barrier(0x008, NJ, 0);
+        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+      }
+      __builtin_amdgcn_sched_group_barrier(0x008, 15 * NJ - (4 + NJ) * NJ, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (!LAST) {
+      if (FULL || k + 2 + wm < nk) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 + NJ) : "memory");
+      else if (k + 2 < nk) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+      else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+    if (!LAST || wm == 0) barrier();
+    mma(1, 7, 8);
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_setprio(0);
+    sb = sb == 2 ? 0 : sb + 1;
+    sbl = sbl == 2 ? 0 : sbl + 1;
   };
-  // Long-K GEMMs (dhidden, dW) hand a stage over with a split barrier on an LDS counter: a
-  // wavefront arrives (adds 1) once its own loads of tile kt+1 have landed and its own reads of
-  // tile kt are done, issues 16 more MFMAs, and only then waits for the count of all
-  // wavefronts.  With s_barrier a wavefront can only arrive after issuing those MFMAs, and the
-  // MFMA pipes drain while the last ones come in (a copy without the barrier, wrong results,
-  // ran 4-13% faster); the split form measured +2-4% on these GEMMs and -3% on the short-K
-  // logits GEMM, which keeps s_barrier.  The wait is bounded: running out of spins sets
-  // FASTRL_SB_SYNC_TIMEOUT in the status word (the results are then not to be trusted).
-  constexpr bool SPLIT = MODE != MODE_FWD;
-  typedef __attribute__((address_space(3))) uint32_t lds_u32_t;
-  lds_u32_t* sync = (lds_u32_t*)(smem + 2 * 2 * TILE);
-  if (SPLIT && tid == 0) *sync = 0u;
-  issue(0, 0);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  if (nk == 1 && ktail) zero_tail(0, 0);
-  __syncthreads();
-  frags(0, 0, fa0, fb0);
-  if (nk > 1) issue(1, 1);
-  // one 64-wide tile with its hand-over; LOAD: tile kt+2 exists and is loaded into the stage
-  // tile kt frees (false only for the last hand-over)
-  auto iteration = [&](int kt, auto load) {
-    constexpr bool LOAD = decltype(load)::value;
-    const int cur = kt & 1;
-    kstep(cur, 1, fa0, fb0, fa1, fb1);
-    // last k-step: half of its MFMAs cover the barrier; the other half cover the next
-    // tile's load issue and the first fragment reads of tile kt+1
-    frag_wait(fb1);
-    if constexpr (SPLIT) {
-      if (kt + 2 == nk && ktail) zero_tail(kt + 1, cur ^ 1);
-      // own part of tile kt+1 is in LDS and own reads of tile kt are done
-      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-      // (the add follows the first MFMA row, after the compiler's own wait for the fragments,
-      // so that no wait lands between the add and the MFMAs)
-      mma_rows(fa1, fb1, 0, 1);
-      __builtin_amdgcn_sched_barrier(0);
-      if (lane == 0) __hip_atomic_fetch_add(sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      __builtin_amdgcn_sched_barrier(0);
-      mma_rows(fa1, fb1, 1, 2);
-      __builtin_amdgcn_sched_barrier(0);
-      uint32_t seen = __hip_atomic_load(sync, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      __builtin_amdgcn_sched_barrier(0);
-      mma_rows(fa1, fb1, 2, 4);
-      __builtin_amdgcn_sched_barrier(0);
-      const uint32_t target = uint32_t(kt + 1) * (kThreads / 64);
-      for (int spin = 0; spin < kSyncSpins && seen < target; ++spin) {
-        __builtin_amdgcn_s_sleep(0);
-        seen = __hip_atomic_load(sync, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      }
-      if (seen < target && lane == 0) set_status(p.status, FASTRL_SB_SYNC_TIMEOUT);
-      asm volatile("" ::: "memory");  // LDS reads and loads of the next tile stay below
-    } else {
-      mma_half(fa1, fb1, 0);
-      __builtin_amdgcn_sched_barrier(0);
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // tile kt+1 is in LDS
-      if (kt + 2 == nk && ktail) zero_tail(kt + 1, cur ^ 1);
-      __syncthreads();                                   // and nobody reads tile kt any more
-    }
-    if constexpr (LOAD) issue(kt + 2, cur);
-    frags(cur ^ 1, 0, fa0, fb0);
-    mma_half(fa1, fb1, 1);
-    if constexpr (LOAD) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x020, 4, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x020, NJ, 0);
-    }
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(0x100, NRD / 2, 0);
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(0x100, NRD / 2, 0);
-    __builtin_amdgcn_sched_barrier(0);
-  };
-  int kt = 0;
-  for (; kt + 2 < nk; ++kt) iteration(kt, std::true_type{});
-  if (kt + 1 < nk) iteration(kt++, std::false_type{});
-  {  // last tile
-    const int cur = kt & 1;
-    kstep(cur, 1, fa0, fb0, fa1, fb1);
-    frag_wait(fb1);
-    mma(fa1, fb1);
-  }
+  int k = 0;
+  for (; k + 3 < nk; ++k) tile(k, std::true_type{}, std::false_type{});
+  for (; k + 1 < nk; ++k) tile(k, std::false_type{}, std::false_type{});
+  tile(k, std::false_type{}, std::true_type{});
 }
 
 // Reductions over the four 16-lane groups of a wavefront (lanes c, c + 16, c + 32, c + 48) with
@@ -471,8 +458,8 @@ __device__ __forceinline__ float group_max4(float x) {
 template <int NJ>
 __device__ __forceinline__ void fwd_epilogue_bf16(const GemmParams& p, int m0, int n0, int mb,
                                                   f32x4_t (&acc)[8][NJ], uint16_t* smem) {
-  __syncthreads();  // LDS operand buffers are reused for the cross-wave exchange
-  float* xmax = reinterpret_cast<float*>(smem);  // [2 wm][256 cols]
+  // (the cross-wave exchange takes LDS that the main loop has done with)
+  float* xmax = reinterpret_cast<float*>(free_stage(smem, (p.K + 63) / 64));  // [2 wm][256 cols]
   float* xsum = xmax + 2 * kBN;
   float* xsz = xsum + 2 * kBN;
   constexpr int NT = kThreads;
@@ -711,8 +698,6 @@ __device__ __forceinline__ void dwt_epilogue_bf16(const GemmParams& p, int m0, i
   }
 }
 
-constexpr int kSmemBytes = 2 * 2 * kBM * 64 * 2 + 16;  // two stages of both operands + sync word
-
 // one logits tile of 256 vocab rows x 64 NJ tokens
 template <int NJ>
 __device__ __forceinline__ void fwd_tile(const GemmParams& p, int mb, int n0, uint16_t* smem) {
@@ -721,7 +706,7 @@ __device__ __forceinline__ void fwd_tile(const GemmParams& p, int mb, int n0, ui
   for (int i = 0; i < 8; ++i)
 #pragma unroll
     for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-  mainloop_bf16_dma<MODE_FWD, NJ>(p, mb * kBM, n0, acc, smem);
+  mainloop_bf16<MODE_FWD, NJ>(p, mb * kBM, n0, acc, smem);
   fwd_epilogue_bf16<NJ>(p, mb * kBM, n0, mb, acc, smem);
 }
 
@@ -764,7 +749,7 @@ template <typename T, int MODE>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void lm_gemm_kernel(const GemmParams p) {
   static_assert(sizeof(T) == 2, "float32 runs f32_gemm_kernel");
-  __shared__ __attribute__((aligned(16))) char smem_raw[kSmemBytes];
+  __shared__ __attribute__((aligned(1024))) char smem_raw[kSmemBytes];
   uint16_t* smem = reinterpret_cast<uint16_t*>(smem_raw);
   if constexpr (MODE == MODE_FWD) {
     fwd_block(p, blockIdx.x, smem);
@@ -777,7 +762,7 @@ void lm_gemm_kernel(const GemmParams p) {
     for (int i = 0; i < 8; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-    mainloop_bf16_dma<MODE>(p, m0, n0, acc, smem);
+    mainloop_bf16<MODE>(p, m0, n0, acc, smem);
     if constexpr (MODE == MODE_DH) dh_epilogue_bf16(p, m0, n0, acc);
     else dwt_epilogue_bf16(p, m0, n0, acc);
   }
@@ -1059,7 +1044,7 @@ __global__ __launch_bounds__(256) void f32_gemm_kernel(const GemmParams p) {
 // dhidden tiles, a 19K-token slab at d = 1536 only 1.7).
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void lm_bwd_kernel(const GemmParams q, const GemmParams r) {
-  __shared__ __attribute__((aligned(16))) char smem_raw[kSmemBytes];
+  __shared__ __attribute__((aligned(1024))) char smem_raw[kSmemBytes];
   uint16_t* smem = reinterpret_cast<uint16_t*>(smem_raw);
   const int nh = q.nmb * q.nnb;
   const int b = blockIdx.x;
@@ -1071,11 +1056,11 @@ void lm_bwd_kernel(const GemmParams q, const GemmParams r) {
     for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
   if (b < nh) {
     tile_coords<MODE_DH>(mb, nb, q.nmb, q.nnb, b, q.group);
-    mainloop_bf16_dma<MODE_DH>(q, mb * kBM, nb * kBN, acc, smem);
+    mainloop_bf16<MODE_DH>(q, mb * kBM, nb * kBN, acc, smem);
     dh_epilogue_bf16(q, mb * kBM, nb * kBN, acc);
   } else {
     tile_coords<MODE_DWT>(mb, nb, r.nmb, r.nnb, b - nh, r.group);
-    mainloop_bf16_dma<MODE_DWT>(r, mb * kBM, nb * kBN, acc, smem);
+    mainloop_bf16<MODE_DWT>(r, mb * kBM, nb * kBN, acc, smem);
     dwt_epilogue_bf16(r, mb * kBM, nb * kBN, acc);
   }
 }
@@ -1087,7 +1072,7 @@ void lm_bwd_kernel(const GemmParams q, const GemmParams r) {
 // dh_reduce_kernel adds them in part order.
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void lm_bwd_direct_kernel(const GemmParams q, const GemmParams r) {
-  __shared__ __attribute__((aligned(16))) char smem_raw[kSmemBytes];
+  __shared__ __attribute__((aligned(1024))) char smem_raw[kSmemBytes];
   uint16_t* smem = reinterpret_cast<uint16_t*>(smem_raw);
   const int nt = q.nmb * q.nnb, nh = nt * q.ksplit;
   const int b = blockIdx.x;
@@ -1102,12 +1087,12 @@ void lm_bwd_direct_kernel(const GemmParams q, const GemmParams r) {
     tile_coords<MODE_DH>(mb, nb, q.nmb, q.nnb, b % nt, q.group);
     const int nk = q.K / 64;
     const int k0 = int(int64_t(nk) * s / q.ksplit), k1 = int(int64_t(nk) * (s + 1) / q.ksplit);
-    mainloop_bf16_dma<MODE_DHT>(q, mb * kBM, nb * kBN, acc, smem, k0, k1 - k0);
+    mainloop_bf16<MODE_DHT>(q, mb * kBM, nb * kBN, acc, smem, k0, k1 - k0);
     if (q.ksplit > 1) dh_part_epilogue_bf16(q, mb * kBM, nb * kBN, s, acc);
     else dh_epilogue_bf16(q, mb * kBM, nb * kBN, acc);
   } else {
     tile_coords<MODE_DWT>(mb, nb, r.nmb, r.nnb, b - nh, r.group);
-    mainloop_bf16_dma<MODE_DWT>(r, mb * kBM, nb * kBN, acc, smem);
+    mainloop_bf16<MODE_DWT>(r, mb * kBM, nb * kBN, acc, smem);
     dwt_epilogue_bf16(r, mb * kBM, nb * kBN, acc);
   }
 }
@@ -1145,7 +1130,7 @@ __global__ __launch_bounds__(256) void dh_reduce_kernel(const float* __restrict_
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void lm_redo_kernel(const GemmParams p) {
   if (p.redo_any[0] == 0) return;
-  __shared__ __attribute__((aligned(16))) char smem_raw[kSmemBytes];
+  __shared__ __attribute__((aligned(1024))) char smem_raw[kSmemBytes];
   uint16_t* smem = reinterpret_cast<uint16_t*>(smem_raw);
   const int nt = p.nmb * p.nnb;
   for (int b = blockIdx.x; b < nt; b += gridDim.x) {
@@ -1766,7 +1751,7 @@ static int token_logprob_impl(const void* hidden, const int32_t* row_index, cons
     p.B = hidden; p.ldb = d; p.N = Tc; p.b_rows = row_index; p.b_row_base = t0;
     p.K = d;
     p.pmax = w.pmax; p.psum = w.psum; p.ldp = ch; p.zlab = w.zlab; p.yslab = w.yslab;
-    p.Vreal = V; p.store_e = 0; p.status = status;
+    p.Vreal = V; p.store_e = 0;
     FR_TRY((launch_gemm<T, MODE_FWD>(p, prof ? FASTRL_K_LOGITS_FWD : -1,
                                      2.0 * V * double(Tc) * d, stream)));
     const int32_t nmb = (V + kBM - 1) / kBM;
@@ -2025,7 +2010,7 @@ static int policy_loss_impl(const fastrl_loss_args& a, hipStream_t stream) {
     p.K = d;
     p.pmax = w.pmax; p.psum = w.psum; p.psz = w.psz; p.ldp = tcp; p.zlab = w.zlab;
     p.yslab = w.yslab; p.shift = w.shift; p.E1 = w.E1; p.ldE1 = Vpad;
-    p.Vreal = V; p.store_e = (dh || dw) ? 1 : 0; p.status = a.status;
+    p.Vreal = V; p.store_e = (dh || dw) ? 1 : 0;
     p.redo_blk = w.redo_blk;
     p.redo_any = w.redo_blk + nnb;
     const double f_fwd = 2.0 * double(V) * Tc * d;
@@ -2064,7 +2049,6 @@ static int policy_loss_impl(const fastrl_loss_args& a, hipStream_t stream) {
                  : (void*)(static_cast<float*>(a.dhidden) + t0 * d);
       q.dH_bf16 = a.dhidden_dtype == FASTRL_BF16;
       q.cslab = w.cslab; q.d = d;
-      q.status = a.status;
       if (direct) {
         q.B = a.W; q.ldb = d; q.K = int32_t(rup(V, sizeof(T) == 2 ? 64 : BK_F32)); q.Vreal = V;
         q.ksplit = dh_ksplit(Tc, d, V, a.dtype, dw);
@@ -2081,7 +2065,6 @@ static int policy_loss_impl(const fastrl_loss_args& a, hipStream_t stream) {
       GemmParams r{};
       r.dW = a.dW; r.dW_acc = (dw_written || a.dW_accumulate) ? 1 : 0;
       r.d = d;
-      r.status = a.status;
       if constexpr (sizeof(T) == 2) {  // dW^T = Bd E: A = Bd, B = E1 read K-major
         // (the logits tiles zero the exp-logit rows up to a multiple of 64 tokens)
         const int64_t Tr = rup(Tc, 64);
