@@ -81,6 +81,7 @@ struct GemmParams {
   const int32_t* redo_any;  // nonzero iff some token block of the slab is marked
   // ---- DH epilogue
   int32_t ksplit;           // DHT: parts of K (1: none)
+  int32_t part_first;       // DHT: blocks take the parts of a tile in a row (dh_ksplit)
   float* part;              // DHT with ksplit > 1: [ksplit][M][d] float32 sums of each part
   void* dH;                 // [.., d] at slab offset
   int32_t dH_bf16;
@@ -176,7 +177,7 @@ __device__ __forceinline__ void mainloop_bf16(const GemmParams& p, int m0, int n
   // in bytes; gathered rows take 64-bit lane addresses.  Rows past the edge load a valid one (their
   // results are never stored).
   const int lrow = lane >> 3;
-  const int gch0 = (lane & 7) ^ (lrow >> 1), gch1 = gch0 ^ 4;  // k-chunk of an even / odd load
+  const int gch = (lane & 7) ^ (lrow >> 1);  // k-chunk of an even load; of an odd one gch ^ 4
   const char* abase[4];
   uint32_t aoff[4];
 #pragma unroll
@@ -184,7 +185,7 @@ __device__ __forceinline__ void mainloop_bf16(const GemmParams& p, int m0, int n
     const int r0 = min(m0 + wave * 32 + j * 8, p.M - 1);
     abase[j] = Ag + 2 * int64_t(r0) * p.lda;
     aoff[j] = 2u * uint32_t(min(r0 + lrow, p.M - 1) - r0) * uint32_t(p.lda);
-    if constexpr (MODE != MODE_FWD) aoff[j] += 16u * uint32_t((j & 1) ? gch1 : gch0);
+    if constexpr (MODE != MODE_FWD) aoff[j] += 16u * uint32_t(gch ^ ((j & 1) << 2));
   }
   const char* bbase[NJ];  // uniform (not gathered) or lane address
   uint32_t boff[NJ];
@@ -222,12 +223,12 @@ __device__ __forceinline__ void mainloop_bf16(const GemmParams& p, int m0, int n
       const int r0 = min(n0 + (wave * NJ + j) * 8, p.N - 1);
       bbase[j] = Bg + 2 * int64_t(r0) * p.ldb;
       boff[j] = 2u * uint32_t(min(r0 + lrow, p.N - 1) - r0) * uint32_t(p.ldb) +
-                16u * uint32_t((j & 1) ? gch1 : gch0);
+                16u * uint32_t(gch ^ ((j & 1) << 2));
     }
   }
   // byte offset of a lane's chunk inside tile kt (logits: K need not be whole tiles, and a partial
   // last tile loads a valid chunk for those past K)
-  auto chunk = [&](int kt, bool odd) { return 2 * min((odd ? gch1 : gch0) * 8, K - 8 - kt * BK); };
+  auto chunk = [&](int kt, int odd) { return 2 * min((gch ^ (odd << 2)) * 8, K - 8 - kt * BK); };
   auto issue_a = [&](int kt, int st) {
     uint16_t* d = sA + st * kStage + wave * 32 * BK;
 #pragma unroll
@@ -252,7 +253,7 @@ __device__ __forceinline__ void mainloop_bf16(const GemmParams& p, int m0, int n
         }
         src = bbase[j] + 2 * int64_t(k) * p.ldb + o;
       } else if constexpr (GATHER) {
-        src = bbase[j] + (kt * (2 * BK) + chunk(kt, ((j + bodd) & 1) != 0));
+        src = bbase[j] + (kt * (2 * BK) + chunk(kt, (j + bodd) & 1));
       } else {
         src = bbase[j] + int64_t(kt) * (2 * BK) + boff[j];
       }
@@ -1083,8 +1084,8 @@ void lm_bwd_direct_kernel(const GemmParams q, const GemmParams r) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
   if (b < nh) {
-    const int s = b / nt;
-    tile_coords<MODE_DH>(mb, nb, q.nmb, q.nnb, b % nt, q.group);
+    const int s = q.part_first ? b % q.ksplit : b / nt;
+    tile_coords<MODE_DH>(mb, nb, q.nmb, q.nnb, q.part_first ? b / q.ksplit : b % nt, q.group);
     const int nk = q.K / 64;
     const int k0 = int(int64_t(nk) * s / q.ksplit), k1 = int(int64_t(nk) * (s + 1) / q.ksplit);
     mainloop_bf16<MODE_DHT>(q, mb * kBM, nb * kBN, acc, smem, k0, k1 - k0);
@@ -1623,24 +1624,33 @@ static bool direct_dh(const fastrl_loss_args& a) {
 }
 
 // Parts of K for the dhidden tiles of a Tc-token slab: the count whose estimated time is least,
-// in K steps of 64 (~1.66 us each on a compute unit of its own).  The launch lasts at least as
-// long as its dhidden rounds (parts x tiles over 256 compute units, each K / parts plus ~6 steps
-// of start and end) and as its total work spread evenly (a dW tile: its K plus ~9 steps); parts
-// add their float32 sums' traffic (written and read at ~5 TB/s).
+// in K steps of 64 (~1.2 us each on a compute unit of its own).  The launch lasts at least as
+// long as its dhidden rounds (parts x tiles over 256 compute units, each K / parts plus ~8 steps
+// of start and end) and as its total work spread evenly (a dW tile: its K plus ~12 steps, mostly
+// dW's own traffic); parts add their float32 sums' traffic (written and read at ~5 TB/s).  Next to
+// dW tiles K stays whole where a tile's chain is hidden behind the rest, else the parts are a power
+// of two (with 15% on their rounds, which the dW tiles beside them slow down), and from 4 on blocks take the parts of a tile in a row: blocks are dealt round-robin to the
+// 8 XCDs, so an XCD sees only one or two parts and its L2 holds their strips (2% assumed).
+// Measured, us a call (1, 2, 4, 8, 16 parts; the rule's choice in brackets): d = 1536, V = 151936,
+// 588 tokens 3234, 1876, 1212, [1005], 1006; 2048 tokens 4090, 2676, [2398], 2441, 2532; 8192
+// [8814], 8900, 9004, 9474, 9690; d = 3584, V = 152064, 1000 tokens 4290, 2988, [2913], 2929, 3007;
+// 1975 tokens [5068], .., 5141; 8192 [19622], 19838, 19984, 21080, 21651.
 static int dh_ksplit(int32_t Tc, int32_t d, int32_t V, int32_t dtype, bool dw) {
   if (dtype == FASTRL_F32) return f32_ksplit(Tc, d, V);
   const double nt = double((Tc + kBM - 1) / kBM) * double((d + kBN - 1) / kBN);
   const double nk = double((V + 63) / 64);
   const double wt = dw ? double((V + kBN - 1) / kBN) * double((d + kBM - 1) / kBM) : 0.0;
-  const double wk = double((Tc + 63) / 64) + 9.0;
+  const double wk = double((Tc + 63) / 64) + 12.0;
   int best = 1;
   double best_t = 0.0;
-  for (int s = 1; s <= kMaxKSplit && double(s) * 8.0 <= nk; ++s) {
-    const double part = nk / s + 6.0;
+  for (int s = 1; s <= kMaxKSplit && double(s) * 8.0 <= nk; s += dw ? s : 1) {
+    const double part = nk / s + 8.0;
     const double rounds = std::ceil(nt * s / 256.0) * part;
     const double even = (nt * s * part + wt * wk) / 256.0 + (dw ? wk : 0.0);
-    double t = std::max(rounds, even);
-    if (s > 1) t += double(s) * Tc * d * 8.0 / 5e12 / 1.66e-6;
+    if (dw && s == 1 && rounds <= even) return 1;
+    double t = std::max(dw ? 1.15 * rounds : rounds, even);
+    if (s > 1) t += double(s) * Tc * d * 8.0 / 5e12 / 1.2e-6;
+    if (dw && s >= 4) t *= 0.98;
     if (s == 1 || t < best_t) {
       best = s;
       best_t = t;
@@ -1656,6 +1666,7 @@ static int launch_bwd_direct(GemmParams q, GemmParams r, bool dw, double flops,
   r.nmb = dw ? int((r.M + kBM - 1) / kBM) : 0;
   r.nnb = dw ? int((r.N + kBN - 1) / kBN) : 0;
   q.group = tile_group(MODE_DH, q.K, q.nnb);
+  q.part_first = dw && q.ksplit >= 4;
   r.group = tile_group(MODE_DWT, r.K, r.nnb);
   const int64_t nh = int64_t(q.nmb) * q.nnb * q.ksplit, nw = int64_t(r.nmb) * r.nnb;
   if (nh + nw == 0) return FASTRL_OK;
