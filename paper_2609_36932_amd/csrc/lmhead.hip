@@ -16,7 +16,7 @@
 //        values, two lane-row swaps, one LDS exchange), the sampled token's logit, and
 //        E1[t][v] = exp(z - s_t) (s_t = 0 unless exp(z) would leave float range).
 //   merge   partials -> lse, logp, row max; rows whose max is too far from s_t get
-//           s_t = max_t and their token block is evaluated again (rare), then merge again.
+//           s_t = max_t and their token block is evaluated again (rare; the loss kernel merges them).
 //   loss    g_t and c_t = g_t exp(s_t - lse_t) per token (one block per sequence).  With a
 //           backward it also folds the one-hot term into the exp-logits: since
 //           g_t = c_t exp(lse_t - s_t), E1[t][y_t] -= exp(lse_t - s_t) makes
@@ -1145,12 +1145,16 @@ void lm_redo_kernel(const GemmParams p) {
 
 // ------------------------------------------------------------------ small kernels
 
-// s_t = 0, labels of the slab, validity
-__global__ void slab_prep_kernel(const int32_t* __restrict__ token_ids,
-                                 const int32_t* __restrict__ row_index, int64_t row_base,
-                                 int32_t Tc, int32_t V, int32_t* __restrict__ yslab,
-                                 float* __restrict__ shift, int32_t* __restrict__ status) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
+// s_t = 0, labels of the slab, validity; also clears the slab's flags (at most Tc + 1 of them) and,
+// on a call's first slab, its count of rows evaluated again
+__global__ __launch_bounds__(256) void slab_prep_kernel(
+    const int32_t* __restrict__ token_ids, const int32_t* __restrict__ row_index, int64_t row_base,
+    int32_t Tc, int32_t V, int32_t* __restrict__ yslab, float* __restrict__ shift,
+    int32_t* __restrict__ status, int32_t* __restrict__ flags, int32_t nflags,
+    int32_t* __restrict__ count) {
+  const int t = blockIdx.x * 256 + threadIdx.x;
+  if (t < nflags) flags[t] = 0;
+  if (t == 0 && count) count[0] = 0;
   if (t >= Tc) return;
   int64_t row = row_base + t;
   if (row_index) row = row_index[row];
@@ -1170,7 +1174,7 @@ __global__ void slab_prep_kernel(const int32_t* __restrict__ token_ids,
 //   rel == 0: psum = sum exp(z - pmax) per vocab block (log-prob only path)
 //   rel == 1: psum = sum exp(z - s_t); with check != 0 a row whose max is too far from s_t
 //             (exp(z - s_t) could leave float range) gets s_t = max and its token block is
-//             marked for a second evaluation.
+//             marked for a second evaluation (whose partials loss_kernel merges).
 constexpr int kMergeTok = 32;
 __global__ __launch_bounds__(1024) void merge_kernel(
     const float* __restrict__ pmax, const float* __restrict__ psum,
@@ -1178,9 +1182,7 @@ __global__ __launch_bounds__(1024) void merge_kernel(
     const int32_t* __restrict__ yslab, int32_t Tc, int32_t rel, int32_t check,
     float* __restrict__ lse_out, float* __restrict__ logp_out, float* __restrict__ ent_out,
     float* __restrict__ shift, int32_t* __restrict__ redo_blk, int32_t* __restrict__ redo_count,
-    int32_t* __restrict__ redo_any, int32_t only_after_redo) {
-  // the second merge only matters when the first marked a row (every block reads the same flag)
-  if (only_after_redo && redo_any[0] == 0) return;
+    int32_t* __restrict__ redo_any) {
   __shared__ float sm[16][kMergeTok], ss[16][kMergeTok], sz[16][kMergeTok];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int tok = lane & 31, slice = wv * 2 + (lane >> 5);
@@ -1257,25 +1259,9 @@ __global__ __launch_bounds__(1024) void merge_kernel(
   }
 }
 
-// sum of x[0..n) in float64, fixed order (one block): the mean entropy of the kept tokens
-__global__ __launch_bounds__(256) void sum_f32_kernel(const float* __restrict__ x, int64_t n,
-                                                      float* __restrict__ out) {
-  __shared__ double red[4];
-  double s = 0.0;
-  const int64_t per = (n + blockDim.x - 1) / blockDim.x;
-  const int64_t b = threadIdx.x * per, e = min(n, b + per);
-  for (int64_t i = b; i < e; ++i) s += double(x[i]);
-  // fixed-shape tree: wave butterfly, then the 4 wave sums in order
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  if (lane == 0) red[wv] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) out[0] = float(((red[0] + red[1]) + red[2]) + red[3]);
-}
-
+// sum over a block of 1024 threads in a fixed order: wave butterflies, then the wave sums in order
+constexpr int kSumThreads = 1024;
 __device__ __forceinline__ double block_sum_d(double v, double* red) {
-  // fixed-shape tree: wave butterfly, then the 4 wave sums in order
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -1283,46 +1269,122 @@ __device__ __forceinline__ double block_sum_d(double v, double* red) {
   if (lane == 0) red[wv] = v;
   __syncthreads();
   double s = 0.0;
-  for (int w = 0; w < (int)(blockDim.x >> 6); ++w) s += red[w];
+#pragma unroll
+  for (int w = 0; w < kSumThreads / 64; ++w) s += red[w];
   return s;
+}
+
+// sum of x[0..n) in float64, fixed order (one block): the mean entropy of the kept tokens
+__global__ __launch_bounds__(kSumThreads) void sum_f32_kernel(const float* __restrict__ x, int64_t n,
+                                                              float* __restrict__ out) {
+  __shared__ double red[kSumThreads / 64];
+  double s = 0.0;
+#pragma unroll 4
+  for (int64_t i = threadIdx.x; i < n; i += kSumThreads) s += double(x[i]);
+  s = block_sum_d(s, red);
+  if (threadIdx.x == 0) out[0] = float(s);
+}
+
+struct LossParams {
+  float *logp, *lse, *ent;  // of all tokens (ent may be NULL)
+  const float *old_logp, *ref_logp;
+  const int32_t* row_index;
+  const int64_t* seq_off;
+  const float* adv;
+  const int32_t* seq_index;
+  int32_t S;
+  int64_t T;
+  int32_t seq_begin;        // of the slab
+  int64_t row_base;
+  int32_t algo, norm;
+  float eps_low, eps_high, beta;
+  const float* shift;       // NULL: no exp-logits, hence no shifts
+  float* cslab;
+  double* seq_loss;
+  int32_t* seq_clip;
+  int32_t* status;
+  int32_t nadv;
+  void* E1;                 // NULL without a backward
+  int64_t ldE1;
+  int32_t e_bf16;
+  const int32_t* yslab;
+  // the second evaluation's partials (rows with a shift)
+  const float *psum, *psz, *zlab;
+  int64_t ldp;
+  int32_t nmb;
+  const int32_t* redo_any;
+  // the call's end
+  const int32_t* redo_count;
+  float *loss, *stats;
+};
+
+// sum of per-sequence loss terms in a fixed order (deterministic)
+__global__ __launch_bounds__(kSumThreads) void loss_final_kernel(const LossParams p) {
+  __shared__ double red[kSumThreads / 64];
+  double s = 0.0, c = 0.0;
+  // a contiguous chunk per thread keeps the order fixed for a given S
+  const int per = (p.S + kSumThreads - 1) / kSumThreads;
+  const int b = threadIdx.x * per, e = min(p.S, b + per);
+  for (int i = b; i < e; ++i) {
+    s += p.seq_loss[i];
+    c += p.seq_clip[i];
+  }
+  s = block_sum_d(s, red);
+  c = block_sum_d(c, red);
+  if (threadIdx.x == 0) {
+    p.loss[0] = float(s);
+    if (p.stats) {
+      p.stats[0] = float(c);
+      p.stats[1] = float(p.redo_count[0]);
+    }
+  }
 }
 
 // one block per sequence of the slab: g_t, c_t, the sequence's loss term and, with a backward,
 // the one-hot term of each token folded into its exp-logit row
-__global__ __launch_bounds__(256) void loss_kernel(
-    const float* __restrict__ logp, const float* __restrict__ lse,
-    const float* __restrict__ old_logp, const float* __restrict__ ref_logp,
-    const int32_t* __restrict__ row_index, const int64_t* __restrict__ seq_off,
-    const float* __restrict__ adv, const int32_t* __restrict__ seq_index, int32_t S,
-    int64_t T, int32_t seq_begin, int64_t row_base, int32_t algo, int32_t norm,
-    float eps_low, float eps_high, float beta, const float* __restrict__ shift,
-    float* __restrict__ cslab, double* __restrict__ seq_loss,
-    int32_t* __restrict__ seq_clip, int32_t* __restrict__ status, int32_t nadv,
-    void* __restrict__ E1, int64_t ldE1, int32_t e_bf16, const int32_t* __restrict__ yslab) {
-  __shared__ double red[4];
-  __shared__ double redc[4];
-  const int i = seq_begin + blockIdx.x;
-  const int64_t a = seq_off[i], b = seq_off[i + 1];
+__global__ __launch_bounds__(kSumThreads) void loss_kernel(const LossParams p) {
+  __shared__ double red[kSumThreads / 64];
+  const int i = p.seq_begin + blockIdx.x;
+  const int64_t a = p.seq_off[i], b = p.seq_off[i + 1];
   const int64_t L = b - a;
-  int ai = seq_index ? seq_index[i] : i;
-  if (ai < 0 || ai >= nadv) {
-    if (threadIdx.x == 0) set_status(status, FASTRL_SB_BAD_INDEX);
+  int ai = p.seq_index ? p.seq_index[i] : i;
+  if (ai < 0 || ai >= p.nadv) {
+    if (threadIdx.x == 0) set_status(p.status, FASTRL_SB_BAD_INDEX);
     ai = -1;
   }
-  const double A = ai >= 0 ? double(adv[ai]) : 0.0;
-  const double w = (norm == FASTRL_NORM_TOKEN_MEAN) ? 1.0 / double(T)
-                                                    : (L > 0 ? 1.0 / (double(S) * double(L)) : 0.0);
-  const double lo = 1.0 - double(eps_low), hi = 1.0 + double(eps_high);
-  const bool kl = beta != 0.0f;
+  const double A = ai >= 0 ? double(p.adv[ai]) : 0.0;
+  const double w = (p.norm == FASTRL_NORM_TOKEN_MEAN)
+                       ? 1.0 / double(p.T)
+                       : (L > 0 ? 1.0 / (double(p.S) * double(L)) : 0.0);
+  const double lo = 1.0 - double(p.eps_low), hi = 1.0 + double(p.eps_high);
+  const bool kl = p.beta != 0.0f;
+  // rows that were evaluated again with a shift (rare): their log-sum-exp from the new partials,
+  // by the thread that uses it below
+  if (p.shift && L > 0 && p.redo_any[0] != 0) {
+    for (int64_t t = a + threadIdx.x; t < b; t += kSumThreads) {
+      const int64_t tl = t - p.row_base;
+      const float s_t = p.shift[tl];
+      if (s_t == 0.0f) continue;
+      double S = 0.0, Z = 0.0;
+      for (int m = 0; m < p.nmb; ++m) {
+        S += double(p.psum[int64_t(m) * p.ldp + tl]);
+        if (p.psz) Z += double(p.psz[int64_t(m) * p.ldp + tl]);
+      }
+      const float l = s_t + __logf(float(S));
+      p.lse[t] = l;
+      p.logp[t] = p.yslab[tl] >= 0 ? p.zlab[tl] - l : __int_as_float(0x7fc00000);
+      if (p.ent) p.ent[t] = l - float(Z / S);
+    }
+  }
   double part = 0.0;  // this sequence's contribution to the loss
   int clip = 0;
   double sratio = 0.0, cseq = 0.0;
-  if (algo == FASTRL_GSPO && L > 0) {
+  if (p.algo == FASTRL_GSPO && L > 0) {
     double sl = 0.0;
-    for (int64_t t = a + threadIdx.x; t < b; t += blockDim.x) {
+    for (int64_t t = a + threadIdx.x; t < b; t += kSumThreads) {
       int64_t row = t;
-      if (row_index) row = row_index[t];
-      sl += double(logp[t]) - double(old_logp[row]);
+      if (p.row_index) row = p.row_index[t];
+      sl += double(p.logp[t]) - double(p.old_logp[row]);
     }
     sl = block_sum_d(sl, red);
     sratio = exp(sl / double(L));
@@ -1332,15 +1394,15 @@ __global__ __launch_bounds__(256) void loss_kernel(
     clip = (cseq == 0.0) ? int(L) : 0;
   }
   double kpart = 0.0;
-  for (int64_t t = a + threadIdx.x; t < b; t += blockDim.x) {
+  for (int64_t t = a + threadIdx.x; t < b; t += kSumThreads) {
     int64_t row = t;
-    if (row_index) row = row_index[t];
-    const double x = logp[t];
+    if (p.row_index) row = p.row_index[t];
+    const double x = p.logp[t];
     double g;
-    if (algo == FASTRL_GSPO) {
+    if (p.algo == FASTRL_GSPO) {
       g = (w * double(L)) * (-cseq * sratio * A / double(L));
     } else {
-      const double rho = exp(x - double(old_logp[row]));
+      const double rho = exp(x - double(p.old_logp[row]));
       const double sur = fmin(rho * A, fmin(fmax(rho, lo), hi) * A);
       const double c = ((A >= 0.0 && rho <= hi) || (A < 0.0 && rho >= lo)) ? 1.0 : 0.0;
       kpart += -w * sur;
@@ -1348,60 +1410,34 @@ __global__ __launch_bounds__(256) void loss_kernel(
       clip += (c == 0.0);
     }
     if (kl) {
-      const double f = ref_logp[row];
+      const double f = p.ref_logp[row];
       const double e = exp(f - x);
-      kpart += double(beta) * w * (e - (f - x) - 1.0);
-      g += double(beta) * w * (1.0 - e);
+      kpart += double(p.beta) * w * (e - (f - x) - 1.0);
+      g += double(p.beta) * w * (1.0 - e);
     }
-    const int64_t tl = t - row_base;
-    const float s_t = shift ? shift[tl] : 0.0f;
-    cslab[tl] = float(g * exp(double(s_t) - double(lse[t])));
+    const int64_t tl = t - p.row_base;
+    const float s_t = p.shift ? p.shift[tl] : 0.0f;
+    p.cslab[tl] = float(g * exp(double(s_t) - double(p.lse[t])));
     // one-hot term of dZ folded into the exp-logits for the backward GEMMs: with
     // g_t = c_t exp(lse_t - s_t), c_t (E1[t][y_t] - exp(lse_t - s_t)) = c_t E1[t][y_t] - g_t
-    const int y = E1 ? yslab[tl] : -1;
+    const int y = p.E1 ? p.yslab[tl] : -1;
     if (y >= 0) {
-      const double corr = exp(double(lse[t]) - double(s_t));
-      const int64_t o = tl * ldE1 + y;
-      if (e_bf16) {
-        uint16_t* e = static_cast<uint16_t*>(E1) + o;
+      const double corr = exp(double(p.lse[t]) - double(s_t));
+      const int64_t o = tl * p.ldE1 + y;
+      if (p.e_bf16) {
+        uint16_t* e = static_cast<uint16_t*>(p.E1) + o;
         *e = f32_to_bf16(float(double(bf16_to_f32(*e)) - corr));
       } else {
-        float* e = static_cast<float*>(E1) + o;
+        float* e = static_cast<float*>(p.E1) + o;
         *e = float(double(*e) - corr);
       }
     }
   }
   kpart = block_sum_d(kpart, red);
-  const double clips = block_sum_d(algo == FASTRL_GSPO ? 0.0 : double(clip), redc);
+  const double clips = block_sum_d(p.algo == FASTRL_GSPO ? 0.0 : double(clip), red);
   if (threadIdx.x == 0) {
-    seq_loss[i] = part + kpart;
-    seq_clip[i] = algo == FASTRL_GSPO ? clip : int(clips);
-  }
-}
-
-// sum of per-sequence loss terms in index order (deterministic)
-__global__ void loss_final_kernel(const double* __restrict__ seq_loss,
-                                  const int32_t* __restrict__ seq_clip, int32_t S,
-                                  const int32_t* __restrict__ redo_count,
-                                  float* __restrict__ loss, float* __restrict__ stats) {
-  __shared__ double red[4];
-  __shared__ double redc[4];
-  double s = 0.0, c = 0.0;
-  // contiguous chunk per thread keeps the order fixed for a given S
-  const int per = (S + blockDim.x - 1) / blockDim.x;
-  const int b = threadIdx.x * per, e = min(S, b + per);
-  for (int i = b; i < e; ++i) {
-    s += seq_loss[i];
-    c += seq_clip[i];
-  }
-  s = block_sum_d(s, red);
-  c = block_sum_d(c, redc);
-  if (threadIdx.x == 0) {
-    loss[0] = float(s);
-    if (stats) {
-      stats[0] = float(c);
-      stats[1] = float(redo_count[0]);
-    }
+    p.seq_loss[i] = part + kpart;
+    p.seq_clip[i] = p.algo == FASTRL_GSPO ? clip : int(clips);
   }
 }
 
@@ -1755,7 +1791,8 @@ static int token_logprob_impl(const void* hidden, const int32_t* row_index, cons
   for (int64_t t0 = 0; t0 < Tn; t0 += ch) {
     const int32_t Tc = int32_t(std::min<int64_t>(ch, Tn - t0));
     hipLaunchKernelGGL(slab_prep_kernel, dim3(nb1d(Tc, 256)), dim3(256), 0, stream, token_ids,
-                       row_index, t0, Tc, V, w.yslab, (float*)nullptr, status);
+                       row_index, t0, Tc, V, w.yslab, (float*)nullptr, status,
+                       (int32_t*)nullptr, 0, (int32_t*)nullptr);
     FR_LAUNCHED();
     GemmParams p{};
     p.A = W; p.lda = d; p.M = V;
@@ -1770,7 +1807,7 @@ static int token_logprob_impl(const void* hidden, const int32_t* row_index, cons
                        (const float*)nullptr, ch, nmb, w.zlab, w.yslab, Tc, 0, 0,
                        lse ? lse + t0 : (float*)nullptr, logp + t0, (float*)nullptr,
                        (float*)nullptr, (int32_t*)nullptr, (int32_t*)nullptr,
-                       (int32_t*)nullptr, 0);
+                       (int32_t*)nullptr);
     FR_LAUNCHED();
   }
   return FASTRL_OK;
@@ -1976,9 +2013,11 @@ static int policy_loss_impl(const fastrl_loss_args& a, hipStream_t stream) {
   const bool dh = a.dhidden != nullptr, dw = a.dW != nullptr;
   const int32_t d = a.d, V = a.V;
 
-  hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(64), 0, stream, w.redo_count, int64_t(1), 0);
-  FR_LAUNCHED();
-  // no token at all (S == 0, or only empty sequences): no GEMM writes dW
+  // no token at all (S == 0, or only empty sequences): no slab clears the count or writes dW
+  if (a.T == 0) {
+    hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(64), 0, stream, w.redo_count, int64_t(1), 0);
+    FR_LAUNCHED();
+  }
   if (dw && !a.dW_accumulate && a.T == 0) {
     hipLaunchKernelGGL(fill_i32_kernel, dim3(1024), dim3(256), 0, stream,
                        reinterpret_cast<int32_t*>(a.dW), int64_t(V) * d, 0);
@@ -1993,27 +2032,35 @@ static int policy_loss_impl(const fastrl_loss_args& a, hipStream_t stream) {
     FR_LAUNCHED();
   }
   const size_t nslab = pl.seq_begin.size() - 1;
+  LossParams lp{};
+  lp.logp = w.logp; lp.lse = w.lse; lp.ent = w.ent;
+  lp.old_logp = a.old_logp; lp.ref_logp = a.ref_logp; lp.row_index = a.row_index;
+  lp.seq_off = a.seq_off; lp.adv = a.adv; lp.seq_index = a.seq_index;
+  lp.S = a.S; lp.T = a.T; lp.algo = a.algo; lp.norm = a.norm;
+  lp.eps_low = a.eps_low; lp.eps_high = a.eps_high; lp.beta = a.beta;
+  lp.shift = dh || dw ? w.shift : nullptr; lp.cslab = w.cslab;
+  lp.seq_loss = w.seq_loss; lp.seq_clip = w.seq_clip; lp.status = a.status;
+  lp.nadv = a.seq_index ? INT32_MAX : a.S;
+  lp.E1 = dh || dw ? w.E1 : nullptr; lp.ldE1 = Vpad; lp.e_bf16 = sizeof(T) == 2;
+  lp.yslab = w.yslab; lp.psum = w.psum; lp.psz = w.psz; lp.zlab = w.zlab;
+  lp.ldp = tcp; lp.nmb = nmb;
+  lp.redo_count = w.redo_count; lp.loss = a.loss; lp.stats = a.stats;
   bool dw_written = false;  // a slab's dW GEMM has overwritten dW
   for (size_t si = 0; si < nslab; ++si) {
     const int32_t s0 = pl.seq_begin[si], s1 = pl.seq_begin[si + 1];
     const int64_t t0 = a.seq_off_host[s0];
     const int32_t Tc = int32_t(a.seq_off_host[s1] - t0);
+    lp.seq_begin = s0;
+    lp.row_base = t0;
     if (Tc == 0) {  // only empty sequences (T == 0): their loss terms and clip counts are 0
-      hipLaunchKernelGGL(loss_kernel, dim3(unsigned(s1 - s0)), dim3(256), 0, stream, w.logp,
-                         w.lse, a.old_logp, a.ref_logp, a.row_index, a.seq_off, a.adv,
-                         a.seq_index, a.S, a.T, s0, t0, a.algo, a.norm, a.eps_low, a.eps_high,
-                         a.beta, w.shift, w.cslab, w.seq_loss, w.seq_clip, a.status,
-                         a.seq_index ? INT32_MAX : a.S, (void*)nullptr, int64_t(0), 0,
-                         (const int32_t*)nullptr);
+      hipLaunchKernelGGL(loss_kernel, dim3(unsigned(s1 - s0)), dim3(kSumThreads), 0, stream, lp);
       FR_LAUNCHED();
       continue;
     }
     const int32_t nnb = int32_t(rup(Tc, kBN) / kBN);
     hipLaunchKernelGGL(slab_prep_kernel, dim3(nb1d(Tc, 256)), dim3(256), 0, stream,
-                       a.token_ids, a.row_index, t0, Tc, V, w.yslab, w.shift, a.status);
-    FR_LAUNCHED();
-    hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(256), 0, stream, w.redo_blk,
-                       int64_t(nnb) + 1, 0);
+                       a.token_ids, a.row_index, t0, Tc, V, w.yslab, w.shift, a.status,
+                       w.redo_blk, nnb + 1, si == 0 ? w.redo_count : (int32_t*)nullptr);
     FR_LAUNCHED();
     GemmParams p{};
     p.A = a.W; p.lda = d; p.M = V;
@@ -2031,24 +2078,13 @@ static int policy_loss_impl(const fastrl_loss_args& a, hipStream_t stream) {
                        w.pmax, w.psum, w.psz, tcp, nmb, w.zlab, w.yslab, Tc, store ? 1 : 0,
                        store ? 1 : 0, w.lse + t0, w.logp + t0, w.ent ? w.ent + t0 : nullptr,
                        store ? w.shift : (float*)nullptr, w.redo_blk, w.redo_count,
-                       w.redo_blk + nnb, 0);
+                       w.redo_blk + nnb);
     FR_LAUNCHED();
-    if (store) {
-      // token blocks holding a row that needs a shift: evaluate again, then merge again (both
-      // return at once on the device when no row was marked)
-      FR_TRY(launch_redo<T>(p, stream));
-      hipLaunchKernelGGL(merge_kernel, dim3(nb1d(Tc, kMergeTok)), dim3(1024), 0, stream,
-                         w.pmax, w.psum, w.psz, tcp, nmb, w.zlab, w.yslab, Tc, 1, 0, w.lse + t0,
-                         w.logp + t0, w.ent ? w.ent + t0 : nullptr, w.shift, w.redo_blk,
-                         w.redo_count, w.redo_blk + nnb, 1);
-      FR_LAUNCHED();
-    }
-    hipLaunchKernelGGL(loss_kernel, dim3(unsigned(s1 - s0)), dim3(256), 0, stream, w.logp,
-                       w.lse, a.old_logp, a.ref_logp, a.row_index, a.seq_off, a.adv,
-                       a.seq_index, a.S, a.T, s0, t0, a.algo, a.norm, a.eps_low, a.eps_high,
-                       a.beta, w.shift, w.cslab, w.seq_loss, w.seq_clip, a.status,
-                       a.seq_index ? INT32_MAX : a.S, store ? w.E1 : nullptr, Vpad,
-                       sizeof(T) == 2 ? 1 : 0, w.yslab);
+    // token blocks holding a row that needs a shift: evaluate again (returns at once on the device
+    // when no row was marked); loss_kernel merges those rows
+    if (store) FR_TRY(launch_redo<T>(p, stream));
+    lp.redo_any = w.redo_blk + nnb;
+    hipLaunchKernelGGL(loss_kernel, dim3(unsigned(s1 - s0)), dim3(kSumThreads), 0, stream, lp);
     FR_LAUNCHED();
     GemmParams q{};  // dhidden: C = E W^T (rows = tokens, cols = d, K = padded vocabulary)
     if (dh) {
@@ -2107,11 +2143,10 @@ static int policy_loss_impl(const fastrl_loss_args& a, hipStream_t stream) {
       dw_written = true;
     }
   }
-  hipLaunchKernelGGL(loss_final_kernel, dim3(1), dim3(256), 0, stream, w.seq_loss, w.seq_clip,
-                     a.S, w.redo_count, a.loss, a.stats);
+  hipLaunchKernelGGL(loss_final_kernel, dim3(1), dim3(kSumThreads), 0, stream, lp);
   FR_LAUNCHED();
   if (a.entropy_sum) {
-    hipLaunchKernelGGL(sum_f32_kernel, dim3(1), dim3(256), 0, stream, w.ent, a.T,
+    hipLaunchKernelGGL(sum_f32_kernel, dim3(1), dim3(kSumThreads), 0, stream, w.ent, a.T,
                        a.entropy_sum);
     FR_LAUNCHED();
   }
