@@ -126,7 +126,8 @@ def _check(rc, what):
 
 
 def _p(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    """Address of a tensor (None: NULL); every signature and structure field converts it."""
+    return None if t is None else t.data_ptr()
 
 
 def _arg(t, dtype, name):
@@ -140,11 +141,12 @@ def _arg(t, dtype, name):
         raise FastRLError(f"{name}: expected a contiguous tensor")
     if dtype is not None and t.dtype != dtype:
         raise FastRLError(f"{name}: expected {dtype}, got {t.dtype}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # torch.cuda.current_stream().cuda_stream without building a Stream object (3 us a call)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _workspace(nbytes, device):
@@ -196,6 +198,14 @@ def prune(token_ids, traj_tok_off, rewards, group_off, class_id, group_valid, *,
     plain call (no adv, no group_eps, no class_out) goes through ``fastrl_prune``.
     ``dp_align`` > 1 fills the kept set up to a multiple of that many data-parallel ranks
     (Alg. 1; needs ``adv``)."""
+    return _prune(token_ids, traj_tok_off, rewards, group_off, class_id, group_valid, V, max_group,
+                  max_len, ngram_n, tau, keep_ratio, adv, group_eps, class_out, dp_align, status)[0]
+
+
+def _prune(token_ids, traj_tok_off, rewards, group_off, class_id, group_valid, V, max_group,
+           max_len, ngram_n, tau, keep_ratio, adv, group_eps, class_out, dp_align, status):
+    """prune() and the array that holds its counts followed by its kept offsets, which the host
+    can read in one copy."""
     dev = rewards.device
     Q = group_off.numel() - 1
     N = rewards.numel()
@@ -206,13 +216,14 @@ def prune(token_ids, traj_tok_off, rewards, group_off, class_id, group_valid, *,
                       (group_valid, torch.uint8, "group_valid"), (adv, torch.float32, "adv"),
                       (status, torch.int32, "status")):
         _arg(t, dt, nm)
+    head = torch.empty(N + 3, dtype=torch.int64, device=dev)
     out = dict(
         keep_mask=torch.empty(N, dtype=torch.uint8, device=dev),
         mdap_count=torch.empty(max(Q, 0), dtype=torch.int32, device=dev),
         kept_traj=torch.empty(max(N, 1), dtype=torch.int32, device=dev),
-        kept_tok_off=torch.empty(N + 1, dtype=torch.int64, device=dev),
+        kept_tok_off=head[2:],
         tok_src=torch.empty(max(T_total, 1), dtype=torch.int32, device=dev),
-        counts=torch.empty(2, dtype=torch.int64, device=dev),
+        counts=head[:2],
     )
     ws_n = _lib.fastrl_prune_workspace_size(Q, N, T_total, max_group, ngram_n)
     ws = _workspace(ws_n, dev)
@@ -223,7 +234,7 @@ def prune(token_ids, traj_tok_off, rewards, group_off, class_id, group_valid, *,
             float(keep_ratio), _p(out["keep_mask"]), _p(out["mdap_count"]),
             _p(out["kept_traj"]), _p(out["kept_tok_off"]), _p(out["tok_src"]),
             _p(out["counts"]), _p(status), _p(ws), ws.numel(), _stream()), "fastrl_prune")
-        return out
+        return out, head
     if class_out:
         out["class_id"] = torch.empty(max(N, 1), dtype=torch.int32, device=dev)
     a = PruneArgs()
@@ -240,7 +251,7 @@ def prune(token_ids, traj_tok_off, rewards, group_off, class_id, group_valid, *,
     a.class_out = _p(out["class_id"]) if class_out else None
     a.dp_align = int(dp_align)
     _check(_lib.fastrl_prune_ex(ctypes.byref(a), _stream()), "fastrl_prune_ex")
-    return out
+    return out, head
 
 
 def token_logprob(hidden, W, token_ids, row_index=None, T=None, status=None):
@@ -318,13 +329,14 @@ class LossCall:
         self.seq_off_host = seq_off_host.to(torch.int64).contiguous().cpu()
         S = self.seq_off_host.numel() - 1
         T = int(self.seq_off_host[-1]) if T is None else T
-        self.loss = torch.zeros(1, dtype=torch.float32, device=dev)
-        self.stats = torch.zeros(2, dtype=torch.float32, device=dev)
+        # (every output is written by each run, also for T = 0)
+        self.loss = torch.empty(1, dtype=torch.float32, device=dev)
+        self.stats = torch.empty(2, dtype=torch.float32, device=dev)
         self.logp = torch.empty(max(T, 1), dtype=torch.float32, device=dev)
         self.lse = torch.empty(max(T, 1), dtype=torch.float32, device=dev)
         self.entropy = (torch.empty(max(T, 1), dtype=torch.float32, device=dev)
                         if need_entropy else None)
-        self.entropy_sum = (torch.zeros(1, dtype=torch.float32, device=dev)
+        self.entropy_sum = (torch.empty(1, dtype=torch.float32, device=dev)
                             if need_entropy else None)
         dhd = torch.float32 if dhidden_dtype is None else dhidden_dtype
         self.dhidden = (torch.empty((max(T, 1), d), dtype=dhd, device=dev)
@@ -459,14 +471,13 @@ def hot_path_step(rewards, group_off, token_ids, traj_tok_off, hidden, W, old_lo
     offsets) -> loss forward/backward on the kept tokens.  Returns a dict.  ``group_eps``
     > 0 prunes under continuous-reward groups |A_i - A_j| < group_eps."""
     adv, cls, valid = advantage(rewards, group_off, drop_uniform=drop_uniform, status=status)
-    pr = prune(token_ids, traj_tok_off, rewards, group_off, cls, valid, V=V,
-               max_group=max_group, max_len=max_len, ngram_n=ngram_n, tau=tau,
-               keep_ratio=keep_ratio, status=status,
-               adv=adv if (group_eps or dp_align > 1) else None, group_eps=group_eps,
-               dp_align=dp_align)
-    counts = pr["counts"].cpu()
-    n_kept, t_kept = int(counts[0]), int(counts[1])
-    koff_host = pr["kept_tok_off"][:n_kept + 1].cpu()
+    pr, head = _prune(token_ids, traj_tok_off, rewards, group_off, cls, valid, V, max_group,
+                      max_len, ngram_n, tau, keep_ratio,
+                      adv if (group_eps or dp_align > 1) else None, group_eps, False, dp_align,
+                      status)
+    head = head.cpu()
+    n_kept, t_kept = head[:2].tolist()
+    koff_host = head[2:n_kept + 3]
     call = LossCall(hidden, W, token_ids, old_logp, pr["kept_tok_off"], koff_host, adv,
                     ref_logp=ref_logp, seq_index=pr["kept_traj"], row_index=pr["tok_src"],
                     algo=algo, norm=norm, eps_low=eps_low, eps_high=eps_high, beta=beta,
