@@ -1530,12 +1530,12 @@ static int launch_dh_reduce(const GemmParams& q, hipStream_t stream) {
 }
 
 // Tile group of a GEMM (tile_coords), measured back to back on the two hidden sizes of the
-// workloads: the logits GEMM takes 32 at K = d = 3584 (8 and 16 lose 5% and 2.5% there, 64 is
-// level) and 16 at d = 1536 (+5% on that GEMM against 32; 8, 12, 20, 24 and 64 are slower
-// too); dhidden 4 when d spans 14 column blocks (2, 8 and 16 lose ~1.5%) and 8 when it spans 6
-// (+2% on the backward launch at d = 1536); the dW tiles 4 at both (2 and 8 lose).
-static int tile_group(int mode, int32_t K, int32_t nnb) {
-  if (mode == MODE_FWD) return K <= 2048 ? 16 : 32;
+// workloads: the logits GEMM takes 32 at K = d = 3584 (8 loses 4%, 16 1%; 64 is level) and, with
+// exp-logits stored, 16 at d = 1536 (32 loses 2% on that GEMM, 64 3%); without them 32 there too
+// (18900 tokens: 6356 us against 6519 with 16 and 6741 with 8).  dhidden 4 when d spans 14 column
+// blocks and 8 when it spans 6, the dW tiles 4 (2 to 16 within 0.7% of each other).
+static int tile_group(int mode, int32_t K, int32_t nnb, bool store_e = false) {
+  if (mode == MODE_FWD) return K <= 2048 && store_e ? 16 : 32;
   if (mode == MODE_DH) return nnb <= 8 ? 8 : 4;
   return 4;
 }
@@ -1550,7 +1550,7 @@ static int64_t fwd_tiles(GemmParams& p) {
   p.nmb = int((p.M + kBM - 1) / kBM);
   p.nnb = int((p.N + kBN - 1) / kBN);
   p.narrow = ((p.N % kBN + 63) / 64) % 4;
-  p.group = tile_group(MODE_FWD, p.K, p.nnb);
+  p.group = tile_group(MODE_FWD, p.K, p.nnb, p.store_e != 0);
   const int64_t whole = int64_t(p.nmb) * p.nnb;
   const int last = int(whole % 256);
   p.tail = p.narrow == 0 && last <= 128 ? last : 0;
@@ -1729,7 +1729,7 @@ static int launch_redo(GemmParams p, hipStream_t stream) {
   if constexpr (sizeof(T) != 2) return launch_gemm<T, MODE_FWD>(p, -1, 0.0, stream);
   p.nmb = int((p.M + kBM - 1) / kBM);
   p.nnb = int((p.N + kBN - 1) / kBN);
-  p.group = tile_group(MODE_FWD, p.K, p.nnb);
+  p.group = tile_group(MODE_FWD, p.K, p.nnb, true);
   const int64_t nblk = int64_t(p.nmb) * p.nnb;
   if (nblk == 0) return FASTRL_OK;
   hipLaunchKernelGGL(lm_redo_kernel, dim3(unsigned(std::min<int64_t>(nblk, 256))), dim3(512), 0,
