@@ -8,8 +8,8 @@
 // with operands moved by direct global->LDS loads:
 //   bf16: 256 x 256 block tiles, 8 wavefronts of 128 x 64, v_mfma_f32_16x16x32_bf16, 64-wide K
 //         steps in two LDS stages;
-//   f32:  4 wavefronts on v_mfma_f32_32x32x2_f32, 32-wide K steps; logits tiles of 256 vocab rows
-//         x 64 tokens, gradient tiles of 64 x 64 or 128 x 128 (f32_gemm_kernel).
+//   f32:  v_mfma_f32_32x32x2_f32, 32-wide K steps; logits tiles of 256 vocab rows x 64 tokens,
+//         gradient tiles of 64 x 64 or 128 x 128 (f32_gemm_kernel).
 // Work is cut into slabs of whole sequences; per slab:
 //   FWD  C = W . H_slab^T  (rows = vocab, cols = tokens, K = d).  Epilogue: per token,
 //        the block's max and sum exp(z - s_t) over its 256 vocab rows (in-lane over 32
@@ -771,15 +771,17 @@ void lm_gemm_kernel(const GemmParams p) {
 
 // ------------------------------------------------------------------ float32 GEMMs
 // C[m, n] = sum_k A[m, k] B[n, k] on v_mfma_f32_32x32x2_f32 (64 cycles each, so a wavefront needs
-// little operand traffic and the tiles can be small): 4 wavefronts as WM x WN over a BM x BN tile,
+// little operand traffic and the tiles can be small): wavefronts as WM x WN over a BM x BN tile,
 // 32-wide K steps, ST LDS stages filled by direct global->LDS loads ST - 1 steps ahead.  Float32
 // problems are small (parity runs), so the grid has to fill the chip and the chain of K steps per
 // block has to be short: 256 x 256 tiles with register-staged loads gave 3 blocks of 256 steps
 // (1090 us) on the 640-token dhidden of d = 256, V = 4096, where these take 22 us.  Loss call with
 // both gradients, 256 x 256 tiles -> these: 300 tokens (d 256, V 4096) 1376 -> 86 us, 2048 (512,
-// 8192) 3000 -> 524, 2048 (1024, 32000) 11.0 -> 3.6 ms, 4096 (3584, 152064) 118.7 -> 118.2 ms.
+// 8192) 3000 -> 524, 2048 (1024, 32000) 11.0 -> 3.6 ms, 4096 (3584, 152064) 118.7 -> 118.2 ms; and
+// with two logits wavefronts per SIMD and no test between a K tile's steps 76 us, 483 us, 3.36 ms,
+// and 64.7 -> 58.8 ms for 2048 (3584, 152064).
 //   FWD (A = W, B = gathered hidden rows): both K-contiguous, 256 x 64, so that the partials have
-//        the same 256-row blocks as bf16.
+//        the same 256-row blocks as bf16; 8 wavefronts, two per SIMD, of 64 x 32.
 //   DH  (A = E1, B[n][k] = W[k][n]): B K-major; K in p.ksplit parts (dh_reduce_kernel adds them).
 //   DW  (A[v][t] = E1[t][v], B[n][t] = c_t H[t][n]): both K-major.
 // Fragments: in step s of a tile, lane l of half h = l / 32 holds k = 8 s + 4 h + j for the j-th of
@@ -788,12 +790,13 @@ void lm_gemm_kernel(const GemmParams p) {
 // columns, chunk c in slot c ^ (((k >> 2) & 1) << 3): the two halves of a 4-byte read (k and k + 4)
 // fall on different banks.
 template <int MODE, int BM, int BN, int WM, int WN, int ST>
-__global__ __launch_bounds__(256) void f32_gemm_kernel(const GemmParams p) {
+__global__ __launch_bounds__(64 * WM * WN) void f32_gemm_kernel(const GemmParams p) {
   constexpr bool AKM = MODE == MODE_DW, BKM = MODE != MODE_FWD;
   constexpr int BK = 32, MI = BM / WM / 32, NI = BN / WN / 32;
   constexpr int ASZ = BM * BK, STAGE = (BM + BN) * BK;   // floats
-  constexpr int LA = BM / 32, LB = BN / 32;              // loads per wavefront and tile
-  static_assert(WM * WN == 4 && STAGE * ST * 4 <= 160 * 1024, "");
+  constexpr int NW = WM * WN;
+  constexpr int LA = BM / (8 * NW), LB = BN / (8 * NW);  // loads per wavefront and tile
+  static_assert(LB > 0 && (MODE != MODE_FWD || WM == 4) && STAGE * ST * 4 <= 160 * 1024, "");
   __shared__ __attribute__((aligned(16))) float smem[STAGE * ST];
   if (MODE == MODE_FWD && p.store_e == 2 && p.redo_any[0] == 0) return;
   const int nt = p.nmb * p.nnb;
@@ -887,10 +890,7 @@ __global__ __launch_bounds__(256) void f32_gemm_kernel(const GemmParams p) {
     if (kt + PF < nk) issue(kt + PF, (kt + PF) % ST);
     const float* as = smem + (kt % ST) * STAGE;
     const float* bs = as + ASZ;
-    const int ns = min(4, (p.K - (kt0 + kt) * BK + 7) / 8);
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      if (s >= ns) break;
+    auto step = [&](int s) {
       f32x4_t fa[MI], fb[NI];
 #pragma unroll
       for (int i = 0; i < MI; ++i) fa[i] = frag(AKM, as, wm * (BM / WM) + i * 32 + l31, BM, s);
@@ -903,6 +903,15 @@ __global__ __launch_bounds__(256) void f32_gemm_kernel(const GemmParams p) {
 #pragma unroll
           for (int j = 0; j < NI; ++j)
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][q], fb[j][q], acc[i][j], 0, 0, 0);
+    };
+    const int ns = (p.K - (kt0 + kt) * BK + 7) / 8;  // below 4 in a partial last tile of the logits
+    if (MODE != MODE_FWD || ns >= 4) {
+      // (no test between the steps: the reads of a step go out among the MFMAs of the one before)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) step(s);
+    } else {
+#pragma clang loop unroll(disable)
+      for (int s = 0; s < ns; ++s) step(s);
     }
   }
   // acc[i][j][r]: row 32 i + 8 (r / 4) + 4 half + r % 4, column 32 j + l31 of the wavefront's part
@@ -1572,8 +1581,8 @@ static int launch_f32_tiles(GemmParams p, int kind, double flops, hipStream_t st
                FASTRL_ERR_UNSUPPORTED, "float32 GEMM: unsupported shape");
   {
     ProfScope prof(kind, stream, flops);
-    hipLaunchKernelGGL((f32_gemm_kernel<MODE, BM, BN, WM, WN, ST>), dim3(unsigned(nblk)), dim3(256),
-                       0, stream, p);
+    hipLaunchKernelGGL((f32_gemm_kernel<MODE, BM, BN, WM, WN, ST>), dim3(unsigned(nblk)),
+                       dim3(64 * WM * WN), 0, stream, p);
     FR_LAUNCHED();
   }
   if (MODE == MODE_DH && p.ksplit > 1) return launch_dh_reduce(p, stream);
@@ -1593,7 +1602,7 @@ static int f32_ksplit(int64_t M, int64_t N, int32_t V) {
 template <int MODE>
 static int launch_f32(const GemmParams& p, int kind, double flops, hipStream_t stream) {
   if constexpr (MODE == MODE_FWD)
-    return launch_f32_tiles<MODE, 256, 64, 4, 1, 2>(p, kind, flops, stream);
+    return launch_f32_tiles<MODE, 256, 64, 4, 2, 2>(p, kind, flops, stream);
   else if (f32_big_tiles(p.M, p.N))
     return launch_f32_tiles<MODE, 128, 128, 2, 2, 2>(p, kind, flops, stream);
   else
