@@ -7,7 +7,7 @@
 // One tiled GEMM kernel does the three contractions.  C[m, n] = sum_k A[m, k] B[n, k]
 // with operands moved by direct global->LDS loads:
 //   bf16: 256 x 256 block tiles, 8 wavefronts of 128 x 64, v_mfma_f32_16x16x32_bf16, 64-wide K
-//         steps in two LDS stages;
+//         steps, the two wavefronts of a SIMD multiplying in turn;
 //   f32:  v_mfma_f32_32x32x2_f32, 32-wide K steps; logits tiles of 256 vocab rows x 64 tokens,
 //         gradient tiles of 64 x 64 or 128 x 128 (f32_gemm_kernel).
 // Work is cut into slabs of whole sequences; per slab:
@@ -1549,6 +1549,10 @@ static int tile_group(int mode, int32_t K, int32_t nnb, bool store_e = false) {
   return 4;
 }
 
+// Longest rows of the bf16 GEMMs' operands, in elements: a lane's offset inside 8 rows is 32 bits of
+// bytes (a row of this length is half a GiB)
+constexpr int64_t kMaxLd = int64_t(1) << 28;
+
 // Tiles of a logits GEMM; returns the blocks.  The last N % 256 tokens take a column of narrow tiles
 // (64, 128 or 192 wide) in place of whole ones that are mostly padding.  Without those, a last
 // wave of at most 128 (64) whole tiles on the 256 compute units is cut into 2 (4) pieces per tile,
@@ -1623,6 +1627,7 @@ static int launch_gemm(GemmParams p, int kind, double flops, hipStream_t stream)
     nblk = int64_t(p.nmb) * p.nnb;
   }
   if (nblk == 0) return FASTRL_OK;
+  FR_CHECK_ARG(p.lda < kMaxLd && p.ldb < kMaxLd, FASTRL_ERR_UNSUPPORTED, "GEMM: rows too long");
   // transposed dW: whole 64-k tiles, whole 256-column tiles of the K-major E, 16-byte dW rows
   FR_CHECK_ARG(MODE != MODE_DWT || (p.K % 64 == 0 && p.ldb >= int64_t(p.nnb) * kBN &&
                                     p.ldb % 8 == 0 && p.d % 4 == 0 && p.M == p.d),
@@ -1645,6 +1650,8 @@ static int launch_bwd(GemmParams q, GemmParams r, double flops, hipStream_t stre
   const int64_t nh = int64_t(q.nmb) * q.nnb, nw = int64_t(r.nmb) * r.nnb;
   if (nh + nw == 0) return FASTRL_OK;
   FR_CHECK_ARG(nh + nw < (int64_t(1) << 31), FASTRL_ERR_UNSUPPORTED, "backward GEMMs: grid too large");
+  FR_CHECK_ARG(q.lda < kMaxLd && q.ldb < kMaxLd && r.lda < kMaxLd && r.ldb < kMaxLd,
+               FASTRL_ERR_UNSUPPORTED, "GEMM: rows too long");
   FR_CHECK_ARG(r.K % 64 == 0 && r.ldb >= int64_t(r.nnb) * kBN && r.ldb % 8 == 0 && r.d % 4 == 0 &&
                    r.M == r.d,
                FASTRL_ERR_UNSUPPORTED, "transposed dW GEMM: unsupported shape");
@@ -1716,6 +1723,8 @@ static int launch_bwd_direct(GemmParams q, GemmParams r, bool dw, double flops,
   const int64_t nh = int64_t(q.nmb) * q.nnb * q.ksplit, nw = int64_t(r.nmb) * r.nnb;
   if (nh + nw == 0) return FASTRL_OK;
   FR_CHECK_ARG(nh + nw < (int64_t(1) << 31), FASTRL_ERR_UNSUPPORTED, "backward GEMMs: grid too large");
+  FR_CHECK_ARG(q.lda < kMaxLd && q.ldb < kMaxLd && r.lda < kMaxLd && r.ldb < kMaxLd,
+               FASTRL_ERR_UNSUPPORTED, "GEMM: rows too long");
   FR_CHECK_ARG(q.K % 64 == 0 && q.K <= q.lda && q.ldb % 8 == 0 && q.N >= 8 && q.ksplit >= 1 &&
                    q.ksplit * 64 <= q.K && (q.ksplit == 1 || q.part),
                FASTRL_ERR_UNSUPPORTED, "direct dhidden GEMM: unsupported shape");
