@@ -1,11 +1,12 @@
 // Maximizing Differential Advantage Pruning (Sec. 3.2; Alg. 1 Phase 2), the keep-ratio
 // budget, and stream compaction of kept tokens.  Every decision is integer or exact:
 //   K1 ngram_set    one block per trajectory: pack n-grams into keys (21 bits per token) and list
-//                   the distinct ones through a set in LDS (bits for n = 1, else hashed).
+//                   the distinct ones through a set in LDS (bits for n = 1, else hashed).  Also
+//                   writes which question owns each trajectory.
 //   K2 pair_conflict one block per trajectory i: |N_n(o_i) & N_n(o_j)| for every j < i of its
 //                   question and class, by looking the keys of j up in a set of i in LDS, then
 //                   theta < tau as  tau_den * (|U| - |I|) < tau_num * |U|  in int64; the
-//                   outcomes are row i of the question's conflict bit matrix.
+//                   outcomes are trajectory i's row of conflict bits.
 //   K0 group_eps    (continuous rewards, appendix on the grounding task) one wavefront per
 //                   question: classes = connected components of |A_i - A_j| < eps, from the
 //                   sorted advantages (a new class wherever a gap is >= eps).
@@ -102,6 +103,10 @@ __device__ __forceinline__ void set_clear(char* lds, int V, int m, int tid, int 
   uint4* p = reinterpret_cast<uint4*>(lds);
   for (int j = tid; j < S::words(V, m) / 4; j += threads) p[j] = make_uint4(c, c, c, c);
 }
+// whether a question's members can be pruned (K3 flags the others)
+__device__ __forceinline__ bool group_ok(int g0, int g1, int N, int max_group) {
+  return g0 >= 0 && g1 >= g0 && g1 <= N && g1 - g0 <= max_group;
+}
 // a trajectory's list of distinct keys: at its first token's place in the key array
 template <typename K>
 __device__ __forceinline__ K* key_list(uint64_t* keys, int64_t first) {
@@ -116,12 +121,20 @@ template <typename S>
 __global__ __launch_bounds__(256) void ngram_set_kernel(
     const int32_t* __restrict__ tokens, const int64_t* __restrict__ toff, int64_t T_total,
     int32_t V, int32_t n, int32_t max_len, uint64_t* __restrict__ keys,
-    int32_t* __restrict__ nuniq, int32_t* __restrict__ status) {
+    int32_t* __restrict__ nuniq, const int32_t* __restrict__ group_off, int32_t Q, int32_t N,
+    int32_t max_group, int32_t* __restrict__ owner, int32_t* __restrict__ status) {
   typedef typename S::Key K;
   extern __shared__ __attribute__((aligned(16))) char set_raw[];
   __shared__ int32_t count, bad_flag;
   const int i = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63;
+  // the last wavefront notes the owner of the members of question i (and i + gridDim.x, ..)
+  if (tid >= 192)
+    for (int64_t q = i; q < Q; q += gridDim.x) {
+      const int g0 = group_off[q], g1 = group_off[q + 1];
+      if (!group_ok(g0, g1, N, max_group)) continue;  // flagged by K3
+      for (int t = g0 + lane; t < g1; t += 64) owner[t] = int32_t(q);
+    }
   const int64_t a = toff[i], b = toff[i + 1];
   const bool off_ok = a >= 0 && b >= a && b <= T_total;
   if (!off_ok || b - a > max_len) {
@@ -221,26 +234,36 @@ __global__ __launch_bounds__(64) void group_eps_kernel(
 }
 
 // ---------------------------------------------------------------------------- K2
-// Row i of its question's conflict matrix: bit j (j < i, same class) is set where theta < tau.
-// Blocks q * max_group + i: the set of i is built once in LDS and each wavefront looks up the keys
-// of every eighth candidate j, 512 at a time (coalesced reads of j's list, all in flight together;
-// one LDS read per key in a bit set).  Bound by the latency of those reads.  128 questions of 8-16
+// Conflict row of trajectory t0 + blockIdx.x, member i of its question: bit j (j < i, same class) is
+// set where theta < tau.  The set of i is built once in LDS and each wavefront looks up the keys of
+// every eighth candidate j, 512 at a time (coalesced reads of j's list, all in flight together; one
+// LDS read per key in a bit set).  Bound by the latency of those reads.  128 questions of 8-16
 // rollouts of 256-2048 tokens: 477 us with one block per question and binary searches in global
-// memory, 154 us with hash-set lookups (a probe loop per key), 15 us so.
+// memory, 154 us with hash-set lookups (a probe loop per key), 15 us so.  One block per trajectory
+// and not per (question, max_group) slot: the launch follows the rollouts there are, whatever bound
+// the caller states for their groups (1024 questions of 8 under max_group = 256, trigrams: 593 us by
+// slot, 131 us so; under max_group = 8 they are level).
 constexpr int kPairThreads = 512;
+// most blocks of one pair launch (a launch's threads number below 2^32)
+constexpr int kPairBlocks = 1 << 22;
 template <typename S>
 __global__ __launch_bounds__(kPairThreads) void pair_conflict_kernel(
     const int64_t* __restrict__ toff, const int32_t* __restrict__ group_off,
     const int32_t* __restrict__ class_id, uint64_t* __restrict__ keys,
-    const int32_t* __restrict__ nuniq, int32_t N, int32_t V, int32_t max_group, int32_t tau_num,
-    int32_t tau_den, uint64_t* __restrict__ conflict) {
+    const int32_t* __restrict__ nuniq, const int32_t* __restrict__ owner, int32_t t0, int32_t Q,
+    int32_t N, int32_t V, int32_t max_group, int32_t tau_num, int32_t tau_den,
+    uint64_t* __restrict__ conflict) {
   typedef typename S::Key K;
   extern __shared__ __attribute__((aligned(16))) char set_raw[];
   __shared__ int32_t cand[kMaxGroupPrune];
   __shared__ unsigned long long row[kConflictWords];
-  const int q = blockIdx.x / max_group, i = blockIdx.x % max_group;
+  const int t = t0 + blockIdx.x;
+  // a trajectory of no valid question has an owner that K1 did not write, which no test lets pass
+  const int q = owner[t];
+  if (q < 0 || q >= Q) return;
   const int g0 = group_off[q], g1 = group_off[q + 1];
-  if (g0 < 0 || g1 < g0 || g1 > N || g1 - g0 > max_group || i >= g1 - g0) return;  // (flagged by K3)
+  if (!group_ok(g0, g1, N, max_group) || t < g0 || t >= g1) return;
+  const int i = t - g0;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int words = (max_group + 63) / 64;
   const int cls = class_id[g0 + i], na = nuniq[g0 + i];
@@ -291,7 +314,7 @@ __global__ __launch_bounds__(kPairThreads) void pair_conflict_kernel(
     }
   }
   __syncthreads();
-  if (tid < words) conflict[(size_t(q) * max_group + i) * words + tid] = row[tid];
+  if (tid < words) conflict[size_t(t) * words + tid] = row[tid];
 }
 
 // ---------------------------------------------------------------------------- K3
@@ -299,9 +322,9 @@ __global__ __launch_bounds__(64) void select_kernel(
     const float* __restrict__ rewards, const int32_t* __restrict__ group_off,
     const int32_t* __restrict__ class_id, const float* __restrict__ adv,
     const uint8_t* __restrict__ group_valid, int32_t N, int32_t max_group, double keep_ratio,
-    const uint64_t* __restrict__ conflict, uint8_t* __restrict__ keep_mask,
-    int32_t* __restrict__ mdap_count, int32_t* __restrict__ class_out,
-    int32_t* __restrict__ status) {
+    const uint64_t* __restrict__ conflict, const int32_t* __restrict__ owner,
+    uint8_t* __restrict__ keep_mask, int32_t* __restrict__ mdap_count,
+    int32_t* __restrict__ class_out, int32_t* __restrict__ status) {
   __shared__ uint64_t crow[kMaxGroupPrune][kConflictWords];  // conflict row of member i
   __shared__ float rew[kMaxGroupPrune];
   __shared__ uint8_t mdap[kMaxGroupPrune];
@@ -370,10 +393,12 @@ __global__ __launch_bounds__(64) void select_kernel(
   }
   __syncthreads();
   const int words = (max_group + 63) / 64;
-  const uint64_t* cq = conflict + size_t(q) * max_group * words;
+  // (offsets that are not monotone can give a trajectory to two questions: they are flagged, and
+  // its row belongs to the one that K1 noted)
+  const uint64_t* cq = conflict + size_t(g0) * words;
   for (int e = lane; e < G * kConflictWords; e += 64) {
     const int i = e / kConflictWords, w = e % kConflictWords;
-    crow[i][w] = w < words ? cq[i * words + w] : 0;
+    crow[i][w] = w < words && owner[g0 + i] == q ? cq[i * words + w] : 0;
   }
   for (int i = lane; i < G; i += 64) rew[i] = rewards[g0 + i];
   __syncthreads();
@@ -673,7 +698,8 @@ size_t prune_workspace(int32_t Q, int32_t N, int64_t T_total, int32_t max_group)
   Carver c(nullptr);
   c.take<uint64_t>(size_t(T_total > 0 ? T_total : 1));
   c.take<int32_t>(size_t(N + 1));
-  c.take<uint64_t>(size_t(Q > 0 ? Q : 1) * max_group * ((max_group + 63) / 64));
+  c.take<uint64_t>(size_t(N + 1) * ((max_group + 63) / 64));
+  c.take<int32_t>(size_t(N + 1));
   c.take<int32_t>(size_t(N + 1));
   c.take<int32_t>(size_t(N + 1));
   c.take<int32_t>(size_t(N + 1));
@@ -688,26 +714,28 @@ static int launch_sets(const int32_t* token_ids, const int64_t* toff, int64_t T_
                        const int32_t* group_off, const int32_t* cls, int32_t Q, int32_t N,
                        int32_t max_group, int32_t max_len, int32_t V, int32_t ngram_n,
                        int32_t tau_num, int32_t tau_den, uint64_t* keys, int32_t* nuniq,
-                       uint64_t* conflict, int32_t* status, hipStream_t stream) {
+                       int32_t* owner, uint64_t* conflict, int32_t* status, hipStream_t stream) {
   const size_t shm = size_t(S::words(V, max_len)) * 4;
   if (N > 0) {
     if (shm > 64 * 1024)
       FR_HIP(hipFuncSetAttribute((const void*)ngram_set_kernel<S>,
                                  hipFuncAttributeMaxDynamicSharedMemorySize, int(shm)));
     hipLaunchKernelGGL((ngram_set_kernel<S>), dim3(N), dim3(256), shm, stream, token_ids, toff,
-                       T_total, V, ngram_n, max_len, keys, nuniq, status);
+                       T_total, V, ngram_n, max_len, keys, nuniq, group_off, Q, N, max_group, owner,
+                       status);
     FR_LAUNCHED();
   }
   if (Q > 0 && N > 0) {
-    FR_CHECK_ARG(int64_t(Q) * max_group < (int64_t(1) << 31), FASTRL_ERR_UNSUPPORTED,
-                 "fastrl_prune: Q * max_group too large");
     if (shm > 64 * 1024)
       FR_HIP(hipFuncSetAttribute((const void*)pair_conflict_kernel<S>,
                                  hipFuncAttributeMaxDynamicSharedMemorySize, int(shm)));
-    hipLaunchKernelGGL((pair_conflict_kernel<S>), dim3(unsigned(Q) * unsigned(max_group)),
-                       dim3(kPairThreads), shm, stream, toff, group_off, cls, keys, nuniq, N, V,
-                       max_group, tau_num, tau_den, conflict);
-    FR_LAUNCHED();
+    for (int64_t t0 = 0; t0 < N; t0 += kPairBlocks) {
+      const unsigned blocks = unsigned(N - t0 < kPairBlocks ? N - t0 : kPairBlocks);
+      hipLaunchKernelGGL((pair_conflict_kernel<S>), dim3(blocks), dim3(kPairThreads), shm, stream,
+                         toff, group_off, cls, keys, nuniq, owner, int32_t(t0), Q, N, V, max_group,
+                         tau_num, tau_den, conflict);
+      FR_LAUNCHED();
+    }
   }
   return FASTRL_OK;
 }
@@ -723,8 +751,8 @@ int launch_prune(const int32_t* token_ids, const int64_t* toff, int64_t T_total,
   Carver c(ws);
   uint64_t* keys = c.take<uint64_t>(size_t(T_total > 0 ? T_total : 1));
   int32_t* nuniq = c.take<int32_t>(size_t(N + 1));
-  uint64_t* conflict =
-      c.take<uint64_t>(size_t(Q > 0 ? Q : 1) * max_group * ((max_group + 63) / 64));
+  uint64_t* conflict = c.take<uint64_t>(size_t(N + 1) * ((max_group + 63) / 64));
+  int32_t* owner = c.take<int32_t>(size_t(N + 1));
   int32_t* kpos = c.take<int32_t>(size_t(N + 1));
   int32_t* cls_eps = c.take<int32_t>(size_t(N + 1));
   int32_t* frank = c.take<int32_t>(size_t(N + 1));
@@ -737,16 +765,14 @@ int launch_prune(const int32_t* token_ids, const int64_t* toff, int64_t T_total,
     FR_LAUNCHED();
     cls = cls_eps;
   }
-  if (ngram_n == 1 && V <= kMaxBitVocab)
-    FR_TRY(launch_sets<BitSet>(token_ids, toff, T_total, group_off, cls, Q, N, max_group, max_len,
-                               V, ngram_n, tau_num, tau_den, keys, nuniq, conflict, status, stream));
-  else
-    FR_TRY(launch_sets<HashSet>(token_ids, toff, T_total, group_off, cls, Q, N, max_group, max_len,
-                                V, ngram_n, tau_num, tau_den, keys, nuniq, conflict, status, stream));
+  const bool bits = ngram_n == 1 && V <= kMaxBitVocab;
+  FR_TRY((bits ? launch_sets<BitSet> : launch_sets<HashSet>)(
+      token_ids, toff, T_total, group_off, cls, Q, N, max_group, max_len, V, ngram_n, tau_num,
+      tau_den, keys, nuniq, owner, conflict, status, stream));
   if (Q > 0) {
     hipLaunchKernelGGL(select_kernel, dim3(Q), dim3(64), 0, stream, rewards, group_off, cls,
-                       adv, group_valid, N, max_group, keep_ratio, conflict, keep_mask,
-                       mdap_count, class_out, status);
+                       adv, group_valid, N, max_group, keep_ratio, conflict, owner,
+                       keep_mask, mdap_count, class_out, status);
     FR_LAUNCHED();
     if (dp_align > 1) {
       hipLaunchKernelGGL(dp_fill_kernel, dim3(1), dim3(1024), 0, stream, keep_mask, adv,

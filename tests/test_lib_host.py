@@ -226,3 +226,12 @@ def test_status_bits_match_header(fr):
     assert len(bits) >= 10
     assert bits == fr.STATUS_BITS
     assert fr.status_names(0x200) == ["SYNC_TIMEOUT"]
+
+
+def test_prune_workspace_follows_the_rollouts(fr):
+    """The workspace follows the rollouts and tokens there are; a loose max_group adds at most its
+    words of conflict bits per rollout."""
+    f = fr._lib.fastrl_prune_workspace_size
+    N, T = 80000, 1 << 20
+    tight, loose = f(40000, N, T, 4, 1), f(40000, N, T, 256, 1)
+    assert 0 < tight <= loose <= tight + 24 * (N + 1) + 256
