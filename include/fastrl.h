@@ -282,8 +282,11 @@ int64_t fastrl_token_logprob_noalloc_max_chunk(int32_t V);
  *   thus carries one rounding to the operand's type: at most 2^-8 |g_t| per token in bf16,
  *   as with a bf16 dlogits operand).  The [T, V] logits are never stored: the workspace holds
  *   slab * V_pad * sizeof(dtype) bytes (V_pad = V rounded up to 256; 10 GB for the default
- *   slab at V = 152064 in bf16), W^T (d * V_pad) when dhidden is wanted, and small per-token
- *   and per-(vocabulary block, token) arrays.
+ *   slab at V = 152064 in bf16), when dhidden is wanted a region of d * V_pad * 2 bytes in bf16
+ *   (W^T, or in calls of few tokens the float32 parts that dhidden is summed from) or of those
+ *   parts alone in float32 (at most 32 * tokens of the slab * d * 4 bytes, which for a small V
+ *   also sets the bf16 region's size), and small per-token and per-(vocabulary block, token)
+ *   arrays.
  * ------------------------------------------------------------------------------------ */
 typedef struct fastrl_loss_args {
   const void* hidden;

@@ -1967,16 +1967,16 @@ static size_t carve_loss(Carver& c, LossWs& w, const fastrl_loss_args& a, const 
   const int64_t tcp = rup(std::max<int64_t>(tc_max, 1), kBN);
   const int64_t nmb = Vpad / kBM;
   const bool dh = a.dhidden != nullptr, dw = a.dW != nullptr;
-  // one region holds W^T or, where dhidden reads W itself, its float32 parts (the queried size
-  // covers W^T in both cases)
-  int64_t wt = dh ? int64_t(a.d) * Vpad * esz : 0;
+  // one region holds W^T or, where dhidden reads W itself, its float32 parts (bf16: room for W^T in
+  // both cases, the size that callers know; float32 never transposes W)
+  int64_t wt = dh && a.dtype == FASTRL_BF16 ? int64_t(a.d) * Vpad * 2 : 0;
   if (direct_dh(a))
     for (size_t si = 0; si + 1 < pl.seq_begin.size(); ++si) {
       const int64_t Tc = a.seq_off_host[pl.seq_begin[si + 1]] - a.seq_off_host[pl.seq_begin[si]];
       const int ks = Tc > 0 ? dh_ksplit(int32_t(Tc), a.d, a.V, a.dtype, dw) : 1;
       if (ks > 1) wt = std::max(wt, Tc * ks * a.d * int64_t(sizeof(float)));
     }
-  w.WT = dh ? c.take<char>(size_t(wt)) : nullptr;
+  w.WT = wt > 0 ? c.take<char>(size_t(wt)) : nullptr;
   w.E1 = (dh || dw) ? c.take<char>(size_t(tcp) * Vpad * esz) : nullptr;
   w.Bd = dw ? c.take<char>(size_t(a.d) * tcp * esz) : nullptr;
   w.pmax = c.take<float>(size_t(nmb * tcp));

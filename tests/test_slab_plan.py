@@ -86,3 +86,23 @@ def test_default_slab_is_bounded_on_the_7b_workloads(fr):
 def test_negative_slab_is_rejected(fr):
     a, _ = _args(fr, np.asarray([5, 6], dtype=np.int64), -1)
     assert fr._lib.fastrl_policy_loss_slab_plan(ctypes.byref(a), None, 0, None) == -3
+
+
+@pytest.mark.parametrize("dtype, T, d, V, wt, parts", [
+    ("F32", 32768, 3584, 152064, 0, 0),     # float32 never transposes W
+    ("F32", 640, 256, 4096, 0, 32),         # K of dhidden in parts
+    ("BF16", 65536, 3584, 152064, 1, 0),
+    ("BF16", 588, 1536, 151936, 1, 0),
+    ("BF16", 4096, 1024, 2048, 0, 32),      # a small V: parts may outgrow W^T
+])
+def test_workspace_for_dhidden(fr, dtype, T, d, V, wt, parts):
+    """What asking for dhidden beside dW adds to the workspace: room for the transposed W in bf16,
+    for the parts of a slab's sums, nothing else (alignment aside)."""
+    a, off = _args(fr, np.full(T // 2, 2), 0)
+    a.dtype, a.d, a.V = getattr(fr, dtype), d, V
+    a.dW = ctypes.c_void_p(256)
+    without = fr._lib.fastrl_policy_loss_workspace_size(ctypes.byref(a))
+    a.dhidden = ctypes.c_void_p(256)
+    added = fr._lib.fastrl_policy_loss_workspace_size(ctypes.byref(a)) - without
+    w_t = d * -(-V // 256) * 256 * 2
+    assert wt * w_t <= added <= max(wt * w_t, parts * T * d * 4) + 256
