@@ -18,6 +18,8 @@
 //   K4 compaction   exclusive scans of kept flags and kept lengths and a coalesced fill of
 //                   tok_src, one block per trajectory (over 4096 trajectories: the scans in a
 //                   one-block launch of their own).
+#include <type_traits>
+
 #include "common.h"
 
 namespace fastrl {
@@ -51,18 +53,31 @@ struct BitSet {
     if (reinterpret_cast<volatile uint32_t*>(w)[key >> 5] & bit) return false;
     return (atomicOr(&w[key >> 5], bit) & bit) == 0;
   }
-  __device__ __forceinline__ bool has(Key key) const { return (w[key >> 5] >> (key & 31)) & 1u; }
+  // an insert of a key that no other thread inserts
+  __device__ __forceinline__ void insert_new(Key key) { atomicOr(&w[key >> 5], 1u << (key & 31)); }
+  // how many of the U keys (kNone: no key) are in the set
+  template <int U>
+  __device__ __forceinline__ int count(const Key (&k)[U]) const {
+    int n = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (k[u] != kNone) n += (w[k[u] >> 5] >> (k[u] & 31)) & 1u;
+    return n;
+  }
 };
 // otherwise a hash set: open addressing, linear probing, of whose slots at least a sixth stay empty
-// (so every probe ends).  No key equals the empty marker: three 21-bit ids fill 63 bits.
+// (so every probe ends).  No key equals the empty marker: three 21-bit ids fill 63 bits.  A wavefront
+// waits for the longest of its probes, so sets of up to 32 KB take four slots a key: with two, the
+// pair tests of 8192 rollouts of 254 trigrams took 158 us in place of 88 (blocks of 512).
 struct HashSet {
   typedef uint64_t Key;
   static constexpr Key kNone = ~0ull;
   // half of the slots empty where the LDS allows it; 156 KB: 16384 keys leave 3584 slots empty
   static constexpr int kMaxSlots = 19968;
+  static constexpr int kSmallSlots = 4096;  // 32 KB
   static __host__ __device__ int slots(int m) {
-    const int s = 2 * m < 64 ? 64 : 2 * m;
-    return s < kMaxSlots ? s : kMaxSlots;
+    const int s = 4 * m < kSmallSlots ? 4 * m : 2 * m < kSmallSlots ? kSmallSlots : 2 * m;
+    return s < 64 ? 64 : s < kMaxSlots ? s : kMaxSlots;
   }
   static __host__ __device__ int words(int V, int m) { return slots(m) * 2; }
   static constexpr uint32_t kClear = 0xffffffffu;
@@ -86,14 +101,39 @@ struct HashSet {
       if (++h == size) h = 0;
     }
   }
-  __device__ __forceinline__ bool has(Key key) const {
+  __device__ __forceinline__ void insert_new(Key key) {
     uint32_t h = slot(key);
-    for (;;) {
-      const Key c = tab[h];
-      if (c == key) return true;
-      if (c == kNone) return false;
+    while (atomicCAS(reinterpret_cast<unsigned long long*>(tab + h), (unsigned long long)kNone,
+                     (unsigned long long)key) != kNone)
       if (++h == size) h = 0;
+  }
+  // (the U probes of a round are in flight together)
+  template <int U>
+  __device__ __forceinline__ int count(const Key (&k)[U]) const {
+    uint32_t h[U];
+    bool open[U], any = false;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      h[u] = slot(k[u]);
+      open[u] = k[u] != kNone;
+      any |= open[u];
     }
+    int n = 0;
+    while (any) {
+      Key c[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (open[u]) c[u] = tab[h[u]];
+      any = false;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        n += open[u] && c[u] == k[u];
+        open[u] = open[u] && c[u] != k[u] && c[u] != kNone;
+        if (++h[u] == size) h[u] = 0;
+        any |= open[u];
+      }
+    }
+    return n;
   }
 };
 // empties a set (its words are a multiple of 4 and at most 16-byte aligned pieces)
@@ -122,7 +162,7 @@ __global__ __launch_bounds__(256) void ngram_set_kernel(
     const int32_t* __restrict__ tokens, const int64_t* __restrict__ toff, int64_t T_total,
     int32_t V, int32_t n, int32_t max_len, uint64_t* __restrict__ keys,
     int32_t* __restrict__ nuniq, const int32_t* __restrict__ group_off, int32_t Q, int32_t N,
-    int32_t max_group, int32_t* __restrict__ owner, int32_t* __restrict__ status) {
+    int32_t max_group, int2* __restrict__ owner, int32_t* __restrict__ status) {
   typedef typename S::Key K;
   extern __shared__ __attribute__((aligned(16))) char set_raw[];
   __shared__ int32_t count, bad_flag;
@@ -133,7 +173,7 @@ __global__ __launch_bounds__(256) void ngram_set_kernel(
     for (int64_t q = i; q < Q; q += gridDim.x) {
       const int g0 = group_off[q], g1 = group_off[q + 1];
       if (!group_ok(g0, g1, N, max_group)) continue;  // flagged by K3
-      for (int t = g0 + lane; t < g1; t += 64) owner[t] = int32_t(q);
+      for (int t = g0 + lane; t < g1; t += 64) owner[t] = make_int2(int(q), g0);
     }
   const int64_t a = toff[i], b = toff[i + 1];
   const bool off_ok = a >= 0 && b >= a && b <= T_total;
@@ -239,18 +279,26 @@ __global__ __launch_bounds__(64) void group_eps_kernel(
 // every eighth candidate j, 512 at a time (coalesced reads of j's list, all in flight together; one
 // LDS read per key in a bit set).  Bound by the latency of those reads.  128 questions of 8-16
 // rollouts of 256-2048 tokens: 477 us with one block per question and binary searches in global
-// memory, 154 us with hash-set lookups (a probe loop per key), 15 us so.  One block per trajectory
-// and not per (question, max_group) slot: the launch follows the rollouts there are, whatever bound
-// the caller states for their groups (1024 questions of 8 under max_group = 256, trigrams: 593 us by
-// slot, 131 us so; under max_group = 8 they are level).
-constexpr int kPairThreads = 512;
+// memory, 15 us so (unigrams).  One block per trajectory and not per (question, max_group) slot: the
+// launch follows the rollouts there are, whatever bound the caller states for their groups (1024
+// questions of 8 under max_group = 256: 593 us by slot, 131 us so; under max_group = 8 level).
+// Threads (launch_sets): with few blocks, or many candidates each, the wavefronts of one work on its
+// candidates at once; from 4096 blocks on the chip is full, and a short list of few candidates
+// occupies a wavefront or two of a block, whose others only keep blocks out.  Pair tests in us, hashed
+// trigrams, 128 / 256 / 512 threads: 8192 rollouts of 254 35 / 38 / 53 (1024 questions of 8), 16384 of
+// 62 22 / 39 / 69 (4096 of 4), 8192 of 698 139 / 100 / 108, 2048 of 698 81 / 53 / 47, 8192 of 1499
+// 471 / 320 / 259; unigrams, 256 / 512: 8192 of 256 20 / 29, 2048 of 256 in groups of 128 46 / 28.
+// (Binary searches in sorted lists, one block per question, took 53, 13 and 195 us in the first three,
+// after sorts of 48, 52 and 151 us where the sets take 21, 22 and 41.)
+// U: keys that a lane looks up at a time.  Hashed, each key of the U waits for the slowest: up to 512
+// keys 2 (16384 rollouts of 62: 22 us, 28 with 4, 46 with 8), above 4 (8 loses 20-30%).
 // most blocks of one pair launch (a launch's threads number below 2^32)
 constexpr int kPairBlocks = 1 << 22;
-template <typename S>
-__global__ __launch_bounds__(kPairThreads) void pair_conflict_kernel(
+template <typename S, int THREADS, int U>
+__global__ __launch_bounds__(THREADS) void pair_conflict_kernel(
     const int64_t* __restrict__ toff, const int32_t* __restrict__ group_off,
     const int32_t* __restrict__ class_id, uint64_t* __restrict__ keys,
-    const int32_t* __restrict__ nuniq, const int32_t* __restrict__ owner, int32_t t0, int32_t Q,
+    const int32_t* __restrict__ nuniq, const int2* __restrict__ owner, int32_t t0, int32_t Q,
     int32_t N, int32_t V, int32_t max_group, int32_t tau_num, int32_t tau_den,
     uint64_t* __restrict__ conflict) {
   typedef typename S::Key K;
@@ -258,15 +306,16 @@ __global__ __launch_bounds__(kPairThreads) void pair_conflict_kernel(
   __shared__ int32_t cand[kMaxGroupPrune];
   __shared__ unsigned long long row[kConflictWords];
   const int t = t0 + blockIdx.x;
-  // a trajectory of no valid question has an owner that K1 did not write, which no test lets pass
-  const int q = owner[t];
-  if (q < 0 || q >= Q) return;
-  const int g0 = group_off[q], g1 = group_off[q + 1];
-  if (!group_ok(g0, g1, N, max_group) || t < g0 || t >= g1) return;
+  // a trajectory of no valid question has an owner that K1 did not write: these tests keep the reads
+  // in range, and the one below refuses it (its loads go out with the candidates')
+  const int2 o = owner[t];
+  const int q = o.x, g0 = o.y;
+  if (q < 0 || q >= Q || g0 < 0 || g0 > t || t - g0 >= max_group) return;
   const int i = t - g0;
+  const int q0 = group_off[q], q1 = group_off[q + 1];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int words = (max_group + 63) / 64;
-  const int cls = class_id[g0 + i], na = nuniq[g0 + i];
+  const int cls = class_id[t], na = nuniq[t];
   // candidates j < i, listed by every wavefront alike (same values to the same places)
   int nc = 0;
   for (int j0 = 0; j0 < i; j0 += 64) {
@@ -275,22 +324,22 @@ __global__ __launch_bounds__(kPairThreads) void pair_conflict_kernel(
     if (c) cand[nc + __popcll(mask & ((1ull << lane) - 1))] = j0 + lane;
     nc += __popcll(mask);
   }
+  if (q0 != g0 || t >= q1 || !group_ok(q0, q1, N, max_group)) return;
   if (tid < kConflictWords) row[tid] = 0;
   S set(set_raw, V, na);
   if (nc > 0 && na > 0) {
-    const K* ka = key_list<K>(keys, toff[g0 + i]);
-    set_clear<S>(set_raw, V, na, tid, kPairThreads);
+    const K* ka = key_list<K>(keys, toff[t]);
+    set_clear<S>(set_raw, V, na, tid, THREADS);
     __syncthreads();
-    for (int e = tid; e < na; e += kPairThreads) set.insert(ka[e]);
+    for (int e = tid; e < na; e += THREADS) set.insert_new(ka[e]);
   }
   __syncthreads();
-  for (int p = wv; p < nc; p += kPairThreads / 64) {
+  for (int p = wv; p < nc; p += THREADS / 64) {
     const int j = cand[p];
     const int nb = nuniq[g0 + j];
     int cnt = 0;
     if (na > 0 && nb > 0) {
       const K* kb = key_list<K>(keys, toff[g0 + j]);
-      constexpr int U = 8;
       for (int e0 = 0; e0 < nb; e0 += 64 * U) {
         K k[U];
 #pragma unroll
@@ -298,18 +347,16 @@ __global__ __launch_bounds__(kPairThreads) void pair_conflict_kernel(
           const int e = e0 + 64 * u + lane;
           k[u] = e < nb ? kb[e] : S::kNone;
         }
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-          if (k[u] != S::kNone) cnt += set.has(k[u]);
+        cnt += set.template count<U>(k);
       }
     }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
     if (lane == 0) {
-      const int64_t I = cnt, U = int64_t(na) + nb - cnt;
+      const int64_t both = cnt, any = int64_t(na) + nb - cnt;
       bool c;
-      if (U == 0) c = tau_num > 0;  // theta = 0 for two empty sets
-      else c = int64_t(tau_den) * (U - I) < int64_t(tau_num) * U;
+      if (any == 0) c = tau_num > 0;  // theta = 0 for two empty sets
+      else c = int64_t(tau_den) * (any - both) < int64_t(tau_num) * any;
       if (c) atomicOr(&row[j >> 6], 1ull << (j & 63));
     }
   }
@@ -322,7 +369,7 @@ __global__ __launch_bounds__(64) void select_kernel(
     const float* __restrict__ rewards, const int32_t* __restrict__ group_off,
     const int32_t* __restrict__ class_id, const float* __restrict__ adv,
     const uint8_t* __restrict__ group_valid, int32_t N, int32_t max_group, double keep_ratio,
-    const uint64_t* __restrict__ conflict, const int32_t* __restrict__ owner,
+    const uint64_t* __restrict__ conflict, const int2* __restrict__ owner,
     uint8_t* __restrict__ keep_mask, int32_t* __restrict__ mdap_count,
     int32_t* __restrict__ class_out, int32_t* __restrict__ status) {
   __shared__ uint64_t crow[kMaxGroupPrune][kConflictWords];  // conflict row of member i
@@ -398,7 +445,9 @@ __global__ __launch_bounds__(64) void select_kernel(
   const uint64_t* cq = conflict + size_t(g0) * words;
   for (int e = lane; e < G * kConflictWords; e += 64) {
     const int i = e / kConflictWords, w = e % kConflictWords;
-    crow[i][w] = w < words && owner[g0 + i] == q ? cq[i * words + w] : 0;
+    const int own = owner[g0 + i].x;
+    const uint64_t c = cq[i * words + min(w, words - 1)];  // (both loads before the test)
+    crow[i][w] = w < words && own == q ? c : 0;
   }
   for (int i = lane; i < G; i += 64) rew[i] = rewards[g0 + i];
   __syncthreads();
@@ -699,7 +748,7 @@ size_t prune_workspace(int32_t Q, int32_t N, int64_t T_total, int32_t max_group)
   c.take<uint64_t>(size_t(T_total > 0 ? T_total : 1));
   c.take<int32_t>(size_t(N + 1));
   c.take<uint64_t>(size_t(N + 1) * ((max_group + 63) / 64));
-  c.take<int32_t>(size_t(N + 1));
+  c.take<int2>(size_t(N + 1));
   c.take<int32_t>(size_t(N + 1));
   c.take<int32_t>(size_t(N + 1));
   c.take<int32_t>(size_t(N + 1));
@@ -714,7 +763,7 @@ static int launch_sets(const int32_t* token_ids, const int64_t* toff, int64_t T_
                        const int32_t* group_off, const int32_t* cls, int32_t Q, int32_t N,
                        int32_t max_group, int32_t max_len, int32_t V, int32_t ngram_n,
                        int32_t tau_num, int32_t tau_den, uint64_t* keys, int32_t* nuniq,
-                       int32_t* owner, uint64_t* conflict, int32_t* status, hipStream_t stream) {
+                       int2* owner, uint64_t* conflict, int32_t* status, hipStream_t stream) {
   const size_t shm = size_t(S::words(V, max_len)) * 4;
   if (N > 0) {
     if (shm > 64 * 1024)
@@ -726,14 +775,30 @@ static int launch_sets(const int32_t* token_ids, const int64_t* toff, int64_t T_
     FR_LAUNCHED();
   }
   if (Q > 0 && N > 0) {
+    // (the sizes: see pair_conflict_kernel)
+    const bool many = N >= 4096 && N <= 64 * int64_t(Q);
+    struct {
+      decltype(&pair_conflict_kernel<S, 512, 4>) kernel;
+      int threads;
+    } pair;
+    if constexpr (std::is_same<S, BitSet>::value) {
+      if (many && max_len <= 512) pair = {pair_conflict_kernel<S, 256, 8>, 256};
+      else pair = {pair_conflict_kernel<S, 512, 8>, 512};
+    } else if (max_len <= 512) {
+      if (many) pair = {pair_conflict_kernel<S, 128, 2>, 128};
+      else pair = {pair_conflict_kernel<S, 512, 2>, 512};
+    } else {
+      if (many && max_len <= 1024) pair = {pair_conflict_kernel<S, 256, 4>, 256};
+      else pair = {pair_conflict_kernel<S, 512, 4>, 512};
+    }
     if (shm > 64 * 1024)
-      FR_HIP(hipFuncSetAttribute((const void*)pair_conflict_kernel<S>,
+      FR_HIP(hipFuncSetAttribute((const void*)pair.kernel,
                                  hipFuncAttributeMaxDynamicSharedMemorySize, int(shm)));
     for (int64_t t0 = 0; t0 < N; t0 += kPairBlocks) {
       const unsigned blocks = unsigned(N - t0 < kPairBlocks ? N - t0 : kPairBlocks);
-      hipLaunchKernelGGL((pair_conflict_kernel<S>), dim3(blocks), dim3(kPairThreads), shm, stream,
-                         toff, group_off, cls, keys, nuniq, owner, int32_t(t0), Q, N, V, max_group,
-                         tau_num, tau_den, conflict);
+      hipLaunchKernelGGL(pair.kernel, dim3(blocks), dim3(pair.threads), shm, stream, toff, group_off,
+                         cls, keys, nuniq, owner, int32_t(t0), Q, N, V, max_group, tau_num, tau_den,
+                         conflict);
       FR_LAUNCHED();
     }
   }
@@ -752,7 +817,7 @@ int launch_prune(const int32_t* token_ids, const int64_t* toff, int64_t T_total,
   uint64_t* keys = c.take<uint64_t>(size_t(T_total > 0 ? T_total : 1));
   int32_t* nuniq = c.take<int32_t>(size_t(N + 1));
   uint64_t* conflict = c.take<uint64_t>(size_t(N + 1) * ((max_group + 63) / 64));
-  int32_t* owner = c.take<int32_t>(size_t(N + 1));
+  int2* owner = c.take<int2>(size_t(N + 1));
   int32_t* kpos = c.take<int32_t>(size_t(N + 1));
   int32_t* cls_eps = c.take<int32_t>(size_t(N + 1));
   int32_t* frank = c.take<int32_t>(size_t(N + 1));

@@ -26,7 +26,11 @@ def fr():
     (2, 70, (1, 260), 9, 3),        # two words; trigrams over 9 ids, more keys than a block
     (4, 8, (510, 514), 1 << 19, 1),  # a key per thread and one more; the largest bit set
     (4, 8, (255, 258), (1 << 19) + 1, 1),  # unigrams in the hash set
-    (3, 8, (28, 36), 50, 2),        # 27-35 bigrams around the smallest hash set
+    (3, 8, (14, 20), 50, 2),        # 13-19 bigrams around the smallest hash set
+    (3, 8, (1022, 1028), 90, 2),    # around the last set with four slots a key
+    (3, 8, (2046, 2052), 90, 2),    # around the last of 32 KB
+    (1366, 3, (508, 518), 700, 2),  # 4098 rollouts of up to 518: blocks of 256
+    (1366, 3, (505, 512), 700, 3),  # and of up to 512: blocks of 128
     (4, 8, (1000, 1300), 3, 1),     # at most 3 distinct ids: every insert but three is a repeat
 ])
 @pytest.mark.parametrize("keep", [0.0, 0.5])
