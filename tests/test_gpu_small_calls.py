@@ -156,3 +156,43 @@ def test_logits_tiles(fr, T, d, V):
     torch.cuda.synchronize()
     assert (call.logp.double().cpu() - logp).abs().max() < 2e-5
     assert _rel(call.dhidden, dH) < 1e-2 and _rel(call.dW, dW) < 1e-2
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("T, big, offs", [
+    (600, range(260, 301), (0, 130, 290, 600)),       # one of three 256-token blocks
+    (600, range(512, 600), (0, 200, 512, 530, 600)),  # the narrow last column's, and only those
+    (300, range(0, 300, 7), (0, 1, 33, 300)),         # some rows of every block
+    (70, range(70), (0, 70)),                         # every row
+])
+def test_shifted_rows_in_one_slab(fr, dtype, T, big, offs):
+    """Rows whose logits leave exp's range, in some 256-token blocks of one slab: exactly those rows
+    are evaluated again with a shift, and every output matches float64, their neighbours' too.
+    Log-probs: float32 values of up to ~300 (half an ulp 1.5e-5) summed over d = 72 and rounded a few
+    times; gradients: bf16 operands, or that error in an exponent."""
+    d, V = 72, 1300
+    H, W, y, *_ = _problem(T, d, V, T + len(big), dtype)
+    H[list(big)] *= 64.0
+    z = H.double() @ W.double().T
+    top = z.max(1).values
+    assert not ((top.abs() > 55) & (top.abs() < 65)).any()
+    lse = torch.logsumexp(z, 1)
+    logp = z.gather(1, y.long()[:, None])[:, 0] - lse
+    old = (logp + 0.05 * torch.randn(T, generator=torch.Generator().manual_seed(3))).float()
+    off = np.asarray(offs, dtype=np.int64)
+    adv = torch.linspace(-1.0, 1.5, len(off) - 1) if len(off) > 2 else torch.ones(1)
+    loss, dH, dW = _reference(H, W, y, z, lse, logp, old, off, adv)
+    rows = torch.arange(T - 1, -1, -1, dtype=torch.int32)
+    call = fr.policy_loss_fwd_bwd(
+        H.flip(0).contiguous().to(DEV), W.to(DEV), y.flip(0).contiguous().to(DEV),
+        old.flip(0).contiguous().to(DEV), torch.from_numpy(off).to(DEV), torch.from_numpy(off),
+        adv.to(DEV), row_index=rows.to(DEV), need_entropy=True, T=T)
+    torch.cuda.synchronize()
+    assert int(call.stats[1].item()) == int((top.abs() >= 60).sum()) == len(big)
+    assert (call.lse.double().cpu() - lse).abs().max() < 2e-4
+    assert (call.logp.double().cpu() - logp).abs().max() < 2e-4
+    ent = lse - (torch.exp(z - lse[:, None]) * z).sum(1)
+    assert (call.entropy.double().cpu() - ent).abs().max() < 2e-3
+    assert abs(call.loss.item() - loss.item()) <= 1e-3 * abs(loss.item())
+    tol = 1e-2 if dtype == torch.bfloat16 else 1e-3
+    assert _rel(call.dhidden, dH) < tol and _rel(call.dW, dW) < tol
