@@ -65,6 +65,7 @@ struct GemmParams {
   int32_t group;            // tile order: M-blocks per sweep over the N-blocks (tile_group)
   int32_t tail, pieces;     // FWD: the last `tail` whole tiles are cut into `pieces` (fwd_tiles)
   int32_t narrow;           // FWD: 64-token columns of the narrow last tile column (0: none)
+  int32_t block0;           // float32: tile number of a launch's first block
   // ---- FWD epilogue
   float* pmax;              // [nmb][ldp]
   float* psum;              // [nmb][ldp]
@@ -800,8 +801,9 @@ __global__ __launch_bounds__(64 * WM * WN) void f32_gemm_kernel(const GemmParams
   __shared__ __attribute__((aligned(16))) float smem[STAGE * ST];
   if (MODE == MODE_FWD && p.store_e == 2 && p.redo_any[0] == 0) return;
   const int nt = p.nmb * p.nnb;
-  const int part = MODE == MODE_DH ? int(blockIdx.x) / nt : 0;
-  const int b = int(blockIdx.x) - part * nt;
+  const int tile = p.block0 + int(blockIdx.x);
+  const int part = MODE == MODE_DH ? tile / nt : 0;
+  const int b = tile - part * nt;
   const int mb = b % p.nmb, nb = b / p.nmb;
   const int m0 = mb * BM, n0 = nb * BN;
   if (MODE == MODE_FWD && p.store_e == 2 && p.redo_blk[n0 / kBN] == 0) return;
@@ -1542,6 +1544,8 @@ static inline int64_t rup(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 
 constexpr int kMaxKSplit = 32;  // parts of K of a dhidden GEMM
 constexpr int BK_F32 = 32;      // K step of the float32 GEMMs
+// blocks of one launch at most: a launch's threads number below 2^32, and the largest blocks are of 1024
+constexpr int64_t kMaxBlocks = int64_t(1) << 21;
 
 static int launch_dh_reduce(const GemmParams& q, hipStream_t stream) {
   const int64_t n4 = int64_t(q.M) * (q.d / 4);
@@ -1579,7 +1583,7 @@ static int64_t fwd_tiles(GemmParams& p) {
   p.group = tile_group(MODE_FWD, p.K, p.nnb, p.store_e != 0);
   const int64_t whole = int64_t(p.nmb) * p.nnb;
   const int last = int(whole % 256);
-  p.tail = p.narrow == 0 && last <= 128 ? last : 0;
+  p.tail = p.narrow == 0 && last <= 128 && whole < kMaxBlocks ? last : 0;
   p.pieces = p.tail == 0 ? 1 : p.tail <= 64 ? 4 : 2;
   return whole + int64_t(p.tail) * (p.pieces - 1);
 }
@@ -1598,9 +1602,13 @@ static int launch_f32_tiles(GemmParams p, int kind, double flops, hipStream_t st
                FASTRL_ERR_UNSUPPORTED, "float32 GEMM: unsupported shape");
   {
     ProfScope prof(kind, stream, flops);
-    hipLaunchKernelGGL((f32_gemm_kernel<MODE, BM, BN, WM, WN, ST>), dim3(unsigned(nblk)),
-                       dim3(64 * WM * WN), 0, stream, p);
-    FR_LAUNCHED();
+    for (int64_t b = 0; b < nblk; b += kMaxBlocks) {
+      p.block0 = int32_t(b);
+      hipLaunchKernelGGL((f32_gemm_kernel<MODE, BM, BN, WM, WN, ST>),
+                         dim3(unsigned(std::min(nblk - b, kMaxBlocks))), dim3(64 * WM * WN), 0, stream,
+                         p);
+      FR_LAUNCHED();
+    }
   }
   if (MODE == MODE_DH && p.ksplit > 1) return launch_dh_reduce(p, stream);
   return FASTRL_OK;
