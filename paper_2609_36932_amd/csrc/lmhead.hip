@@ -1193,11 +1193,11 @@ __global__ __launch_bounds__(1024) void merge_kernel(
     const int32_t* __restrict__ yslab, int32_t Tc, int32_t rel, int32_t check,
     float* __restrict__ lse_out, float* __restrict__ logp_out, float* __restrict__ ent_out,
     float* __restrict__ shift, int32_t* __restrict__ redo_blk, int32_t* __restrict__ redo_count,
-    int32_t* __restrict__ redo_any) {
+    int32_t* __restrict__ redo_any, int32_t block0) {
   __shared__ float sm[16][kMergeTok], ss[16][kMergeTok], sz[16][kMergeTok];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int tok = lane & 31, slice = wv * 2 + (lane >> 5);
-  const int t = blockIdx.x * kMergeTok + tok;
+  const int t = (block0 + int(blockIdx.x)) * kMergeTok + tok;
   const bool ok = t < Tc;
   const bool ent = psz != nullptr;
   // S = sum exp(z - ref), Z = sum exp(z - ref) z, both relative to the same reference
@@ -1785,6 +1785,21 @@ static int launch_redo(GemmParams p, hipStream_t stream) {
 
 static inline unsigned nb1d(int64_t n, int b) { return unsigned((n + b - 1) / b); }
 
+// partials -> lse, logp (and entropy); rel: of stored exp-logits, whose rows are checked for a shift
+static int launch_merge(const float* pmax, const float* psum, const float* psz, int64_t ldp,
+                        int32_t nmb, const float* zlab, const int32_t* yslab, int32_t Tc, bool rel,
+                        float* lse, float* logp, float* ent, float* shift, int32_t* redo_blk,
+                        int32_t* redo_count, int32_t* redo_any, hipStream_t stream) {
+  const int64_t blocks = nb1d(Tc, kMergeTok);
+  for (int64_t b = 0; b < blocks; b += kMaxBlocks) {
+    hipLaunchKernelGGL(merge_kernel, dim3(unsigned(std::min(blocks - b, kMaxBlocks))), dim3(1024), 0,
+                       stream, pmax, psum, psz, ldp, nmb, zlab, yslab, Tc, rel ? 1 : 0, rel ? 1 : 0,
+                       lse, logp, ent, shift, redo_blk, redo_count, redo_any, int32_t(b));
+    FR_LAUNCHED();
+  }
+  return FASTRL_OK;
+}
+
 // ---------------------------------------------------------------- token log-prob only
 constexpr int64_t kLogprobChunk = 65536;
 
@@ -1842,12 +1857,9 @@ static int token_logprob_impl(const void* hidden, const int32_t* row_index, cons
     FR_TRY((launch_gemm<T, MODE_FWD>(p, prof ? FASTRL_K_LOGITS_FWD : -1,
                                      2.0 * V * double(Tc) * d, stream)));
     const int32_t nmb = (V + kBM - 1) / kBM;
-    hipLaunchKernelGGL(merge_kernel, dim3(nb1d(Tc, kMergeTok)), dim3(1024), 0, stream, w.pmax, w.psum,
-                       (const float*)nullptr, ch, nmb, w.zlab, w.yslab, Tc, 0, 0,
-                       lse ? lse + t0 : (float*)nullptr, logp + t0, (float*)nullptr,
-                       (float*)nullptr, (int32_t*)nullptr, (int32_t*)nullptr,
-                       (int32_t*)nullptr);
-    FR_LAUNCHED();
+    FR_TRY(launch_merge(w.pmax, w.psum, nullptr, ch, nmb, w.zlab, w.yslab, Tc, false,
+                        lse ? lse + t0 : nullptr, logp + t0, nullptr, nullptr, nullptr, nullptr,
+                        nullptr, stream));
   }
   return FASTRL_OK;
 }
@@ -2113,12 +2125,9 @@ static int policy_loss_impl(const fastrl_loss_args& a, hipStream_t stream) {
     const double f_fwd = 2.0 * double(V) * Tc * d;
     FR_TRY((launch_gemm<T, MODE_FWD>(p, FASTRL_K_LOGITS_FWD, f_fwd, stream)));
     const bool store = dh || dw;
-    hipLaunchKernelGGL(merge_kernel, dim3(nb1d(Tc, kMergeTok)), dim3(1024), 0, stream,
-                       w.pmax, w.psum, w.psz, tcp, nmb, w.zlab, w.yslab, Tc, store ? 1 : 0,
-                       store ? 1 : 0, w.lse + t0, w.logp + t0, w.ent ? w.ent + t0 : nullptr,
-                       store ? w.shift : (float*)nullptr, w.redo_blk, w.redo_count,
-                       w.redo_blk + nnb);
-    FR_LAUNCHED();
+    FR_TRY(launch_merge(w.pmax, w.psum, w.psz, tcp, nmb, w.zlab, w.yslab, Tc, store, w.lse + t0,
+                        w.logp + t0, w.ent ? w.ent + t0 : nullptr, store ? w.shift : nullptr,
+                        w.redo_blk, w.redo_count, w.redo_blk + nnb, stream));
     // token blocks holding a row that needs a shift: evaluate again (returns at once on the device
     // when no row was marked); loss_kernel merges those rows
     if (store) FR_TRY(launch_redo<T>(p, stream));

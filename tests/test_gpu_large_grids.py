@@ -37,3 +37,31 @@ def test_float32_logits_tiles(fr):
     logp = z.gather(1, y.long()[:, None])[:, 0] - lse
     assert (ls.double() - lse[rows.long()]).abs().max() < 2e-5
     assert (lp.double() - logp[rows.long()]).abs().max() < 2e-5
+
+
+def test_merge_of_a_large_slab(fr):
+    """One slab of 2^27 + 2^13 tokens (loss alone, no gradient): 2^22 + 2^8 merge blocks of 1024
+    threads.  Log-probs to float32 sums of a few terms (2e-5)."""
+    S, L, R, d, V = 128, (1 << 20) + 64, 61, 8, 40
+    T = S * L
+    g = torch.Generator(device=DEV).manual_seed(2)
+    H = torch.randn(R, d, device=DEV, generator=g)
+    W = torch.randn(V, d, device=DEV, generator=g) / d ** 0.5
+    y = torch.randint(0, V, (R,), device=DEV, dtype=torch.int32, generator=g)
+    z = H.double() @ W.double().T
+    lse = torch.logsumexp(z, 1)
+    logp = z.gather(1, y.long()[:, None])[:, 0] - lse
+    old = (logp + 0.02 * torch.randn(R, device=DEV, generator=g)).float()
+    rows = _rows(R, T)
+    off = torch.arange(S + 1, dtype=torch.int64) * L
+    adv = torch.linspace(-1.0, 1.5, S, device=DEV)
+    print(f"[large] merge T={T}", flush=True)
+    call = fr.policy_loss_fwd_bwd(H, W, y, old, off.to(DEV), off, adv, row_index=rows, T=T,
+                                  need_dhidden=False, need_dW=False, slab_tokens=T)
+    assert len(call.slab_plan()[0]) == 2
+    torch.cuda.synchronize()
+    for name, got, want in (("lse", call.lse, lse), ("logp", call.logp, logp)):
+        for a in range(0, T, 1 << 25):
+            b = min(T, a + (1 << 25))
+            err = (got[a:b] - want.float()[rows[a:b].long()]).abs().max()
+            assert err < 2e-5, (name, a, float(err))
