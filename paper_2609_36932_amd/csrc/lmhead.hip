@@ -1518,18 +1518,20 @@ __global__ __launch_bounds__(256) void scale_rows_f32_kernel(
     const float* __restrict__ in, const int32_t* __restrict__ row_index, int64_t row_base,
     int32_t R, int32_t Rpad, int32_t C, const float* __restrict__ scale, float* __restrict__ out) {
   const int c4 = C / 4;
-  const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  const int r = int(i / c4);
-  if (r >= Rpad) return;
-  f32x4_t v = {0.0f, 0.0f, 0.0f, 0.0f};
-  if (r < R) {
-    int64_t row = row_base + r;
-    if (row_index) row = row_index[row];
-    v = reinterpret_cast<const f32x4_t*>(in + row * C)[i % c4];
-    const float s = scale[r];
-    v = f32x4_t{s * v[0], s * v[1], s * v[2], s * v[3]};
+  const int64_t n4 = int64_t(Rpad) * c4;
+  // (once around, unless a launch cannot hold a thread for each piece)
+  for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < n4; i += int64_t(gridDim.x) * 256) {
+    const int r = int(i / c4);
+    f32x4_t v = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (r < R) {
+      int64_t row = row_base + r;
+      if (row_index) row = row_index[row];
+      v = reinterpret_cast<const f32x4_t*>(in + row * C)[i % c4];
+      const float s = scale[r];
+      v = f32x4_t{s * v[0], s * v[1], s * v[2], s * v[3]};
+    }
+    reinterpret_cast<f32x4_t*>(out)[i] = v;
   }
-  reinterpret_cast<f32x4_t*>(out)[i] = v;
 }
 
 __global__ void fill_i32_kernel(int32_t* p, int64_t n, int32_t v) {
@@ -2180,7 +2182,9 @@ static int policy_loss_impl(const fastrl_loss_args& a, hipStream_t stream) {
       } else {  // dW = E^T Bd: A = E1 and B = Bd (here c_t H[t] as rows) both read K-major
         r.K = int32_t(rup(Tc, BK_F32));
         const int64_t n4 = int64_t(r.K) * (d / 4);
-        hipLaunchKernelGGL(scale_rows_f32_kernel, dim3(nb1d(n4, 256)), dim3(256), 0, stream,
+        hipLaunchKernelGGL(scale_rows_f32_kernel,
+                           dim3(unsigned(std::min<int64_t>((n4 + 255) / 256, 4 * kMaxBlocks))),
+                           dim3(256), 0, stream,
                            static_cast<const float*>(a.hidden), a.row_index, t0, Tc, r.K, d,
                            w.cslab, static_cast<float*>(w.Bd));
         FR_LAUNCHED();

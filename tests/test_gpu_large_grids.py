@@ -65,3 +65,33 @@ def test_merge_of_a_large_slab(fr):
             b = min(T, a + (1 << 25))
             err = (got[a:b] - want.float()[rows[a:b].long()]).abs().max()
             assert err < 2e-5, (name, a, float(err))
+
+
+def test_float32_dW_of_long_rows(fr):
+    """Hidden rows of 2^20 elements, 16416 tokens: the scaled rows are 2^32 + 2^23 pieces of 16 bytes,
+    and each of them reaches dW.  1e-3: a logit sums 2^20 float32 products of which the partial sums
+    are around 1 (2^20 roundings of 2^-25, as a random walk 3e-5), and exp turns that into a relative
+    error."""
+    T, R, d, V = 16416, 32, 1 << 20, 8
+    g = torch.Generator(device=DEV).manual_seed(3)
+    H = torch.randn(R, d, device=DEV, generator=g)
+    W = torch.randn(V, d, device=DEV, generator=g) / d ** 0.5
+    y = torch.randint(0, V, (R,), device=DEV, dtype=torch.int32, generator=g)
+    z = H.double() @ W.double().T
+    lse = torch.logsumexp(z, 1)
+    logp = z.gather(1, y.long()[:, None])[:, 0] - lse
+    rows = _rows(R, T)
+    off = torch.tensor([0, T // 2, T])
+    adv = torch.tensor([1.0, -0.5], device=DEV)
+    print(f"[large] float32 dW T={T} d={d}", flush=True)
+    call = fr.policy_loss_fwd_bwd(H, W, y, logp.float(), off.to(DEV), off, adv, row_index=rows, T=T,
+                                  need_dhidden=False)
+    torch.cuda.synchronize()
+    # old = current: every ratio is 1 (inside the clip range), g_t = -A / (2 L)
+    gt = torch.where(torch.arange(T, device=DEV) < T // 2, adv[0], adv[1]).double() * (-1.0 / T)
+    gr = torch.zeros(R, dtype=torch.float64, device=DEV).index_add_(0, rows.long(), gt)
+    dZ = -gr[:, None] * torch.exp(z - lse[:, None])
+    dZ[torch.arange(R, device=DEV), y.long()] += gr
+    for a in range(0, d, 1 << 17):
+        want = dZ.T @ H[:, a:a + (1 << 17)].double()
+        assert (call.dW[:, a:a + (1 << 17)].double() - want).norm() < 1e-3 * want.norm(), a
