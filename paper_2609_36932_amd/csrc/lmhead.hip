@@ -156,7 +156,9 @@ constexpr int kSmemBytes = (2 + 3) * kStage * 2;          // 160 KB: all of a co
 __device__ __forceinline__ uint16_t* free_stage(uint16_t* smem, int nk) {
   return smem + (nk & 1) * kStage;
 }
-template <int MODE, int NJ = 4>
+// Off, Step: a lane's offset and a K tile's, in bytes; of 64 bits for rows of kMaxLd elements or more
+// (lm_wide_kernel).
+template <int MODE, int NJ = 4, typename Off = uint32_t, typename Step = int>
 __device__ __forceinline__ void mainloop_bf16(const GemmParams& p, int m0, int n0,
                                               f32x4_t (&acc)[8][NJ], uint16_t* smem, int kt0 = 0,
                                               int nkt = 0) {
@@ -174,22 +176,22 @@ __device__ __forceinline__ void mainloop_bf16(const GemmParams& p, int m0, int n
   uint16_t* const sB = smem + 2 * kStage;
   const int K = p.K;
   const int nk = DHT ? nkt : (K + BK - 1) / BK;
-  // ---- loads.  Addresses are a uniform base (the first of a load's rows) plus a 32-bit lane offset
+  // ---- loads.  Addresses are a uniform base (the first of a load's rows) plus a lane offset (32 bits)
   // in bytes; gathered rows take 64-bit lane addresses.  Rows past the edge load a valid one (their
   // results are never stored).
   const int lrow = lane >> 3;
   const int gch = (lane & 7) ^ (lrow >> 1);  // k-chunk of an even load; of an odd one gch ^ 4
   const char* abase[4];
-  uint32_t aoff[4];
+  Off aoff[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int r0 = min(m0 + wave * 32 + j * 8, p.M - 1);
     abase[j] = Ag + 2 * int64_t(r0) * p.lda;
-    aoff[j] = 2u * uint32_t(min(r0 + lrow, p.M - 1) - r0) * uint32_t(p.lda);
+    aoff[j] = 2u * Off(min(r0 + lrow, p.M - 1) - r0) * Off(p.lda);
     if constexpr (MODE != MODE_FWD) aoff[j] += 16u * uint32_t(gch ^ ((j & 1) << 2));
   }
   const char* bbase[NJ];  // uniform (not gathered) or lane address
-  uint32_t boff[NJ];
+  Off boff[NJ];
   const int bodd = (NJ & 1) ? (wave & 1) : 0;  // load j of B: an odd one if j + bodd is
   uint32_t bhi = 0;
   if constexpr (BKM) {
@@ -223,7 +225,7 @@ __device__ __forceinline__ void mainloop_bf16(const GemmParams& p, int m0, int n
     for (int j = 0; j < NJ; ++j) {
       const int r0 = min(n0 + (wave * NJ + j) * 8, p.N - 1);
       bbase[j] = Bg + 2 * int64_t(r0) * p.ldb;
-      boff[j] = 2u * uint32_t(min(r0 + lrow, p.N - 1) - r0) * uint32_t(p.ldb) +
+      boff[j] = 2u * Off(min(r0 + lrow, p.N - 1) - r0) * Off(p.ldb) +
                 16u * uint32_t(gch ^ ((j & 1) << 2));
     }
   }
@@ -234,10 +236,11 @@ __device__ __forceinline__ void mainloop_bf16(const GemmParams& p, int m0, int n
     uint16_t* d = sA + st * kStage + wave * 32 * BK;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      uint32_t o = aoff[j];
+      Off o = aoff[j];
       if constexpr (MODE == MODE_FWD) o += uint32_t(chunk(kt, j & 1));
       const char* base = abase[j] + int64_t(DHT ? kt + kt0 : kt) * (2 * BK);
-      __builtin_amdgcn_global_load_lds(base + o, (lds_void_t*)(d + j * 8 * BK), 16, 0, 0);
+      const char* src = base + o;
+      __builtin_amdgcn_global_load_lds(src, (lds_void_t*)(d + j * 8 * BK), 16, 0, 0);
     }
   };
   auto issue_b = [&](int kt, int st) {
@@ -247,14 +250,14 @@ __device__ __forceinline__ void mainloop_bf16(const GemmParams& p, int m0, int n
       const char* src;
       if constexpr (BKM) {
         int k = (DHT ? kt + kt0 : kt) * BK + wave * 8 + 2 * j;
-        uint32_t o = boff[j];
+        Off o = boff[j];
         if constexpr (DHT) {  // vocab rows past the end load the last one (their exp-logits are 0)
           if (k + 1 < p.Vreal) o += bhi;
           k = min(k, p.Vreal - 1);
         }
         src = bbase[j] + 2 * int64_t(k) * p.ldb + o;
       } else if constexpr (GATHER) {
-        src = bbase[j] + (kt * (2 * BK) + chunk(kt, (j + bodd) & 1));
+        src = bbase[j] + (Step(kt) * (2 * BK) + chunk(kt, (j + bodd) & 1));
       } else {
         src = bbase[j] + int64_t(kt) * (2 * BK) + boff[j];
       }
@@ -701,14 +704,14 @@ __device__ __forceinline__ void dwt_epilogue_bf16(const GemmParams& p, int m0, i
 }
 
 // one logits tile of 256 vocab rows x 64 NJ tokens
-template <int NJ>
+template <int NJ, typename Off = uint32_t, typename Step = int>
 __device__ __forceinline__ void fwd_tile(const GemmParams& p, int mb, int n0, uint16_t* smem) {
   f32x4_t acc[8][NJ];
 #pragma unroll
   for (int i = 0; i < 8; ++i)
 #pragma unroll
     for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-  mainloop_bf16<MODE_FWD, NJ>(p, mb * kBM, n0, acc, smem);
+  mainloop_bf16<MODE_FWD, NJ, Off, Step>(p, mb * kBM, n0, acc, smem);
   fwd_epilogue_bf16<NJ>(p, mb * kBM, n0, mb, acc, smem);
 }
 
@@ -1154,6 +1157,31 @@ void lm_redo_kernel(const GemmParams p) {
   }
 }
 
+// The bf16 GEMMs over rows of kMaxLd elements or more, one 256 x 256 tile a block: logits (also their
+// second evaluation), dhidden from W^T or from W itself (K whole), transposed dW.
+template <int MODE>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void lm_wide_kernel(const GemmParams p) {
+  __shared__ __attribute__((aligned(1024))) char smem_raw[kSmemBytes];
+  uint16_t* smem = reinterpret_cast<uint16_t*>(smem_raw);
+  int mb, nb;
+  tile_coords<MODE>(mb, nb, p.nmb, p.nnb, blockIdx.x, p.group);
+  if constexpr (MODE == MODE_FWD) {
+    if (p.store_e == 2 && (p.redo_any[0] == 0 || p.redo_blk[nb] == 0)) return;
+    fwd_tile<4, uint64_t, int64_t>(p, mb, nb * kBN, smem);
+  } else {
+    const int m0 = mb * kBM, n0 = nb * kBN;
+    f32x4_t acc[8][4];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    mainloop_bf16<MODE, 4, uint64_t, int64_t>(p, m0, n0, acc, smem, 0, p.K / 64);
+    if constexpr (MODE == MODE_DWT) dwt_epilogue_bf16(p, m0, n0, acc);
+    else dh_epilogue_bf16(p, m0, n0, acc);
+  }
+}
+
 // ------------------------------------------------------------------ small kernels
 
 // s_t = 0, labels of the slab, validity; also clears the slab's flags (at most Tc + 1 of them) and,
@@ -1568,9 +1596,30 @@ static int tile_group(int mode, int32_t K, int32_t nnb, bool store_e = false) {
   return 4;
 }
 
-// Longest rows of the bf16 GEMMs' operands, in elements: a lane's offset inside 8 rows is 32 bits of
-// bytes (a row of this length is half a GiB)
+// Rows of the bf16 GEMMs' row-by-row operands from which lm_wide_kernel runs, in elements: a lane's
+// offset inside 8 rows is 32 bits of bytes elsewhere (a row of this length is half a GiB; K-major
+// operands have no such limit)
 constexpr int64_t kMaxLd = int64_t(1) << 28;
+
+template <int MODE>
+static bool wide_rows(const GemmParams& p) {
+  return p.lda >= kMaxLd || (MODE == MODE_DH && p.ldb >= kMaxLd);
+}
+
+template <int MODE>
+static int launch_wide(GemmParams p, int kind, double flops, hipStream_t stream) {
+  p.nmb = int((p.M + kBM - 1) / kBM);
+  p.nnb = int((p.N + kBN - 1) / kBN);
+  p.group = tile_group(MODE == MODE_DHT ? int(MODE_DH) : MODE, p.K, p.nnb, p.store_e != 0);
+  p.narrow = p.tail = 0;
+  const int64_t nblk = int64_t(p.nmb) * p.nnb;
+  if (nblk == 0) return FASTRL_OK;
+  FR_CHECK_ARG(MODE == MODE_FWD || p.K % 64 == 0, FASTRL_ERR_UNSUPPORTED, "GEMM: unsupported shape");
+  ProfScope prof(kind, stream, flops);
+  hipLaunchKernelGGL(lm_wide_kernel<MODE>, dim3(unsigned(nblk)), dim3(kThreads), 0, stream, p);
+  FR_LAUNCHED();
+  return FASTRL_OK;
+}
 
 // Tiles of a logits GEMM; returns the blocks.  The last N % 256 tokens take a column of narrow tiles
 // (64, 128 or 192 wide) in place of whole ones that are mostly padding.  Without those, a last
@@ -1640,6 +1689,7 @@ template <typename T, int MODE>
 static int launch_gemm(GemmParams p, int kind, double flops, hipStream_t stream) {
   if constexpr (sizeof(T) == 4) return launch_f32<MODE>(p, kind, flops, stream);
   else {
+  if (wide_rows<MODE>(p)) return launch_wide<MODE>(p, kind, flops, stream);
   int64_t nblk;
   if constexpr (MODE == MODE_FWD) {
     nblk = fwd_tiles(p);
@@ -1650,7 +1700,6 @@ static int launch_gemm(GemmParams p, int kind, double flops, hipStream_t stream)
     nblk = int64_t(p.nmb) * p.nnb;
   }
   if (nblk == 0) return FASTRL_OK;
-  FR_CHECK_ARG(p.lda < kMaxLd && p.ldb < kMaxLd, FASTRL_ERR_UNSUPPORTED, "GEMM: rows too long");
   // transposed dW: whole 64-k tiles, whole 256-column tiles of the K-major E, 16-byte dW rows
   FR_CHECK_ARG(MODE != MODE_DWT || (p.K % 64 == 0 && p.ldb >= int64_t(p.nnb) * kBN &&
                                     p.ldb % 8 == 0 && p.d % 4 == 0 && p.M == p.d),
@@ -1673,8 +1722,6 @@ static int launch_bwd(GemmParams q, GemmParams r, double flops, hipStream_t stre
   const int64_t nh = int64_t(q.nmb) * q.nnb, nw = int64_t(r.nmb) * r.nnb;
   if (nh + nw == 0) return FASTRL_OK;
   FR_CHECK_ARG(nh + nw < (int64_t(1) << 31), FASTRL_ERR_UNSUPPORTED, "backward GEMMs: grid too large");
-  FR_CHECK_ARG(q.lda < kMaxLd && q.ldb < kMaxLd && r.lda < kMaxLd && r.ldb < kMaxLd,
-               FASTRL_ERR_UNSUPPORTED, "GEMM: rows too long");
   FR_CHECK_ARG(r.K % 64 == 0 && r.ldb >= int64_t(r.nnb) * kBN && r.ldb % 8 == 0 && r.d % 4 == 0 &&
                    r.M == r.d,
                FASTRL_ERR_UNSUPPORTED, "transposed dW GEMM: unsupported shape");
@@ -1712,6 +1759,7 @@ static bool direct_dh(const fastrl_loss_args& a) {
 // 1975 tokens [5068], .., 5141; 8192 [19622], 19838, 19984, 21080, 21651.
 static int dh_ksplit(int32_t Tc, int32_t d, int32_t V, int32_t dtype, bool dw) {
   if (dtype == FASTRL_F32) return f32_ksplit(Tc, d, V);
+  if (rup(V, kBM) >= kMaxLd) return 1;  // lm_wide_kernel
   const double nt = double((Tc + kBM - 1) / kBM) * double((d + kBN - 1) / kBN);
   const double nk = double((V + 63) / 64);
   const double wt = dw ? double((V + kBN - 1) / kBN) * double((d + kBM - 1) / kBM) : 0.0;
@@ -1746,8 +1794,6 @@ static int launch_bwd_direct(GemmParams q, GemmParams r, bool dw, double flops,
   const int64_t nh = int64_t(q.nmb) * q.nnb * q.ksplit, nw = int64_t(r.nmb) * r.nnb;
   if (nh + nw == 0) return FASTRL_OK;
   FR_CHECK_ARG(nh + nw < (int64_t(1) << 31), FASTRL_ERR_UNSUPPORTED, "backward GEMMs: grid too large");
-  FR_CHECK_ARG(q.lda < kMaxLd && q.ldb < kMaxLd && r.lda < kMaxLd && r.ldb < kMaxLd,
-               FASTRL_ERR_UNSUPPORTED, "GEMM: rows too long");
   FR_CHECK_ARG(q.K % 64 == 0 && q.K <= q.lda && q.ldb % 8 == 0 && q.N >= 8 && q.ksplit >= 1 &&
                    q.ksplit * 64 <= q.K && (q.ksplit == 1 || q.part),
                FASTRL_ERR_UNSUPPORTED, "direct dhidden GEMM: unsupported shape");
@@ -1768,6 +1814,7 @@ template <typename T>
 static int launch_redo(GemmParams p, hipStream_t stream) {
   p.store_e = 2;
   if constexpr (sizeof(T) != 2) return launch_gemm<T, MODE_FWD>(p, -1, 0.0, stream);
+  if (wide_rows<MODE_FWD>(p)) return launch_wide<MODE_FWD>(p, -1, 0.0, stream);
   p.nmb = int((p.M + kBM - 1) / kBM);
   p.nnb = int((p.N + kBN - 1) / kBN);
   p.group = tile_group(MODE_FWD, p.K, p.nnb, true);
@@ -2153,8 +2200,11 @@ static int policy_loss_impl(const fastrl_loss_args& a, hipStream_t stream) {
       }
     }
     // bf16 with both gradients: the two GEMMs run as one launch (after dW's inputs are ready)
-    const bool fused = dh && dw && sizeof(T) == 2;
-    if (dh && !dw && direct && sizeof(T) == 2)
+    const bool wide = sizeof(T) == 2 && (Vpad >= kMaxLd || (dw && tcp >= kMaxLd));
+    const bool fused = dh && dw && sizeof(T) == 2 && !wide;
+    if (dh && wide && direct)
+      FR_TRY(launch_wide<MODE_DHT>(q, FASTRL_K_DHIDDEN, 2.0 * double(Tc) * d * V, stream));
+    else if (dh && !dw && direct && sizeof(T) == 2)
       FR_TRY(launch_bwd_direct(q, GemmParams{}, false, 2.0 * double(Tc) * d * V, stream));
     else if (dh && !fused)
       FR_TRY((launch_gemm<T, MODE_DH>(q, FASTRL_K_DHIDDEN, 2.0 * double(Tc) * d * V, stream)));

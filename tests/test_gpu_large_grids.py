@@ -1,5 +1,6 @@
-"""GPU calls whose kernels need more threads than one launch can hold (2^32) at the tile and block
-sizes in use, against float64 on the few distinct rows that they gather."""
+"""GPU calls past the limits of 32 bits: kernels that need more threads than one launch can hold (2^32)
+at the tile and block sizes in use, and bf16 rows of more than 2^28 elements; against float64 on the few
+distinct rows or entries that they hold."""
 import pytest
 import torch
 
@@ -95,3 +96,71 @@ def test_float32_dW_of_long_rows(fr):
     for a in range(0, d, 1 << 17):
         want = dZ.T @ H[:, a:a + (1 << 17)].double()
         assert (call.dW[:, a:a + (1 << 17)].double() - want).norm() < 1e-3 * want.norm(), a
+
+
+def _sparse(rows, n, seed, value):
+    """bf16 [rows, n], zero but for the same ~400 columns in every row: some of each end and middle"""
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    cols = torch.unique(torch.cat([torch.arange(72, device=DEV), n - 1 - torch.arange(72, device=DEV),
+                                   torch.randint(0, n, (256,), device=DEV, generator=g)]))
+    x = torch.zeros((rows, n), dtype=torch.bfloat16, device=DEV)
+    part = (value * torch.randn(rows, len(cols), device=DEV, generator=g)).bfloat16()
+    x[:, cols] = part
+    return x, cols, part
+
+
+def test_bf16_long_rows(fr):
+    """d = 320 M: the eighth row of a load starts past 32 bits of bytes.  The logits' few nonzero terms
+    sum to float32 accuracy (2e-5 at values around 1)."""
+    d, V, T = 320_000_000, 9, 3
+    print(f"[large] bf16 d={d}", flush=True)
+    W, cols, wp = _sparse(V, d, 4, 0.05)
+    H, hcols, hp = _sparse(T, d, 4, 1.0)
+    assert torch.equal(cols, hcols)
+    y = torch.tensor([8, 0, 7], dtype=torch.int32, device=DEV)
+    lp, ls = fr.token_logprob(H, W, y)
+    torch.cuda.synchronize()
+    z = hp.double() @ wp.double().T
+    lse = torch.logsumexp(z, 1)
+    assert (ls.double() - lse).abs().max() < 2e-5
+    assert (lp.double() - (z.gather(1, y.long()[:, None])[:, 0] - lse)).abs().max() < 2e-5
+
+
+def test_bf16_backward_over_long_rows(fr):
+    """V = 307 M: the exp-logit rows that dhidden reads, ten of them, start past 32 bits of bytes within
+    a load, and dW spans 2^20 vocabulary blocks.  W is zero but for 96 rows, so that the oracle is short.
+    1e-2 is the bar of bf16 gradients."""
+    d, V, T = 8, 307_000_000, 10
+    if torch.cuda.mem_get_info()[0] < 220 << 30:
+        pytest.skip("needs 190 GB")
+    print(f"[large] bf16 V={V}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(5)
+    rows = torch.unique(torch.cat([torch.arange(16, device=DEV), V - 1 - torch.arange(16, device=DEV),
+                                   torch.randint(0, V, (64,), device=DEV, generator=g)]))
+    W = torch.zeros((V, d), dtype=torch.bfloat16, device=DEV)
+    wp = torch.randn(len(rows), d, device=DEV, generator=g).bfloat16()
+    W[rows] = wp
+    H = torch.randn(T, d, device=DEV, generator=g).bfloat16()
+    pick = torch.randint(0, len(rows), (T,), device=DEV, generator=g)
+    pick[0], pick[T - 1] = 0, len(rows) - 1
+    y = rows[pick].int()
+    z = H.double() @ wp.double().T
+    lse = torch.log((V - len(rows)) + torch.exp(z).sum(1))
+    logp = z.gather(1, pick[:, None])[:, 0] - lse
+    off = torch.tensor([0, 4, T])
+    adv = torch.tensor([1.0, -0.5], device=DEV)
+    call = fr.policy_loss_fwd_bwd(H, W, y, logp.float(), off.to(DEV), off, adv)
+    torch.cuda.synchronize()
+    assert (call.logp.double() - logp).abs().max() < 2e-5
+    seq = (torch.arange(T, device=DEV) >= 4).long()
+    gt = -adv.double()[seq] / (2.0 * torch.tensor([4.0, 6.0], device=DEV).double()[seq])
+    dZ = -gt[:, None] * torch.exp(z - lse[:, None])
+    dZ[torch.arange(T, device=DEV), pick] += gt
+    dH, dWp = dZ @ wp.double(), dZ.T @ H.double()
+    assert (call.dhidden.double() - dH).norm() < 1e-2 * dH.norm()
+    assert (call.dW[rows].double() - dWp).norm() < 1e-2 * dWp.norm()
+    rest = (-(gt * torch.exp(-lse))[:, None] * H.double()).sum(0)  # every row whose logits are 0
+    call.dW[rows] = rest.float()
+    for a in range(0, V, 1 << 24):
+        err = (call.dW[a:a + (1 << 24)] - rest.float()).abs().max()
+        assert err < 1e-2 * rest.abs().max(), (a, float(err))
