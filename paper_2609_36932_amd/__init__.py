@@ -144,9 +144,15 @@ def _arg(t, dtype, name):
     return t.data_ptr()
 
 
+# handle of a device's current stream without building a Stream object (3 us a call); not a public
+# function, so a torch without it takes the public way
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
-    # torch.cuda.current_stream().cuda_stream without building a Stream object (3 us a call)
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _workspace(nbytes, device):

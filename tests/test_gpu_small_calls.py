@@ -196,3 +196,13 @@ def test_shifted_rows_in_one_slab(fr, dtype, T, big, offs):
     assert abs(call.loss.item() - loss.item()) <= 1e-3 * abs(loss.item())
     tol = 1e-2 if dtype == torch.bfloat16 else 1e-3
     assert _rel(call.dhidden, dH) < tol and _rel(call.dW, dW) < tol
+
+
+def test_launches_follow_the_current_stream(fr):
+    """The handle passed to the library is torch's current stream, on the default one and inside a
+    stream context."""
+    assert fr._stream() == torch.cuda.current_stream().cuda_stream
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        assert fr._stream() == side.cuda_stream == torch.cuda.current_stream().cuda_stream
+    assert fr._stream() == torch.cuda.current_stream().cuda_stream

@@ -235,3 +235,18 @@ def test_prune_workspace_follows_the_rollouts(fr):
     N, T = 80000, 1 << 20
     tight, loose = f(40000, N, T, 4, 1), f(40000, N, T, 256, 1)
     assert 0 < tight <= loose <= tight + 24 * (N + 1) + 256
+
+
+def test_stream_handle_with_and_without_torchs_raw_call(fr, monkeypatch):
+    """The launches' stream is the current device's current one, also on a torch that has no call for
+    the raw handle."""
+    import types
+
+    import torch
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(fr, "_raw_stream", lambda device: 1000 + device)
+    assert fr._stream() == 1003
+    monkeypatch.setattr(fr, "_raw_stream", None)
+    monkeypatch.setattr(torch.cuda, "current_stream",
+                        lambda: types.SimpleNamespace(cuda_stream=77))
+    assert fr._stream() == 77
