@@ -718,8 +718,11 @@ __device__ __forceinline__ void fwd_tile(const GemmParams& p, int mb, int n0, ui
 // The tiles of a logits GEMM (fwd_tiles), in tile order over p.nnb columns: the last `tail` are cut
 // into 64- or 128-token pieces; with p.narrow the last column is 64 p.narrow tokens wide.  Up to
 // kMixCols columns the narrow tiles run among the others of their vocab block, which share its rows
-// of W (read again from HBM otherwise: 300 tokens at 7B 504 -> 398 us, 2309 tokens 2180 -> 2098);
-// beyond, they run last and fill the final wave (20600 tokens: 17.2 ms among the others, 16.7 last).
+// of W (read again from HBM otherwise); beyond, they run last and fill the final wave.  token_logprob
+// with 80 tokens in the narrow column, us, last / among the others: d = 1536 336 tokens 220 / 185, 2128
+// 831 / 810, 3152 1194 / 1172, 4176 1539 / 1536, 12368 4381 / 4407, 20560 7270 / 7336; d = 3584 336
+// 452 / 395, 2128 1770 / 1740, 2640 2173 / 2160, 3152 (13 columns) 2557 / 2564, 5200 4068 / 4157, 20560
+// 15630 / 16120.
 constexpr int kMixCols = 12;
 __device__ __forceinline__ void fwd_block(const GemmParams& p, int b, uint16_t* smem) {
   const bool own = p.narrow && p.nnb > kMixCols;  // narrow column after all others
@@ -1082,7 +1085,7 @@ void lm_bwd_kernel(const GemmParams q, const GemmParams r) {
 
 // The same two GEMMs for calls of few tokens (direct_dh): dhidden reads W itself, K-major, with
 // K cut into q.ksplit parts.  With few tokens there are few dhidden tiles but each has the whole
-// vocabulary as K: one block per tile is a chain of V / 64 steps of ~1.7 us on a handful of
+// vocabulary as K: one block per tile is a chain of V / 64 steps of ~1.2 us on a handful of
 // compute units (12 of 256 at 507 tokens, d = 1536).  A part's float32 sums go to q.part and
 // dh_reduce_kernel adds them in part order.
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
@@ -1624,9 +1627,9 @@ static int launch_wide(GemmParams p, int kind, double flops, hipStream_t stream)
 // Tiles of a logits GEMM; returns the blocks.  The last N % 256 tokens take a column of narrow tiles
 // (64, 128 or 192 wide) in place of whole ones that are mostly padding.  Without those, a last
 // wave of at most 128 (64) whole tiles on the 256 compute units is cut into 2 (4) pieces per tile,
-// which run at once.  token_logprob, us, whole tiles only -> so (and with the merge in 32 slices):
-// d = 1536 (V = 151936) 16 tokens 207 -> 121, 193 216 -> 147, 300 289 -> 198, 1200 557 -> 492;
-// d = 3584 (V = 152064) 16 348 -> 245, 300 520 -> 398, 2309 2235 -> 2097, 33733 27819 -> 27372.
+// which run at once.  token_logprob, us, whole tiles only -> so: d = 1536 (V = 151936) 16 tokens
+// 141 -> 104, 193 145 -> 137, 300 215 -> 174, 1200 488 -> 473; d = 3584 (V = 152064) 16 284 -> 210, 300
+// 442 -> 369, 2309 1997 -> 1927, 33733 level.
 static int64_t fwd_tiles(GemmParams& p) {
   p.nmb = int((p.M + kBM - 1) / kBM);
   p.nnb = int((p.N + kBN - 1) / kBN);
@@ -1731,18 +1734,23 @@ static int launch_bwd(GemmParams q, GemmParams r, double flops, hipStream_t stre
   return FASTRL_OK;
 }
 
-// Calls of at most kDirectTokens tokens read W itself in dhidden (MODE_DHT): the transposed copy
-// of W, built per call (0.39 ms at 7B, 0.16 ms at d = 1536), costs more there than the
-// transposing LDS reads do, and K can be cut.  Measured, transposed copy -> W itself, us a call
-// with both gradients: d = 1536 (V = 151936) 507 tokens 4373 -> 1381, 2048 5165 -> 2764, 8192
-// 9837 -> 9749, 16384 18787 -> 18724; d = 3584 (V = 152064) 2048 6607 -> 6121, 8192 21271 ->
-// 20986, 16384 41628 -> 40899, 32768 82320 -> 83281, 131072 330.4 -> 333.6 ms; d = 2048
-// (V = 100000) 27000 27029 -> 27136.
-constexpr int64_t kDirectTokens = 20480;
+// Calls of few tokens read W itself in dhidden (MODE_DHT): the transposed copy of W, built per call
+// (0.39 ms at 7B, 0.16 ms at d = 1536), costs more there than the transposing LDS reads do, and K can
+// be cut.  Beside dW tiles, whose traffic slows those reads, up to kDirectTokens tokens; dhidden alone
+// up to kDirectTokensAlone.  Measured, transposed copy / W itself, us a call: both gradients,
+// d = 1536 (V = 151936) 1024 tokens 3608 / 1364, 2048 4083 / 2407, 4096 5068 / 4634, 6144 6744 / 6816,
+// 8192 8788 / 8863, 16384 17221 / 17701; d = 3584 (V = 152064) 2048 5717 / 5364, 4096 10043 / 9970,
+// 8192 19672 / 19735, 16384 39265 / 39623, 20480 49089 / 50019, 32768 76808 / 80305; d = 896
+// (V = 151936) 4096 4190 / 3138, 8192 5990 / 5992, 16384 11704 / 11989; d = 2048 (V = 100000) 4096
+// 3948 / 3899, 8192 7569 / 7626, 16384 14880 / 15244.  dhidden alone, d = 1536 8192 6313 / 6171, 16384
+// 12803 / 12167, 32768 23672 / 24838; d = 3584 8192 13275 / 13357, 16384 27377 / 26917, 32768 52193 /
+// 54763.
+constexpr int64_t kDirectTokens = 6144, kDirectTokensAlone = 20480;
 
 // (float32 dhidden always reads W itself)
 static bool direct_dh(const fastrl_loss_args& a) {
-  return a.dhidden != nullptr && (a.dtype == FASTRL_F32 || a.T <= kDirectTokens);
+  return a.dhidden != nullptr &&
+         (a.dtype == FASTRL_F32 || a.T <= (a.dW ? kDirectTokens : kDirectTokensAlone));
 }
 
 // Parts of K for the dhidden tiles of a Tc-token slab: the count whose estimated time is least,

@@ -206,3 +206,21 @@ def test_launches_follow_the_current_stream(fr):
     with torch.cuda.stream(side):
         assert fr._stream() == side.cuda_stream == torch.cuda.current_stream().cuda_stream
     assert fr._stream() == torch.cuda.current_stream().cuda_stream
+
+
+@pytest.mark.parametrize("T, need_dW", [(6144, True), (6145, True), (20480, False), (20481, False)])
+def test_dhidden_on_both_sides_of_the_transposed_copy(fr, T, need_dW):
+    """The last call that reads W itself and the first that transposes it, beside dW and alone (1e-2:
+    the bar of bf16 gradients)."""
+    d, V = 40, 330
+    H, W, y, z, lse, logp, old = _problem(T, d, V, T)
+    off = np.asarray([0, T // 3, T // 3 + T // 2, T], dtype=np.int64)
+    adv = torch.linspace(-1.0, 1.5, 3)
+    _, dH, dW = _reference(H, W, y, z, lse, logp, old, off, adv)
+    call = fr.policy_loss_fwd_bwd(
+        H.to(DEV), W.to(DEV), y.to(DEV), old.to(DEV), torch.from_numpy(off).to(DEV),
+        torch.from_numpy(off), adv.to(DEV), need_dW=need_dW)
+    torch.cuda.synchronize()
+    assert _rel(call.dhidden, dH) < 1e-2
+    if need_dW:
+        assert _rel(call.dW, dW) < 1e-2
