@@ -1,7 +1,7 @@
 """GPU parity on the edges of what the C ABI accepts: groups of 65 to 256 rollouts (the
 selection and pair kernels then loop past one wavefront), zero-length trajectories (through
-pruning and the whole loss), a trajectory of max_len = 16384 tokens (a 128 KB n-gram sort in
-LDS), trigrams at the largest vocabulary (V = 2^21 - 1: three 21-bit ids fill 63 bits of a
+pruning and the whole loss), a trajectory of max_len = 16384 tokens (the largest hash set, 156 KB
+of LDS), trigrams at the largest vocabulary (V = 2^21 - 1: three 21-bit ids fill 63 bits of a
 key), and a loss call whose kept sequences are all empty over a NaN-filled workspace.
 Pruning results are compared bit for bit with the oracle."""
 

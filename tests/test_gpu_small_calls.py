@@ -224,3 +224,44 @@ def test_dhidden_on_both_sides_of_the_transposed_copy(fr, T, need_dW):
     assert _rel(call.dhidden, dH) < 1e-2
     if need_dW:
         assert _rel(call.dW, dW) < 1e-2
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("V", [300, 20011])  # 2 vocabulary blocks (30 of the merge's slices empty); 79
+def test_rows_that_are_not_finite_or_very_negative(fr, dtype, V):
+    """NaN and infinite hidden rows give NaN or infinite log-probs and leave their neighbours alone, in
+    token_logprob and in a loss call with entropy and dhidden; logits around -3e4 over whole vocabulary
+    blocks count for nothing.  Tolerances as in test_logits_tiles."""
+    T, d = 40, 72
+    H, W, y, *_ = _problem(T, d, V, V, dtype)
+    H[:, 0] = 1.0
+    W[:, 0] = 0.0
+    W[256:290, 0] = -3e4                    # the second block's rows (all of it but a few at V = 300)
+    if V > 512:
+        W[256:512, 0] = -3e4
+        W[-1, 0] = -3e4
+    y[:] = torch.arange(T, dtype=torch.int32) * 6
+    z = H.double() @ W.double().T
+    lse = torch.logsumexp(z, 1)
+    logp = z.gather(1, y.long()[:, None])[:, 0] - lse
+    old = (logp + 0.01).float()
+    off = np.asarray([0, 10, T], dtype=np.int64)
+    adv = torch.tensor([1.0, -0.5])
+    _, dH, _ = _reference(H, W, y, z, lse, logp, old, off, adv)
+    ent = lse - (torch.exp(z - lse[:, None]) * z).sum(1)
+    bad = torch.zeros(T, dtype=torch.bool)
+    bad[[3, 11, 39]] = True
+    H[3, 5] = float("nan")
+    H[11, 7] = float("inf")
+    H[39, 9] = -float("inf")
+    args = (H.to(DEV), W.to(DEV), y.to(DEV))
+    lp, ls = fr.token_logprob(*args)
+    call = fr.policy_loss_fwd_bwd(*args, old.to(DEV), torch.from_numpy(off).to(DEV),
+                                  torch.from_numpy(off), adv.to(DEV), need_dW=False,
+                                  need_entropy=True)
+    torch.cuda.synchronize()
+    for got, want in ((lp, logp), (call.logp, logp), (ls, lse), (call.lse, lse), (call.entropy, ent)):
+        got = got.double().cpu()
+        assert not torch.isfinite(got[bad]).any()
+        assert (got[~bad] - want[~bad]).abs().max() < 2e-5
+    assert _rel(call.dhidden[~bad.to(DEV)], dH[~bad]) < 1e-2
