@@ -144,15 +144,16 @@ def _arg(t, dtype, name):
     return t.data_ptr()
 
 
-# handle of a device's current stream without building a Stream object (3 us a call); not a public
-# function, so a torch without it takes the public way
+# handle of a device's current stream without building a Stream object (3 us a call); not public
+# functions, so a torch without them takes the public way
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
 
 
 def _stream():
-    if _raw_stream is None:
+    if _raw_stream is None or _raw_device is None:
         return torch.cuda.current_stream().cuda_stream
-    return _raw_stream(torch.cuda.current_device())
+    return _raw_stream(_raw_device())
 
 
 def _workspace(nbytes, device):

@@ -243,10 +243,13 @@ def test_stream_handle_with_and_without_torchs_raw_call(fr, monkeypatch):
     import types
 
     import torch
-    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream",
+                        lambda: types.SimpleNamespace(cuda_stream=77))
+    monkeypatch.setattr(fr, "_raw_device", lambda: 3)
     monkeypatch.setattr(fr, "_raw_stream", lambda device: 1000 + device)
     assert fr._stream() == 1003
     monkeypatch.setattr(fr, "_raw_stream", None)
-    monkeypatch.setattr(torch.cuda, "current_stream",
-                        lambda: types.SimpleNamespace(cuda_stream=77))
+    assert fr._stream() == 77
+    monkeypatch.setattr(fr, "_raw_stream", lambda device: 1000 + device)
+    monkeypatch.setattr(fr, "_raw_device", None)
     assert fr._stream() == 77
