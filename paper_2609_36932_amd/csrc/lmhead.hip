@@ -1382,17 +1382,18 @@ __global__ __launch_bounds__(kSumThreads) void loss_final_kernel(const LossParam
   }
 }
 
-// sum of x[0], x[ld], .. x[(n - 1) ld] in order, 16 loads in flight.  (One after the other, the 594 of
-// a row at V = 151936 took 0.2-0.4 ms of a loss call whose rows are all shifted: 588 tokens, d = 1536,
-// 1519 us, 1338 so; 2048 tokens of one sequence, d = 3584, 7415 us, 7000 so.)
+// sum of x[0], x[ld], .. x[(n - 1) ld] in order, 8 loads in flight.  (One after the other, the 594 of a
+// row at V = 151936 took 0.2-0.4 ms of a loss call whose rows are all shifted: 588 tokens, d = 1536,
+// 1519 us, 1330 so; 2048 tokens of one sequence, d = 3584, 7415 us, 7010 so.  16 gain 1% more there,
+// but their code costs every call 0.5 us.)
 __device__ __forceinline__ double column_sum_d(const float* x, int64_t ld, int n) {
   double s = 0.0;
-  for (int m = 0; m < n; m += 16) {
-    float v[16];
+  for (int m = 0; m < n; m += 8) {
+    float v[8];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) v[u] = x[int64_t(min(m + u, n - 1)) * ld];
+    for (int u = 0; u < 8; ++u) v[u] = x[int64_t(min(m + u, n - 1)) * ld];
 #pragma unroll
-    for (int u = 0; u < 16; ++u)
+    for (int u = 0; u < 8; ++u)
       if (m + u < n) s += double(v[u]);
   }
   return s;
@@ -1423,8 +1424,12 @@ __global__ __launch_bounds__(kSumThreads) void loss_kernel(const LossParams p) {
       const int64_t tl = t - p.row_base;
       const float s_t = p.shift[tl];
       if (s_t == 0.0f) continue;
-      const double S = column_sum_d(p.psum + tl, p.ldp, p.nmb);
-      const double Z = p.psz ? column_sum_d(p.psz + tl, p.ldp, p.nmb) : 0.0;
+      double S = 0.0, Z = 0.0;  // (one loop's code for both: it lies in every call's way)
+#pragma clang loop unroll(disable)
+      for (int k = p.psz ? 0 : 1; k < 2; ++k) {
+        Z = S;
+        S = column_sum_d((k == 0 ? p.psz : p.psum) + tl, p.ldp, p.nmb);
+      }
       const float l = s_t + __logf(float(S));
       p.lse[t] = l;
       p.logp[t] = p.yslab[tl] >= 0 ? p.zlab[tl] - l : __int_as_float(0x7fc00000);

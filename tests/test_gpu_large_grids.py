@@ -131,6 +131,7 @@ def test_bf16_backward_over_long_rows(fr):
     a load, and dW spans 2^20 vocabulary blocks.  W is zero but for 96 rows, so that the oracle is short.
     1e-2 is the bar of bf16 gradients."""
     d, V, T = 8, 307_000_000, 10
+    torch.cuda.empty_cache()  # (what earlier tests of the process left)
     if torch.cuda.mem_get_info()[0] < 220 << 30:
         pytest.skip("needs 190 GB")
     print(f"[large] bf16 V={V}", flush=True)
