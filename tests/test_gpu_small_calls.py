@@ -4,6 +4,8 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
+
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
@@ -265,3 +267,32 @@ def test_rows_that_are_not_finite_or_very_negative(fr, dtype, V):
         assert not torch.isfinite(got[bad]).any()
         assert (got[~bad] - want[~bad]).abs().max() < 2e-5
     assert _rel(call.dhidden[~bad.to(DEV)], dH[~bad]) < 1e-2
+
+
+@pytest.mark.parametrize("lens", [
+    (512, 3, 0, 255, 256, 257),       # 256 threads a sequence, up to two tokens a thread
+    (513, 3, 0, 1024, 1025),          # 1024 threads
+    (900,) + (2,) * 600,              # many short ones and a long one: 256
+])
+@pytest.mark.parametrize("algo", ["grpo", "gspo"])
+def test_loss_of_long_and_short_sequences(fr, lens, algo):
+    """The loss kernel's block sizes: loss, clip count and the log-probs' gradient through dhidden for
+    sequences around them (loss: float64 sums of float32 log-probs; dhidden: float32 GEMM)."""
+    d, V = 16, 40
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    T, S = int(off[-1]), len(lens)
+    H, W, y, z, lse, logp, _ = _problem(T, d, V, T, torch.float32)
+    old = (logp + 0.2 * torch.randn(T, generator=torch.Generator().manual_seed(7))).float()
+    adv = torch.linspace(-1.0, 1.5, S)
+    eps = float(np.float32(0.2))
+    loss, g, info = oracle.policy_loss(logp.numpy(), old.double().numpy(), None, off,
+                                       adv.double().numpy(), algo=algo, eps_low=eps, eps_high=eps)
+    dZ = -torch.from_numpy(g)[:, None] * torch.exp(z - lse[:, None])
+    dZ[torch.arange(T), y.long()] += torch.from_numpy(g)
+    call = fr.policy_loss_fwd_bwd(
+        H.to(DEV), W.to(DEV), y.to(DEV), old.to(DEV), torch.from_numpy(off).to(DEV),
+        torch.from_numpy(off), adv.to(DEV), algo=algo, need_dW=False)
+    torch.cuda.synchronize()
+    assert abs(call.loss.item() - loss) <= 1e-5  # (terms of order 1 and of both signs)
+    assert int(call.stats[0].item()) == info["clipped_tokens"]
+    assert _rel(call.dhidden, dZ @ W.double()) < 1e-5
