@@ -1209,23 +1209,28 @@ __global__ __launch_bounds__(256) void slab_prep_kernel(
   if (shift) shift[t] = 0.0f;
 }
 
-// partials -> lse, logp.  A block of 1024 threads handles 32 tokens in 32 slices of the vocabulary
-// blocks (slice s takes blocks s, s + 32, ..), combined through lane swaps and LDS.  Bound by the
-// latency of a thread's loads, four of each array in flight: at 193 tokens and V = 151936 four
-// wavefronts per 64 tokens walked 149 blocks each one by one in 73 us, 11 us so.
+// partials -> lse, logp.  A block handles 32 tokens in SLICES slices of the vocabulary blocks (slice s
+// takes blocks s, s + SLICES, ..), combined through lane swaps and LDS.  Bound by the latency of a
+// thread's loads, four of each array in flight: at 193 tokens and V = 151936 four wavefronts per 64
+// tokens walked 149 blocks each one by one in 73 us, with 32 slices 11 us.  Up to 64 vocabulary blocks
+// 8 slices do (most of 32 would be empty, and their wavefronts keep other tokens out): us, 8 / 32
+// slices, V = 1000 2500 tokens 3.1 / 4.0, 45000 4.5 / 7.5; V = 4096 45000 4.8 / 8.5; V = 10000 2500
+// 4.0 / 4.7, 20000 4.7 / 7.0; V = 32000 257 6.0 / 5.4, 20000 7.3 / 9.1; V = 100000 2500 13.3 / 7.7.
 //   rel == 0: psum = sum exp(z - pmax) per vocab block (log-prob only path)
 //   rel == 1: psum = sum exp(z - s_t); with check != 0 a row whose max is too far from s_t
 //             (exp(z - s_t) could leave float range) gets s_t = max and its token block is
 //             marked for a second evaluation (whose partials loss_kernel merges).
 constexpr int kMergeTok = 32;
-__global__ __launch_bounds__(1024) void merge_kernel(
+template <int SLICES>
+__global__ __launch_bounds__(32 * SLICES) void merge_kernel(
     const float* __restrict__ pmax, const float* __restrict__ psum,
     const float* __restrict__ psz, int64_t ldp, int32_t nmb, const float* __restrict__ zlab,
     const int32_t* __restrict__ yslab, int32_t Tc, int32_t rel, int32_t check,
     float* __restrict__ lse_out, float* __restrict__ logp_out, float* __restrict__ ent_out,
     float* __restrict__ shift, int32_t* __restrict__ redo_blk, int32_t* __restrict__ redo_count,
     int32_t* __restrict__ redo_any, int32_t block0) {
-  __shared__ float sm[16][kMergeTok], ss[16][kMergeTok], sz[16][kMergeTok];
+  constexpr int W = SLICES / 2;  // wavefronts
+  __shared__ float sm[W][kMergeTok], ss[W][kMergeTok], sz[W][kMergeTok];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int tok = lane & 31, slice = wv * 2 + (lane >> 5);
   const int t = (block0 + int(blockIdx.x)) * kMergeTok + tok;
@@ -1251,19 +1256,19 @@ __global__ __launch_bounds__(1024) void merge_kernel(
     }
   };
   if (ok) {
-    for (int b = slice; b < nmb; b += 128) {
+    for (int b = slice; b < nmb; b += 4 * SLICES) {
       float m[4], x[4], y[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const int64_t o = int64_t(b + 32 * u) * ldp + t;
-        const bool in = b + 32 * u < nmb;
+        const int64_t o = int64_t(b + SLICES * u) * ldp + t;
+        const bool in = b + SLICES * u < nmb;
         m[u] = in ? pmax[o] : 0.0f;
         x[u] = in ? psum[o] : 0.0f;
         y[u] = in && ent ? psz[o] : 0.0f;
       }
 #pragma unroll
       for (int u = 0; u < 4; ++u)
-        if (b + 32 * u < nmb) add(m[u], x[u], y[u]);
+        if (b + SLICES * u < nmb) add(m[u], x[u], y[u]);
     }
   }
   // slices without a block hold (-inf, 0, 0) and add nothing
@@ -1285,7 +1290,7 @@ __global__ __launch_bounds__(1024) void merge_kernel(
   S = ss[0][tok];
   Z = sz[0][tok];
 #pragma unroll
-  for (int w = 1; w < 16; ++w) join(sm[w][tok], ss[w][tok], sz[w][tok]);
+  for (int w = 1; w < W; ++w) join(sm[w][tok], ss[w][tok], sz[w][tok]);
   const float s_t = (rel && shift) ? shift[t] : 0.0f;
   const float l = rel ? s_t + __logf(S) : M + __logf(S);
   const int y = yslab[t];
@@ -1855,8 +1860,10 @@ static int launch_merge(const float* pmax, const float* psum, const float* psz, 
                         float* lse, float* logp, float* ent, float* shift, int32_t* redo_blk,
                         int32_t* redo_count, int32_t* redo_any, hipStream_t stream) {
   const int64_t blocks = nb1d(Tc, kMergeTok);
+  const bool few = nmb <= 64;
   for (int64_t b = 0; b < blocks; b += kMaxBlocks) {
-    hipLaunchKernelGGL(merge_kernel, dim3(unsigned(std::min(blocks - b, kMaxBlocks))), dim3(1024), 0,
+    hipLaunchKernelGGL(few ? merge_kernel<8> : merge_kernel<32>,
+                       dim3(unsigned(std::min(blocks - b, kMaxBlocks))), dim3(few ? 256 : 1024), 0,
                        stream, pmax, psum, psz, ldp, nmb, zlab, yslab, Tc, rel ? 1 : 0, rel ? 1 : 0,
                        lse, logp, ent, shift, redo_blk, redo_count, redo_any, int32_t(b));
     FR_LAUNCHED();

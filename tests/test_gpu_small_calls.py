@@ -296,3 +296,20 @@ def test_loss_of_long_and_short_sequences(fr, lens, algo):
     assert abs(call.loss.item() - loss) <= 1e-5  # (terms of order 1 and of both signs)
     assert int(call.stats[0].item()) == info["clipped_tokens"]
     assert _rel(call.dhidden, dZ @ W.double()) < 1e-5
+
+
+@pytest.mark.parametrize("V", [16384, 16385])  # 64 vocabulary blocks, 65: 8 slices, 32
+@pytest.mark.parametrize("T", [31, 33])        # around a block's 32 tokens
+def test_merge_slices(fr, V, T):
+    """Log-probs and entropy through both forms of the merge (2e-5: as in test_logits_tiles)."""
+    d = 24
+    H, W, y, z, lse, logp, old = _problem(T, d, V, V + T, torch.float32)
+    lp, ls = fr.token_logprob(H.to(DEV), W.to(DEV), y.to(DEV))
+    off = torch.tensor([0, T])
+    call = fr.policy_loss_fwd_bwd(
+        H.to(DEV), W.to(DEV), y.to(DEV), old.to(DEV), off.to(DEV), off, torch.ones(1, device=DEV),
+        need_dW=False, need_entropy=True)
+    torch.cuda.synchronize()
+    ent = lse - (torch.exp(z - lse[:, None]) * z).sum(1)
+    for got, want in ((lp, logp), (call.logp, logp), (ls, lse), (call.lse, lse), (call.entropy, ent)):
+        assert (got.double().cpu() - want).abs().max() < 2e-5
